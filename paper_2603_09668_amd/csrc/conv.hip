@@ -49,14 +49,9 @@ __device__ __forceinline__ float silu_grad(float z) {
   return sg * (1.0f + z * (1.0f - sg));
 }
 
-constexpr int CT_X = 16, CT_Y = 4, CT_Z = 4;              // output voxels per workgroup tile
-constexpr int PX = CT_X + 2, PY = CT_Y + 2, PZ = CT_Z + 2;  // staged input patch
-
 struct ConvGeom {
   int B, nx, ny, nz;
   int64_t L;  // voxels per field
-  int tiles_x, tiles_y, tiles_z;
-  int64_t n_tiles;
 };
 
 // ----------------------------------------------------------------- forward
@@ -539,136 +534,295 @@ __global__ void k_conv_pack(const float *__restrict__ w, int cin, int cout, int 
   wk[q] = f2bf(val);
 }
 
-// Weight gradient of one layer on MFMA:
+// Weight and bias gradient of one layer on MFMA:
 //   dW[tap][co][ci] = sum over voxels v of dz[v][co] * x[v + off(tap)][ci]
-// (x zero-padded), M = co, K = 32 voxels per MFMA (two rows of 16), N =
-// (dz, dy, ci) of one x-shift dx.  Per tile the output gradient is staged
-// transposed as [co][256 voxels] and, once per dx, the input patch transposed
-// and shifted as [ci][z][y][16 x], so every fragment is one aligned 16-byte
-// LDS read.  Each wave owns a fixed quarter of the (dx, n-tile, m-tile)
-// combinations and accumulates it over all its tiles; the workgroup's partial
-// sums go to part[block][27][COUTP][CINP] and conv_wgrad_reduce adds the
-// blocks in a fixed order.
-template <int CINP, int COUTP>
-__global__ __launch_bounds__(256) void k_conv_wgrad(ConvGeom G, const uint16_t *__restrict__ x,
-                                                    const uint16_t *__restrict__ dz, int zs, int cout,
-                                                    float *__restrict__ part) {
-  constexpr int MT = COUTP / 16;
-  constexpr int NPASS = 9 * CINP;                // n extent per dx pass
-  constexpr int NT = (NPASS + 15) / 16;          // n tiles per pass
-  constexpr int QP = NT * MT;                    // combinations per pass
-  constexpr int NQ = (3 * QP + 3) / 4;           // accumulators per wave
-  __shared__ __attribute__((aligned(16))) uint16_t s_dz[COUTP * 256];
-  __shared__ __attribute__((aligned(16))) uint16_t s_x[CINP * PZ * PY * 16];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int g = lane >> 4, r16 = lane & 15;
-  floatx4 acc[NQ];
+// (x zero-padded), dB[co] = sum over v of dz[v][co]: K = 32 voxels per MFMA,
+// 16 along x of two z planes.  Both operands need their channels' voxels
+// side by side while the fields are channels-last, so the fragments are read
+// from LDS with the transposing read (ds_read_b64_tr_b16: 16 lanes read 4
+// voxels of 16 channels, lane i receives the 4 voxels of channel i); no
+// transposed copy is made anywhere.
+//
+// A workgroup (8 waves, one per CU for the 32 -> 32 layer) walks columns of
+// 16 (x) x 4 (z) voxels along y.  A stage holds WG_Y rows of the column: x
+// with a halo of one plane on either side in z, dz with a halo of one voxel
+// on either side in x.  Shifting dz rather than x along x leaves the x
+// fragments the same for the three dx taps, and each x row fragment stays in
+// registers for the three rows of dz that use it: a step reads 3 + 3
+// fragments for its 27 MFMAs.  Stages are copied into a ring of NBUF LDS
+// buffers with buffer_load ... lds, NBUF - 1 stages ahead, across item
+// boundaries, with one barrier per stage.  A wave owns 16 output x 16 input
+// channels of one z pair, all 27 taps in registers; 3-channel fields (padded
+// to 8) pack two z taps (x) or two x taps (dz) into one 16-wide operand.  The
+// waves whose operand holds the unshifted dz take the bias gradient with one
+// more MFMA against ones.  The z pairs are added in LDS, the workgroup's sums
+// go to part[block], and k_conv_wgrad_reduce adds the blocks in a fixed
+// order (bit-reproducible).
+// Bound by the matrix cores and, behind them, by the 200 bytes read per
+// voxel.  32 -> 32 at 16 x 64^3 voxels: 253 us for the whole call (950
+// TFLOP/s in the kernel) against 5,898 us for a form that transposed each
+// tile into LDS with 2-byte stores and summed the bias in a pass of its own;
+// 3 -> 32 93 us (1,941), 32 -> 3 107 us (3,437); 1 x 64^3: 37, 23 and 23 us
+// (574, 321, 432).
+constexpr int WG_X = 16, WG_Z = 4, WG_Y = 3;
+constexpr int WG_THREADS = 512;
+
+struct WgPlan {
+  int nx, ny, nz;
+  int tx, tz, ncol;  // column tiles in x and z, columns over the batch
+  int ylen, nitems;  // rows of a work item, items = columns x y segments
+  int64_t L;
+  int cin, cout;
+};
+
+// one 16-byte chunk per lane from `off` of the buffer into LDS at `lds` +
+// 16 lane; completion is counted in vmcnt only.  Written in assembly because
+// the compiler cannot tell which LDS bytes the copy writes and would wait
+// for it (and for every store before it) ahead of the next LDS read.  The
+// caller waits (s_waitcnt vmcnt) and passes a barrier before reading.  m0 is
+// set here and used by nothing else in these kernels.
+__device__ __forceinline__ void copy_to_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t lds, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(off), "s"(rsrc)
+               : "memory");
+}
+
+typedef __attribute__((address_space(3))) char *lds_bytes_t;
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) bf16x4 *lds_bf16x4_t;
+
+// MFMA operand fragment of 8 voxels per lane: two transposing reads, the
+// second `step` bytes (4 voxels) on
+__device__ __forceinline__ bf16x8 read_tr(lds_bytes_t p, int step) {
+  const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t)p);
+  const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t)(p + step));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+template <int CINP, int ZS>
+struct WgShape {
+  static constexpr int XV = CINP / 8, ZV = ZS / 8;                            // 16-byte chunks per voxel
+  static constexpr int NXC = WG_Y * (WG_Z + 2) * WG_X * XV;                   // chunks per stage
+  static constexpr int NZC = WG_Y * WG_Z * (WG_X + 2) * ZV;
+  static constexpr int XW = (NXC + 63) / 64, ZW = (NZC + 63) / 64;            // copies of one wave
+  static constexpr int NL = (XW + ZW + WG_THREADS / 64 - 1) / (WG_THREADS / 64);  // copies per wave and stage
+  // LDS buffers: 131 KB for 32 -> 32 (one workgroup per CU), two workgroups per CU for the others
+  static constexpr int NBUF = CINP == 32 && ZS == 8 ? 3 : 4;
+  static constexpr int XBYTES = XW * 1024, STAGE = XBYTES + ZW * 1024;
+  static constexpr int NA = ZS == 32 ? 3 : 1;                                 // dz operands of a step (x shifts)
+  static constexpr int NB = CINP == 32 ? 3 : 1;                               // x operands of a row (z taps)
+  static constexpr int NACC = NA * 3 * NB + 1;                                // and the bias
+  // one more 1 KB slot takes the copies that even out the waves' counts
+  static constexpr int LDS = NBUF * STAGE + 1024;
+  static_assert(LDS >= 4 * NACC * 1024, "the z pairs are added in the stage buffers");
+};
+
+template <int CINP, int ZS>
+__global__ __launch_bounds__(WG_THREADS, 2) void k_conv_wgrad(WgPlan P, const uint16_t *__restrict__ x,
+                                                              const uint16_t *__restrict__ dz,
+                                                              float *__restrict__ part) {
+  using S = WgShape<CINP, ZS>;
+  __shared__ __attribute__((aligned(1024))) char s_buf[S::LDS];
+  const lds_bytes_t lds0 = (lds_bytes_t)s_buf;
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = (int)gridDim.x;
+  // neighbouring columns to the workgroups of one XCD (dispatch is round-robin)
+  const int v0 = (nb & 7) ? (int)blockIdx.x : ((int)blockIdx.x & 7) * (nb >> 3) + ((int)blockIdx.x >> 3);
+  const uint32_t lds_base = (uint32_t)(uintptr_t)lds0;
+
+  // -- copies: the cursor runs S::NBUF - 1 stages ahead of the computation
+  int iv = v0, ist = 0;                     // item and stage of the next copies
+  int ib = 0, iy0 = 0, iys = 0, iye = 0;    // its field, first x row, dz row range
+  int inst = 0, ibuf = 0;
+  uint32_t ioff[S::NL];                     // byte offset of the lane's chunk at row 0 of the field
+  bool iin[S::NL];                          // inside the field in x and z
+  auto begin_item = [&]() {
+    const int col = iv % P.ncol, seg = iv / P.ncol;
+    const int x0 = (col % P.tx) * WG_X, r = col / P.tx;
+    const int z0 = (r % P.tz) * WG_Z;
+    ib = r / P.tz;
+    iys = seg * P.ylen;
+    iye = min(P.ny, iys + P.ylen);
+    inst = (iye - iys + 2 + WG_Y - 1) / WG_Y;
 #pragma unroll
-  for (int a = 0; a < NQ; ++a) acc[a] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int64_t t = blockIdx.x; t < G.n_tiles; t += gridDim.x) {
-    int tx = (int)(t % G.tiles_x);
-    int ty = (int)((t / G.tiles_x) % G.tiles_y);
-    int64_t r = t / ((int64_t)G.tiles_x * G.tiles_y);
-    int tz = (int)(r % G.tiles_z);
-    int b = (int)(r / G.tiles_z);
-    int x0 = tx * CT_X, y0 = ty * CT_Y, z0 = tz * CT_Z;
-    __syncthreads();
-    for (int q = threadIdx.x; q < COUTP * 256; q += blockDim.x) {
-      int v = q % 256, co = q / 256;
-      int row = v / 16, xx = v % 16;
-      int gx = x0 + xx, gy = y0 + row % CT_Y, gz = z0 + row / CT_Y;
-      bool in = co < cout && gx < G.nx && gy < G.ny && gz < G.nz;
-      int64_t gv = (int64_t)b * G.L + gx + (int64_t)G.nx * (gy + (int64_t)G.ny * gz);
-      s_dz[q] = in ? dz[gv * zs + co] : (uint16_t)0;
-    }
-#pragma unroll 1
-    for (int dx = 0; dx < 3; ++dx) {
-      __syncthreads();
-      for (int q = threadIdx.x; q < CINP * PZ * PY * 16; q += blockDim.x) {
-        int xx = q % 16, yy = (q / 16) % PY, zz = (q / (16 * PY)) % PZ, ci = q / (16 * PY * PZ);
-        int gx = x0 - 1 + dx + xx, gy = y0 - 1 + yy, gz = z0 - 1 + zz;
-        uint16_t val = 0;
-        if (gx >= 0 && gy >= 0 && gz >= 0 && gx < G.nx && gy < G.ny && gz < G.nz)
-          val = x[((int64_t)b * G.L + gx + (int64_t)G.nx * (gy + (int64_t)G.ny * gz)) * CINP + ci];
-        s_x[q] = val;
+    for (int k = 0; k < S::NL; ++k) {
+      const int w = wid + k * (WG_THREADS / 64);
+      if (w < S::XW) {
+        const int q = w * 64 + lane, v = q / S::XV, c = q % S::XV;
+        const int gx = x0 + v % WG_X, gz = z0 - 1 + (v / WG_X) % (WG_Z + 2);
+        iin[k] = q < S::NXC && gx < P.nx && gz >= 0 && gz < P.nz;
+        ioff[k] = (uint32_t)((gx + P.nx * P.ny * gz) * (CINP * 2) + c * 16);
+      } else {
+        const int q = (w - S::XW) * 64 + lane, v = q / S::ZV, c = q % S::ZV;
+        const int gx = x0 - 1 + v % (WG_X + 2), gz = z0 + (v / (WG_X + 2)) % WG_Z;
+        iin[k] = q < S::NZC && gx >= 0 && gx < P.nx && gz < P.nz;
+        ioff[k] = (uint32_t)((gx + P.nx * P.ny * gz) * (ZS * 2) + c * 16);
       }
+    }
+  };
+  auto issue = [&]() {
+    const bool live = iv < P.nitems;  // past the last item: copies of zeros, so every stage counts the same
+    if (live && ist == 0) begin_item();
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)(x + (int64_t)ib * P.L * CINP), (short)0,
+                                                                        (int)(P.L * CINP * 2), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc((void *)(dz + (int64_t)ib * P.L * ZS), (short)0,
+                                                                        (int)(P.L * ZS * 2), 0x00020000);
+#pragma unroll
+    for (int k = 0; k < S::NL; ++k) {
+      const int w = wid + k * (WG_THREADS / 64);
+      if (w < S::XW) {
+        const int row = (w * 64 + lane) / (S::XV * WG_X * (WG_Z + 2));
+        const int gy = iys - 1 + ist * WG_Y + row;
+        const bool in = live && iin[k] && gy >= 0 && gy < P.ny;
+        copy_to_lds(rx, lds_base + ibuf * S::STAGE + w * 1024,
+                    in ? ioff[k] + (uint32_t)(gy * P.nx * (CINP * 2)) : 0x80000000u);
+      } else {
+        // step t of the item takes x row iys - 1 + t and dz row iys - 2 + t
+        const int row = ((w - S::XW) * 64 + lane) / (S::ZV * (WG_X + 2) * WG_Z);
+        const int gy = iys - 2 + ist * WG_Y + row;
+        const bool in = live && iin[k] && gy >= iys && gy < iye;
+        const uint32_t dst = w < S::XW + S::ZW ? ibuf * S::STAGE + w * 1024 : S::NBUF * S::STAGE;
+        copy_to_lds(rz, lds_base + dst, in ? ioff[k] + (uint32_t)(gy * P.nx * (ZS * 2)) : 0x80000000u);
+      }
+    }
+    ibuf = ibuf + 1 == S::NBUF ? 0 : ibuf + 1;
+    if (live && ++ist == inst) {
+      ist = 0;
+      iv += nb;
+    }
+  };
+
+  // -- this wave's fragments.  Lane l: voxels 8 ((l >> 4) & 1) .. + 8 along x
+  // of plane (l >> 5) of the z pair; it reads voxel (l & 15) >> 2 of a group of 4
+  const int zp = wid >> 2, qa = wid & 1, qb = (wid >> 1) & 1;
+  const int l16 = lane & 15, c4 = l16 & 3;
+  const int vox = 8 * ((lane >> 4) & 1) + (l16 >> 2), zr = 2 * zp + (lane >> 5);
+  int xa, za[S::NA];
+  if (CINP == 32) xa = (zr * WG_X + vox) * 64 + (16 * qb + 4 * c4) * 2;
+  else xa = ((zr + min(2 * qb + (c4 >> 1), 2)) * WG_X + vox) * 16 + (c4 & 1) * 8;  // two z taps side by side
+#pragma unroll
+  for (int a = 0; a < S::NA; ++a) {
+    // tap dx pairs x at p with dz at p + 1 - dx; dz is staged from x0 - 1
+    if (ZS == 32) za[a] = S::XBYTES + (zr * (WG_X + 2) + vox + 2 - a) * 64 + (16 * qa + 4 * c4) * 2;
+    else za[a] = S::XBYTES + (zr * (WG_X + 2) + vox + 2 - min(2 * qa + (c4 >> 1), 2)) * 16 + (c4 & 1) * 8;
+  }
+  const bool bias_wave = qb == 0 && (ZS == 32 || qa == 0);
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+  floatx4 acc[S::NACC];
+#pragma unroll
+  for (int a = 0; a < S::NACC; ++a) acc[a] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  for (int k = 0; k < S::NBUF - 1; ++k) issue();
+  bf16x8 xf[3][S::NB];
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+#pragma unroll
+    for (int k = 0; k < S::NB; ++k) xf[d][k] = bf16x8{};
+  int buf = 0;
+  for (int v = v0; v < P.nitems; v += nb) {
+    const int ys = (v / P.ncol) * P.ylen;
+    const int nsteps = min(P.ny, ys + P.ylen) - ys + 2;
+    for (int t0 = 0; t0 < nsteps; t0 += WG_Y) {
+      // this wave's copies of the stage have landed (the later stages' may be
+      // in flight), then every wave's have, and every wave is done with the
+      // stage before, whose buffer takes the next copies
+      __builtin_amdgcn_s_waitcnt(0x0f70 | ((S::NBUF - 2) * S::NL));
       __syncthreads();
+      issue();
+      const lds_bytes_t st = lds0 + buf * S::STAGE;
+      buf = buf + 1 == S::NBUF ? 0 : buf + 1;
 #pragma unroll
-      for (int a = 0; a < NQ; ++a) {
-        int qg = a * 4 + wid;
-        if (qg >= 3 * QP || qg / QP != dx) continue;
-        int qq = qg % QP;
-        int mt = qq % MT, nt = qq / MT;
-        int n = nt * 16 + r16;
-        bool nlive = n < NPASS;
-        int dzdy = nlive ? n / CINP : 0, ci = nlive ? n % CINP : 0;
-        int ddz = dzdy / 3, ddy = dzdy % 3;
+      for (int r = 0; r < WG_Y; ++r) {
+        static_assert(WG_Y == 3, "the x row of step r stays in register slot r");
+        const int t = t0 + r;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-          int row = 2 * ks + (g >> 1), xo = 8 * (g & 1);
-          bf16x8 af = *reinterpret_cast<const bf16x8 *>(s_dz + (mt * 16 + r16) * 256 + row * 16 + xo);
-          int rz = row / CT_Y, ry = row % CT_Y;
-          bf16x8 bfr = *reinterpret_cast<const bf16x8 *>(s_x + ((ci * PZ + rz + ddz) * PY + ry + ddy) * 16 + xo);
-          if (!nlive) bfr = bf16x8{};
-          acc[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr, acc[a], 0, 0, 0);
-        }
+        for (int k = 0; k < S::NB; ++k)
+          xf[r][k] = read_tr(st + xa + (r * (WG_Z + 2) + k) * WG_X * CINP * 2, 4 * CINP * 2);
+        if (t < 2 || t >= nsteps) continue;  // no dz row (uniform)
+        bf16x8 zf[S::NA];
+#pragma unroll
+        for (int a = 0; a < S::NA; ++a) zf[a] = read_tr(st + za[a] + r * WG_Z * (WG_X + 2) * ZS * 2, 4 * ZS * 2);
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+          for (int a = 0; a < S::NA; ++a)
+#pragma unroll
+            for (int k = 0; k < S::NB; ++k) {
+              floatx4 &d = acc[(a * 3 + dy) * S::NB + k];
+              d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf[a], xf[(r + 1 + dy) % 3][k], d, 0, 0, 0);
+            }
+        if (bias_wave)
+          acc[S::NACC - 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf[S::NA == 3 ? 1 : 0], ones, acc[S::NACC - 1], 0,
+                                                                     0, 0);
       }
     }
   }
-  // lane holds D[co = mt*16 + 4g + j][n = nt*16 + r16]
+  // add the z pairs: the copies still in flight land first
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  __syncthreads();
+  float4 *s_acc = reinterpret_cast<float4 *>(s_buf);
+  if (zp == 1) {
 #pragma unroll
-  for (int a = 0; a < NQ; ++a) {
-    int qg = a * 4 + wid;
-    if (qg >= 3 * QP) continue;
-    int dx = qg / QP, qq = qg % QP;
-    int mt = qq % MT, nt = qq / MT;
-    int n = nt * 16 + r16;
-    if (n >= NPASS) continue;
-    int dzdy = n / CINP, ci = n % CINP;
-    int tap = (dzdy / 3) * 9 + (dzdy % 3) * 3 + dx;
+    for (int a = 0; a < S::NACC; ++a)
+      s_acc[((wid & 3) * S::NACC + a) * 64 + lane] = make_float4(acc[a][0], acc[a][1], acc[a][2], acc[a][3]);
+  }
+  __syncthreads();
+  if (zp == 1) return;
+  // lane holds D[m = 4 (l / 16) + j][n = l % 16]
+  const int count = 27 * P.cin * P.cout + P.cout;
+  float *out = part + (int64_t)blockIdx.x * count;
+#pragma unroll
+  for (int a = 0; a < S::NACC; ++a) {
+    const float4 o = s_acc[((wid & 3) * S::NACC + a) * 64 + lane];
+    const float sum[4] = {acc[a][0] + o.x, acc[a][1] + o.y, acc[a][2] + o.z, acc[a][3] + o.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      int co = mt * 16 + 4 * g + j;
-      part[(((int64_t)blockIdx.x * 27 + tap) * COUTP + co) * CINP + ci] = acc[a][j];
+      const int m = 4 * (lane >> 4) + j;
+      const int co = ZS == 32 ? 16 * qa + m : (m & 7);
+      if (a == S::NACC - 1) {
+        // 8-channel dz: rows 8 .. 15 hold the unshifted tap
+        if (bias_wave && l16 == 0 && co < P.cout && (ZS == 32 || m >= 8)) out[27 * P.cin * P.cout + co] = sum[j];
+        continue;
+      }
+      const int dy = (a / S::NB) % 3;
+      const int dx = ZS == 32 ? a / (3 * S::NB) : 2 * qa + (m >> 3);
+      const int ci = CINP == 32 ? 16 * qb + l16 : (l16 & 7);
+      const int dzt = CINP == 32 ? a % S::NB : 2 * qb + (l16 >> 3);
+      if (co < P.cout && ci < P.cin && dx < 3 && dzt < 3)
+        out[((9 * dzt + 3 * dy + dx) * P.cout + co) * P.cin + ci] = sum[j];
     }
   }
 }
 
-// dW[co][ci][tap] (+)= sum over blocks of part[block][tap][co][ci], fixed order
-__global__ void k_conv_wgrad_reduce(const float *__restrict__ part, int nblocks, int cinp, int coutp, int cin,
-                                    int cout, float *__restrict__ dw, int accumulate) {
-  int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= cout * cin * 27) return;
-  int tap = q % 27, ci = (q / 27) % cin, co = q / (27 * cin);
+// dW[co][ci][tap] (+)= sum over blocks of part[block][tap][co][ci], and the
+// bias gradient behind it: 64 entries per workgroup, four threads per entry
+// over every fourth block (coalesced), their sums added in order.
+__global__ __launch_bounds__(256) void k_conv_wgrad_reduce(const float *__restrict__ part, int nblocks, int cin,
+                                                           int cout, float *__restrict__ dw, float *__restrict__ db,
+                                                           int accumulate) {
+  __shared__ float s_p[4][64];
+  const int nw = 27 * cin * cout, count = nw + cout;
+  const int e = threadIdx.x & 63, k0 = threadIdx.x >> 6;
+  const int q = blockIdx.x * 64 + e;
   float s = 0.f;
-  for (int k = 0; k < nblocks; ++k) s += part[(((int64_t)k * 27 + tap) * coutp + co) * cinp + ci];
-  dw[q] = accumulate ? dw[q] + s : s;
-}
-
-// bias gradient: db[c] = sum over voxels of dz[v][c], per-block partials
-__global__ __launch_bounds__(256) void k_bias_grad(const uint16_t *__restrict__ dz, int64_t nvox, int zs, int c,
-                                                   float *__restrict__ part) {
-  __shared__ float red[256];
-  int ch = threadIdx.x % 32, ph = threadIdx.x / 32;
-  float s = 0.f;
-  if (ch < c)
-    for (int64_t v = (int64_t)blockIdx.x * 8 + ph; v < nvox; v += (int64_t)gridDim.x * 8) s += bf2f(dz[v * zs + ch]);
-  red[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x < 32) {
-    float t = 0.f;
-    for (int k = 0; k < 8; ++k) t += red[k * 32 + threadIdx.x];
-    part[blockIdx.x * 32 + threadIdx.x] = t;
+  if (q < count) {
+#pragma unroll 8
+    for (int k = k0; k < nblocks; k += 4) s += part[(int64_t)k * count + q];
   }
-}
-
-__global__ void k_bias_grad_reduce(const float *__restrict__ part, int nblocks, int c, float *__restrict__ db,
-                                   int accumulate) {
-  int q = threadIdx.x;
-  if (q >= c) return;
-  float s = 0.f;
-  for (int k = 0; k < nblocks; ++k) s += part[k * 32 + q];
-  db[q] = accumulate ? db[q] + s : s;
+  s_p[k0][e] = s;
+  __syncthreads();
+  if (k0 != 0 || q >= count) return;
+  s = (s_p[0][e] + s_p[1][e]) + (s_p[2][e] + s_p[3][e]);
+  float *dst;
+  if (q < nw) {
+    const int ci = q % cin, co = (q / cin) % cout, tap = q / (cin * cout);
+    dst = dw + (co * cin + ci) * 27 + tap;
+  } else {
+    if (!db) return;
+    dst = db + (q - nw);
+  }
+  *dst = accumulate ? *dst + s : s;
 }
 
 // Loss L = mean over b, c, v of ((u_out - u_tgt) / s_b)^2 and its gradient
@@ -864,10 +1018,6 @@ static int make_geom(int B, int nx, int ny, int nz, ConvGeom *G) {
   // byte offsets within one field's 32-channel activations fit 31 bits
   DW_REQUIRE(G->L * 64 < ((int64_t)1 << 31), DW_ERANGE, "conv: field too large (at most 2^25 voxels)");
   DW_REQUIRE(G->L * B < ((int64_t)1 << 31), DW_ERANGE, "conv: batch too large (at most 2^31 voxels)");
-  G->tiles_x = (nx + CT_X - 1) / CT_X;  // edge tiles may be partial
-  G->tiles_y = (ny + CT_Y - 1) / CT_Y;
-  G->tiles_z = (nz + CT_Z - 1) / CT_Z;
-  G->n_tiles = (int64_t)G->tiles_x * G->tiles_y * G->tiles_z * B;
   return DW_OK;
 }
 
@@ -971,6 +1121,37 @@ extern "C" size_t conv_wgrad_scratch_floats(void) {
   return (size_t)WGRAD_BLOCKS * 27 * 32 * 32 + (size_t)BGRAD_BLOCKS * 32;
 }
 
+// Work items of the weight gradient: columns cut into y segments.  Every
+// item reads two rows beyond its own and the last workgroups of an uneven
+// division run alone, so the segment count is the one with the least rows on
+// the busiest workgroup.
+static WgPlan wgrad_plan(const ConvGeom &G, int cin, int cout, int blocks) {
+  WgPlan P;
+  P.nx = G.nx;
+  P.ny = G.ny;
+  P.nz = G.nz;
+  P.L = G.L;
+  P.cin = cin;
+  P.cout = cout;
+  P.tx = (G.nx + WG_X - 1) / WG_X;
+  P.tz = (G.nz + WG_Z - 1) / WG_Z;
+  P.ncol = P.tx * P.tz * G.B;
+  int64_t best = INT64_MAX;
+  P.ylen = G.ny;
+  for (int segs = 1; segs <= (G.ny + 3) / 4; ++segs) {
+    const int len = (G.ny + segs - 1) / segs;
+    const int64_t items = (int64_t)P.ncol * ((G.ny + len - 1) / len);
+    const int64_t rows = (items + blocks - 1) / blocks * (len + 2);
+    if (rows < best) {
+      best = rows;
+      P.ylen = len;
+    }
+    if (items >= 8 * (int64_t)blocks) break;
+  }
+  P.nitems = P.ncol * ((G.ny + P.ylen - 1) / P.ylen);
+  return P;
+}
+
 extern "C" int conv3d_bf16_wgrad(int B, int nx, int ny, int nz, int cin, int cout, const uint16_t *x,
                                  const uint16_t *dz, float *dw, float *db, int accumulate, float *scratch,
                                  void *stream) {
@@ -979,24 +1160,21 @@ extern "C" int conv3d_bf16_wgrad(int B, int nx, int ny, int nz, int cin, int cou
   if (rc) return rc;
   DW_REQUIRE(x && dz && dw && scratch, DW_EINVAL, "conv3d_bf16_wgrad: NULL pointer");
   DW_REQUIRE((cin == 3 || cin == 32) && (cout == 3 || cout == 32), DW_EINVAL, "conv3d_bf16_wgrad: channels");
-  hipStream_t s = (hipStream_t)stream;
-  int cinp = cin == 3 ? 8 : 32, coutp = cout == 3 ? 16 : 32, zs = cout == 3 ? 8 : 32;
-  unsigned nb = (unsigned)(G.n_tiles < WGRAD_BLOCKS ? G.n_tiles : WGRAD_BLOCKS);
-  if (cinp == 8 && coutp == 32)
-    hipLaunchKernelGGL((k_conv_wgrad<8, 32>), dim3(nb), dim3(256), 0, s, G, x, dz, zs, cout, scratch);
-  else if (cinp == 32 && coutp == 32)
-    hipLaunchKernelGGL((k_conv_wgrad<32, 32>), dim3(nb), dim3(256), 0, s, G, x, dz, zs, cout, scratch);
-  else if (cinp == 32 && coutp == 16)
-    hipLaunchKernelGGL((k_conv_wgrad<32, 16>), dim3(nb), dim3(256), 0, s, G, x, dz, zs, cout, scratch);
-  else
+  if (cin == 3 && cout == 3)
     return set_error(DW_EINVAL, "conv3d_bf16_wgrad: unsupported layer %d -> %d", cin, cout);
-  hipLaunchKernelGGL(k_conv_wgrad_reduce, dim3(grid_blocks((int64_t)cout * cin * 27, 256)), dim3(256), 0, s,
-                     scratch, (int)nb, cinp, coutp, cin, cout, dw, accumulate);
-  if (db) {
-    float *bpart = scratch + (size_t)WGRAD_BLOCKS * 27 * 32 * 32;
-    hipLaunchKernelGGL(k_bias_grad, dim3(BGRAD_BLOCKS), dim3(256), 0, s, dz, (int64_t)B * G.L, zs, cout, bpart);
-    hipLaunchKernelGGL(k_bias_grad_reduce, dim3(1), dim3(32), 0, s, bpart, BGRAD_BLOCKS, cout, db, accumulate);
-  }
+  hipStream_t s = (hipStream_t)stream;
+  // one workgroup per CU for 32 -> 32 (131 KB of LDS), two for the others
+  const int most = cin == 32 && cout == 32 ? 256 : 512;
+  const WgPlan P = wgrad_plan(G, cin, cout, most);
+  const int nb = P.nitems < most ? P.nitems : most;
+  if (cin == 3)
+    hipLaunchKernelGGL((k_conv_wgrad<8, 32>), dim3(nb), dim3(WG_THREADS), 0, s, P, x, dz, scratch);
+  else if (cout == 32)
+    hipLaunchKernelGGL((k_conv_wgrad<32, 32>), dim3(nb), dim3(WG_THREADS), 0, s, P, x, dz, scratch);
+  else
+    hipLaunchKernelGGL((k_conv_wgrad<32, 8>), dim3(nb), dim3(WG_THREADS), 0, s, P, x, dz, scratch);
+  hipLaunchKernelGGL(k_conv_wgrad_reduce, dim3(grid_blocks(27 * (int64_t)cin * cout + cout, 64)), dim3(256), 0, s,
+                     scratch, nb, cin, cout, dw, db, accumulate);
   return check_launch("conv3d_bf16_wgrad");
 }
 

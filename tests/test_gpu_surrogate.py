@@ -167,6 +167,26 @@ def test_weight_and_bias_gradient(dims, cin, cout):
     assert torch.equal(dw2, dw1)
 
 
+@pytest.mark.parametrize("dims", [(1, 15, 1, 3), (1, 17, 2, 5), (2, 16, 3, 4), (1, 33, 7, 9), (1, 16, 64, 4), (30, 18, 3, 33)])
+@pytest.mark.parametrize("cin,cout", [(3, 32), (32, 32), (32, 3)])
+def test_weight_gradient_tile_edges(dims, cin, cout):
+    """Columns of 16 x 4 voxels one short of, at and past a whole one, one to
+    three rows, a column cut into y segments, and more work items than
+    workgroups (the last size: 30 x 2 x 9 columns).  The bound is ACC of the
+    sum of absolute terms, as above."""
+    say(f"wgrad edges dims={dims} {cin}->{cout}")
+    rng = np.random.default_rng(sum(dims) + cin)
+    x, dz = _rand_act(rng, dims, cin), _rand_act(rng, dims, cout, 1e-2)
+    dw, db = torch.empty(cout, cin, 27, device=DEV), torch.empty(cout, device=DEV)
+    scratch = torch.full((api.conv_wgrad_scratch_floats(),), float("nan"), device=DEV)
+    api.conv3d_bf16_wgrad(dims, cin, cout, _to_dev_act(x, _cp(cin)), _to_dev_act(dz, _cp(cout)), dw, db, scratch)
+    wshape = (cout, cin, 3, 3, 3)
+    ref, a = (torch.nn.grad.conv3d_weight(p, wshape, q, padding=1).reshape(cout, cin, 27)
+              for p, q in ((x, dz), (x.abs(), dz.abs())))
+    _check("dW", dw.double().cpu(), ref, ACC * a + 1e-30)
+    _check("db", db.double().cpu(), dz.sum(dim=(0, 2, 3, 4)), ACC * dz.abs().sum(dim=(0, 2, 3, 4)) + 1e-30)
+
+
 def test_prep_input_and_mse_grad():
     say("prep input / mse grad")
     rng = np.random.default_rng(3)
