@@ -14,19 +14,18 @@
 //      writes one (tile, kernel) pair per covered tile, in depth order.
 //   4. stable radix sort of the pairs by tile (depth order kept inside a
 //      tile), then each tile's range in the sorted list.
-//   5. k_gs_raster: one 256-thread workgroup per tile, one pixel per thread;
-//      batches of 256 kernels staged in LDS, alpha blended front to back.
-//      A pixel stops once its transmittance falls below t_min; its count of
-//      blended list entries is kept for the reverse pass.
-// Reverse (gs_render_adj): the same traversal per pixel, front to back,
-// recomputing alpha and T; dC/dalpha_i = T_i c_i - (C - A_i) / (1 - alpha_i)
-// with A_i the colour blended up to and including i (C includes the
-// background term).  The reverse pass runs one wave per tile with four
-// pixels per lane: per-kernel adjoints of the centre, conic, opacity and
-// colour are summed over the lane's pixels, then over the wave with DPP
-// row operations, and added to global memory with one atomic per value;
-// k_gs_project_adj then takes the centre and conic adjoints back to mu and
-// Sigma through the projection.
+//   5. k_gs_classify: tiles whose lists are long and hold small kernels are
+//      rasterised by four workgroups, the others by one.
+//   6. k_gs_raster: batches of list entries staged in LDS, each wave keeps
+//      those whose pixel box meets its pixels and blends them front to back.
+//      A pixel stops once its transmittance falls below t_min; the list
+//      position it stopped at is kept for the reverse pass.
+// Reverse (gs_render_adj): front to back again, recomputing alpha and T, 16
+// entries x 4 pixels at a time.  With s_i = G . c_i (G the image gradient at
+// the pixel), dL/dalpha_i = T_i s_i - (G . C - P_i) / (1 - alpha_i) where
+// P_i = sum_{j <= i} T_j alpha_j s_j and C includes the background term.  The
+// sums over pixels run on the matrix cores; k_gs_project_adj takes the centre
+// and conic adjoints back to mu and Sigma through the projection.
 // Loss (render_loss): L1 and SSIM with an 11 x 11 Gaussian window
 // (sigma 1.5, zero padding) per channel; the five window sums are separable
 // convolutions staged in LDS; the gradient of the SSIM mean is the window
@@ -34,12 +33,18 @@
 // symmetric).  Loss partial sums are reduced in a fixed order.
 #include <hip/hip_runtime.h>
 
+#include <climits>
+
 #include "dw_internal.h"
 
 namespace dw {
 
 constexpr int GS_TILE = 16;
-constexpr int GS_THREADS = GS_TILE * GS_TILE;
+constexpr int GS_THREADS = 256;
+// per-kernel sums of the reverse pass, e = dL/dalpha exp(-q/2) summed over
+// pixels with the weights: [0..2] colour, [3] e, [4] e dx, [5] e dx^2,
+// [6] e dx dy, [7] e dy^2, [8] e dy
+constexpr int GS_NB = 9;
 constexpr int RS_THREADS = 256;
 constexpr int RS_ROUNDS = 16;
 constexpr int RS_CHUNK = RS_THREADS * RS_ROUNDS;  // keys per radix-sort block
@@ -49,7 +54,9 @@ constexpr int SCAN_CHUNK = SCAN_THREADS * SCAN_PER;
 constexpr int SCAN_TOP_THREADS = 1024;
 constexpr int SCAN_TOP_MAX = SCAN_TOP_THREADS * 16;  // block sums the top level scans
 
-// workspace header: [0] status, [1] pair count, [GS_CNT0 ...] 64 partial
+// workspace header: [0] status, [1] pair count, [2] tiles of one raster
+// workgroup, [3] tiles of four, [4] and [5] raster and reverse tickets, [6] a drawn kernel has a non-finite
+// colour, [GS_CNT0 ...] 64 partial
 // 64-bit pair totals (one per block residue, to spread the atomics)
 constexpr int GS_HDR_INTS = 256;
 constexpr int GS_CNT0 = 64;
@@ -65,14 +72,16 @@ struct CamDev {
 
 // Workspace of gs_render / gs_render_adj (all sections 256-aligned):
 //   header [256] int32: status, pair count, 64 partial pair totals (u64)
-//   rec [n] 3 float4: (mx, my, A, B), (C, o, c0, c1), (c2, -, -, -)
+//   rec [n] 3 float4: (mx, my, A, B), (C, o, c0, c1), (c2, pixel box, -),
+//   the box as two words of two 16-bit numbers: first | last << 16 in x, y
 //   rect [n] int4 tile box (tx0, tx1, ty0, ty1); cnt [n] int32
 //   key_a, key_b [n] u32, id_a, id_b [n] int32   (depth sort)
 //   off [n + 1] int32 (tile-count scan in depth order)
 //   pk_a, pk_b [P] u32, pv_a, pv_b [P] int32      (pair sort)
 //   hist [256 * nblk(max(n, P))] int32, bsum [SCAN_TOP_MAX] int32
-//   range [T] int2, last [W * H] int32
-//   gbar [5][n] float (centre and conic adjoints, reverse pass)
+//   range [T] int2, whole, split [T] int32 (tiles of one raster workgroup and
+//   of four), last [W * H] int32
+//   gbar [n][9] float (per-kernel sums of the reverse pass, GS_NB)
 struct GsWs {
   int32_t *hdr;
   float4 *rec;
@@ -85,6 +94,7 @@ struct GsWs {
   int32_t *pv_a, *pv_b;
   int32_t *hist, *bsum;
   int2 *range;
+  int32_t *whole, *split;
   int32_t *last;
   float *gbar;
   size_t bytes;
@@ -120,8 +130,10 @@ static GsWs gs_layout(char *base, int64_t n, int64_t P, int W, int H) {
   w.hist = (int32_t *)take((size_t)256 * nb * 4);
   w.bsum = (int32_t *)take((size_t)SCAN_TOP_MAX * 4);
   w.range = (int2 *)take((size_t)T * sizeof(int2));
+  w.whole = (int32_t *)take((size_t)T * 4);
+  w.split = (int32_t *)take((size_t)T * 4);
   w.last = (int32_t *)take((size_t)W * H * 4);
-  w.gbar = (float *)take((size_t)5 * n * 4);
+  w.gbar = (float *)take((size_t)GS_NB * n * 4);
   w.bytes = o;
   return w;
 }
@@ -136,6 +148,7 @@ struct Proj {
   float a, b, c;         // 2-D covariance [[a, b], [b, c]]
   float A, B, C;         // its inverse
   float T0[3], T1[3];    // rows of J R
+  int i0, i1, j0, j1;    // pixels where alpha can reach alpha_min
   int tx0, tx1, ty0, ty1;
 };
 
@@ -194,6 +207,10 @@ __device__ __forceinline__ Proj gs_proj(const CamDev &K, float mux, float muy, f
     j1 = (int)fminf(fy1, (float)(K.H - 1));
     if (i0 > i1 || j0 > j1) return r;
   }
+  r.i0 = i0;
+  r.i1 = i1;
+  r.j0 = j0;
+  r.j1 = j1;
   r.tx0 = i0 / GS_TILE;
   r.tx1 = i1 / GS_TILE;
   r.ty0 = j0 / GS_TILE;
@@ -224,9 +241,11 @@ __global__ __launch_bounds__(256) void k_gs_project(CamDev K, int n, const float
   if (r.drawn) {
     c = (r.tx1 - r.tx0 + 1) * (r.ty1 - r.ty0 + 1);
     key = __float_as_uint(r.pz);  // pz > near >= 0: the bits order like the values
+    if (!(isfinite(col[g]) && isfinite(col[(int64_t)n + g]) && isfinite(col[2 * (int64_t)n + g]))) atomicOr(&w.hdr[6], 1);
     w.rec[3 * (int64_t)g] = make_float4(r.mx, r.my, r.A, r.B);
     w.rec[3 * (int64_t)g + 1] = make_float4(r.C, o, col[g], col[(int64_t)n + g]);
-    w.rec[3 * (int64_t)g + 2] = make_float4(col[2 * (int64_t)n + g], 0.f, 0.f, 0.f);
+    w.rec[3 * (int64_t)g + 2] = make_float4(col[2 * (int64_t)n + g], __uint_as_float((uint32_t)r.i0 | (uint32_t)r.i1 << 16),
+                                            __uint_as_float((uint32_t)r.j0 | (uint32_t)r.j1 << 16), 0.f);
   }
   if (has) {
     w.rect[g] = make_int4(r.tx0, r.tx1, r.ty0, r.ty1);
@@ -588,61 +607,206 @@ struct GsRec {
   float mx, my, A, B, C, o, c0, c1, c2;
 };
 
-__device__ __forceinline__ GsRec load_rec(const float4 *rec, int g) {
-  const float4 a = rec[3 * (int64_t)g], b = rec[3 * (int64_t)g + 1], c = rec[3 * (int64_t)g + 2];
-  return GsRec{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, c.x};
-}
-
 // alpha of kernel r at pixel centre (x, y); the same expression in the
 // forward and reverse passes, so both take the same alpha_min decisions
-__device__ __forceinline__ float gs_alpha(const GsRec &r, float x, float y, float &dx, float &dy, float &e) {
-  dx = x - r.mx;
-  dy = y - r.my;
+__device__ __forceinline__ float gs_alpha(const GsRec &r, float x, float y, float &e) {
+  const float dx = x - r.mx;
+  const float dy = y - r.my;
   const float q = r.A * dx * dx + 2.0f * r.B * dx * dy + r.C * dy * dy;
   e = __expf(-0.5f * q);
   return r.o * e;
 }
 
-__global__ __launch_bounds__(GS_THREADS) void k_gs_raster(CamDev K, const int32_t *__restrict__ hdr,
-                                                         const int2 *__restrict__ range,
-                                                         const int32_t *__restrict__ pv, const float4 *__restrict__ rec,
-                                                         float *__restrict__ image, int32_t *__restrict__ last) {
-  __shared__ GsRec s_r[GS_THREADS];
-  if (gs_failed(hdr)) return;  // over capacity: the image is not written
-  const int tile = blockIdx.x;
-  const int tx = tile % K.tw, ty = tile / K.tw;
-  const int i = tx * GS_TILE + (threadIdx.x % GS_TILE), j = ty * GS_TILE + (threadIdx.x / GS_TILE);
+typedef float gs_floatx4 __attribute__((ext_vector_type(4)));
+
+template <int N>
+struct GsBatch {
+  float4 a[N];  // mx, my, A, B
+  float2 b[N];  // C, o
+  float4 rgb[N];
+  uint2 box[N];
+  // per wave: entries of the batch that meet its pixels
+  __attribute__((aligned(16))) uint8_t list[GS_THREADS / 64][N];
+};
+
+// The list of one tile, a batch of N at a time; with AHEAD the records of the
+// next batch and the ids of the one after are requested while a batch is
+// blended.  Without, the first batch is half a batch long and nothing but ids
+// is requested early: where large kernels cover a tile its pixels are opaque
+// after some hundred entries of a list of thousands.
+template <int N, bool AHEAD>
+struct GsFeed {
+  const int32_t *pv;
+  const float4 *rec;
+  int pos, len, end;  // list position and length of the batch to stage
+  int id, id_next;
+  gs_floatx4 r0, r1, r2;
+
+  __device__ __forceinline__ int entry(int p) { return (int)threadIdx.x < N && p < end ? pv[p] : 0; }
+  __device__ __forceinline__ void load_rec() {
+    // threads past the batch read kernel 0's record and do not store it
+    const gs_floatx4 *p = reinterpret_cast<const gs_floatx4 *>(rec + 3 * (int64_t)((int)threadIdx.x < len ? id : 0));
+    r0 = p[0];
+    r1 = p[1];
+    r2 = p[2];
+  }
+  __device__ __forceinline__ GsFeed(const int32_t *pv_, const float4 *rec_, int first, int end_)
+      : pv(pv_), rec(rec_), pos(first), end(end_) {
+    len = min(AHEAD ? N : N / 2, end - pos);
+    id = entry(pos + threadIdx.x);
+    id_next = entry(pos + len + threadIdx.x);
+    if (AHEAD) load_rec();
+  }
+  __device__ __forceinline__ bool more() const { return pos < end; }
+  // puts the batch into LDS
+  __device__ __forceinline__ void stage(GsBatch<N> &s, int *s_id) {
+    const int t = threadIdx.x;
+    if (!AHEAD) load_rec();
+    if (t < len) {
+      s.a[t] = make_float4(r0.x, r0.y, r0.z, r0.w);
+      s.b[t] = make_float2(r1.x, r1.y);
+      s.rgb[t] = make_float4(r1.z, r1.w, r2.x, 0.f);
+      s.box[t] = make_uint2(__float_as_uint(r2.y), __float_as_uint(r2.z));
+      if (s_id) s_id[t] = id;
+    }
+  }
+  // moves on to the next batch and requests what belongs to it
+  __device__ __forceinline__ void advance() {
+    pos += len;
+    len = min(N, end - pos);
+    id = id_next;
+    if (AHEAD) load_rec();
+    id_next = entry(pos + len + threadIdx.x);
+  }
+};
+
+// entries of the batch whose pixel box meets pixels [wx, wx + ext] x [wy, wy + ext],
+// in order, into the wave's list; returns their number.  hits (optional): the
+// mask of the entries taken, 64 to a word
+template <int N>
+__device__ __forceinline__ int gs_pick(GsBatch<N> &s, int wid, int lane, int n, int wx, int wy, int ext,
+                                       uint64_t *hits = nullptr) {
+  int cnt = 0;
+  for (int c = 0; c < n; c += 64) {
+    const int j = c + lane;
+    bool hit = false;
+    if (j < n) {
+      const uint2 b = s.box[j];
+      hit = (int)(b.x & 0xffffu) <= wx + ext && (int)(b.x >> 16) >= wx && (int)(b.y & 0xffffu) <= wy + ext &&
+            (int)(b.y >> 16) >= wy;
+    }
+    const uint64_t m = __ballot(hit);
+    if (hit) s.list[wid][cnt + __popcll(m & ((1ull << lane) - 1ull))] = (uint8_t)j;
+    if (hits && lane == 0) hits[c >> 6] = m;
+    cnt += __popcll(m);
+  }
+  __builtin_amdgcn_wave_barrier();  // other lanes of this wave read the list back (LDS is in order)
+  return cnt;
+}
+
+template <int N>
+__device__ __forceinline__ GsRec gs_entry(const GsBatch<N> &s, int j) {
+  const float4 a = s.a[j], c = s.rgb[j];
+  const float2 b = s.b[j];
+  return GsRec{a.x, a.y, a.z, a.w, b.x, b.y, c.x, c.y, c.z};
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float old, float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
+// Sorts the tiles into those that one workgroup rasterises and those that
+// four do (k_gs_raster says how): long lists of small kernels, judged by the
+// 4 x 4 pixel blocks of the tile that 16 entries from the list's first 1024
+// meet.  Four lanes per tile, one atomic per class and 64 tiles (an atomic
+// per tile took 53 us at 4096 tiles).  The order inside the lists does not
+// matter.
+constexpr int GS_SPLIT_LEN = 192, GS_SPLIT_BLOCKS = 6;
+
+__global__ __launch_bounds__(256) void k_gs_classify(CamDev K, GsWs w, const int32_t *__restrict__ pv) {
+  __shared__ int s_n[2], s_at[2];
+  if (gs_failed(w.hdr)) return;
+  const int tile = blockIdx.x * 64 + (threadIdx.x >> 2), sub = threadIdx.x & 3;
+  if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+  __syncthreads();
+  const bool has = tile < K.tw * K.th;
+  int len = 0, blocks = 0;
+  if (has) {
+    const int2 rg = w.range[tile];
+    len = rg.y - rg.x;
+    if (len > GS_SPLIT_LEN) {
+      const int X0 = (tile % K.tw) * GS_TILE, Y0 = (tile / K.tw) * GS_TILE;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float4 r2 = w.rec[3 * (int64_t)pv[rg.x + (4 * k + sub) * min(len, 1024) / 16] + 2];
+        const uint32_t bx = __float_as_uint(r2.y), by = __float_as_uint(r2.z);
+        const int nx = (min((int)(bx >> 16) - X0, GS_TILE - 1) >> 2) - (max((int)(bx & 0xffffu) - X0, 0) >> 2) + 1;
+        const int ny = (min((int)(by >> 16) - Y0, GS_TILE - 1) >> 2) - (max((int)(by & 0xffffu) - Y0, 0) >> 2) + 1;
+        blocks += nx * ny;
+      }
+    }
+  }
+  blocks += __shfl_xor(blocks, 1, 64);
+  blocks += __shfl_xor(blocks, 2, 64);
+  const int split = len > GS_SPLIT_LEN && blocks < 16 * GS_SPLIT_BLOCKS ? 1 : 0;
+  const int at = has && sub == 0 ? atomicAdd(&s_n[split], 1) : 0;
+  __syncthreads();
+  if (threadIdx.x < 2) s_at[threadIdx.x] = atomicAdd(&w.hdr[2 + threadIdx.x], s_n[threadIdx.x]);
+  __syncthreads();
+  if (has && sub == 0) (split ? w.split : w.whole)[s_at[split] + at] = tile;
+}
+
+// One workgroup per tile, a wave per 8 x 8 pixels, one pixel per lane.  The
+// four alphas of a step are independent and hide each other's latency, only
+// the blending is a chain.
+__device__ __forceinline__ void gs_raster_whole(const CamDev &K, GsBatch<GS_THREADS> &s, int tile, int2 rg,
+                                                const int32_t *__restrict__ pv, const float4 *__restrict__ rec,
+                                                float *__restrict__ image, int32_t *__restrict__ last) {
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wx = (tile % K.tw) * GS_TILE + 8 * (wid & 1), wy = (tile / K.tw) * GS_TILE + 8 * (wid >> 1);
+  const int i = wx + (lane & 7), j = wy + (lane >> 3);
   const bool inside = i < K.W && j < K.H;
   const float x = i + 0.5f, y = j + 0.5f;
-  const int2 rg = range[tile];
   float T = 1.f, c0 = 0.f, c1 = 0.f, c2 = 0.f;
-  int used = 0;
-  bool done = !inside;
-  for (int b = rg.x; b < rg.y; b += GS_THREADS) {
-    if (__syncthreads_count(!done) == 0) break;
-    const int nbatch = min(GS_THREADS, rg.y - b);
-    if ((int)threadIdx.x < nbatch) s_r[threadIdx.x] = load_rec(rec, pv[b + threadIdx.x]);
+  bool live = inside;
+  int used = rg.y - rg.x;
+  GsFeed<GS_THREADS, false> feed(pv, rec, rg.x, rg.y);
+  while (feed.more()) {
+    const bool done = __ballot(live) == 0ull;
+    if (__syncthreads_and(done)) break;
+    feed.stage(s, nullptr);
     __syncthreads();
+    const int first = feed.pos - rg.x;
     if (!done) {
-      for (int q = 0; q < nbatch; ++q) {
-        const GsRec r = s_r[q];
-        float dx, dy, e;
-        const float al = gs_alpha(r, x, y, dx, dy, e);
-        if (al >= K.amin) {
-          const float wgt = T * al;
-          c0 += wgt * r.c0;
-          c1 += wgt * r.c1;
-          c2 += wgt * r.c2;
-          T *= 1.0f - al;
+      const int cnt = gs_pick(s, wid, lane, feed.len, wx, wy, 7);
+      for (int q = 0; q < cnt; q += 4) {
+        const uint32_t four = __builtin_amdgcn_readfirstlane(*reinterpret_cast<const uint32_t *>(&s.list[wid][q]));
+        GsRec r[4];
+        float al[4], e;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          r[u] = gs_entry(s, (four >> (8 * u)) & 255u);
+          al[u] = gs_alpha(r[u], x, y, e);
         }
-        if (T < K.tmin) {
-          used = b - rg.x + q + 1;
-          done = true;
-          break;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (live && q + u < cnt && al[u] >= K.amin) {
+            const float wgt = T * al[u];
+            c0 += wgt * r[u].c0;
+            c1 += wgt * r[u].c1;
+            c2 += wgt * r[u].c2;
+            T *= 1.0f - al[u];
+            if (T < K.tmin) {
+              live = false;
+              used = first + (int)((four >> (8 * u)) & 255u) + 1;
+            }
+          }
         }
+        if (__ballot(live) == 0ull) break;
       }
-      if (!done) used = b - rg.x + nbatch;
     }
+    feed.advance();
   }
   if (!inside) return;
   const int64_t pix = i + (int64_t)K.W * j, HW = (int64_t)K.W * K.H;
@@ -650,6 +814,147 @@ __global__ __launch_bounds__(GS_THREADS) void k_gs_raster(CamDev K, const int32_
   image[HW + pix] = c1 + T * K.bg[1];
   image[2 * HW + pix] = c2 + T * K.bg[2];
   last[pix] = used;
+}
+
+// One workgroup per 8 x 8 pixels, a wave per 4 x 4: lane l holds pixel l / 4
+// and entry l % 4 of a step, so four alphas of every pixel are one
+// evaluation; the lanes of a pixel then take the four entries' alphas from
+// each other in order, lane c < 3 blending channel c.
+__device__ __forceinline__ void gs_raster_split(const CamDev &K, GsBatch<GS_THREADS> &s, int tile, int quarter, int2 rg, bool strict,
+                                                const int32_t *__restrict__ pv, const float4 *__restrict__ rec,
+                                                float *__restrict__ image, int32_t *__restrict__ last) {
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wx = (tile % K.tw) * GS_TILE + 8 * (quarter & 1) + 4 * (wid & 1);
+  const int wy = (tile / K.tw) * GS_TILE + 8 * (quarter >> 1) + 4 * (wid >> 1);
+  const int e = lane & 3, i = wx + ((lane >> 2) & 3), j = wy + (lane >> 4);
+  const bool inside = i < K.W && j < K.H;
+  const float x = i + 0.5f, y = j + 0.5f;
+  // T: the transmittance while the pixel blends, then 0; Tend: what it was
+  // when the pixel stopped (so T + Tend is the final one)
+  float T = inside ? 1.f : 0.f, Tend = 0.f, c = 0.f;
+  int used = 0;
+  bool on = inside;
+  GsFeed<GS_THREADS, true> feed(pv, rec, rg.x, rg.y);
+  while (feed.more()) {
+    const bool done = __ballot(on) == 0ull;
+    if (__syncthreads_and(done)) break;
+    feed.stage(s, nullptr);
+    __syncthreads();
+    const int first = feed.pos - rg.x + 1, n = feed.len;
+    feed.advance();
+    if (done) continue;
+    const int cnt = gs_pick(s, wid, lane, n, wx, wy, 3);
+    struct Step {
+      uint32_t four;
+      float4 ra;
+      float2 rb;
+      float col[4];
+    };
+    auto fetch = [&](int q) {
+      Step f;
+      f.four = __builtin_amdgcn_readfirstlane(*reinterpret_cast<const uint32_t *>(&s.list[wid][q]));
+      const int m = (f.four >> (8 * e)) & 255u;
+      f.ra = s.a[m];
+      f.rb = s.b[m];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) f.col[u] = reinterpret_cast<const float *>(&s.rgb[(f.four >> (8 * u)) & 255u])[e];
+      return f;
+    };
+    Step nx = fetch(0);
+    for (int q = 0; q < cnt; q += 4) {
+      const Step f = nx;
+      nx = fetch(min(q + 4, GS_THREADS - 4));
+      const GsRec r{f.ra.x, f.ra.y, f.ra.z, f.ra.w, f.rb.x, f.rb.y, 0.f, 0.f, 0.f};
+      float ex;
+      const float al = gs_alpha(r, x, y, ex);
+      const float a = q + e < cnt && al >= K.amin ? al : -1.f;
+      // the four entries one after another, each alpha from its lane of the pixel
+      const float a0 = dpp_mov<0x00>(a, a), a1 = dpp_mov<0x55>(a, a), a2 = dpp_mov<0xAA>(a, a), a3 = dpp_mov<0xFF>(a, a);
+      const float v0 = fmaxf(a0, 0.f), v1 = fmaxf(a1, 0.f), v2 = fmaxf(a2, 0.f), v3 = fmaxf(a3, 0.f);
+      const float T1 = T * (1.0f - v0), T2 = T1 * (1.0f - v1), T3 = T2 * (1.0f - v2), T4 = T3 * (1.0f - v3);
+      if (!strict && __ballot(on && !(T4 >= K.tmin)) == 0ull) {
+        // no pixel of the wave stops in this step (and an alpha of zero adds
+        // nothing: the colours are finite)
+        c += (T * v0) * f.col[0];
+        c += (T1 * v1) * f.col[1];
+        c += (T2 * v2) * f.col[2];
+        c += (T3 * v3) * f.col[3];
+        T = T4;
+        used = on ? first + (int)((f.four >> (8 * min(3, cnt - 1 - q))) & 255u) : used;
+        continue;
+      }
+      auto blend = [&](float au, float col, int u) {
+        const bool hit = au >= 0.f;
+        const float av = fmaxf(au, 0.f);
+        const float cn = c + (T * av) * col, Tn = T * (1.0f - av);
+        c = hit && on ? cn : c;
+        used = on && q + u < cnt ? first + (int)((f.four >> (8 * u)) & 255u) : used;
+        on = on && Tn >= K.tmin;
+        T = on ? Tn : 0.f;
+        Tend += on ? 0.f : Tn;
+      };
+      blend(a0, f.col[0], 0);
+      blend(a1, f.col[1], 1);
+      blend(a2, f.col[2], 2);
+      blend(a3, f.col[3], 3);
+      if (__ballot(on) == 0ull) break;
+    }
+  }
+  if (!inside) return;
+  T += Tend;
+  const int64_t pix = i + (int64_t)K.W * j, HW = (int64_t)K.W * K.H;
+  if (e < 3) image[e * HW + pix] = c + T * (e == 0 ? K.bg[0] : e == 1 ? K.bg[1] : K.bg[2]);
+  else last[pix] = used;
+}
+
+// Work items of both raster passes: the quarters of the split tiles, then
+// the whole tiles; a workgroup starts with the item of its index and draws
+// further ones from a ticket.  One workgroup per tile costs the least work
+// in all, but its waves walk the whole list: views whose lists hold
+// thousands of small kernels on a few tiles leave the chip idle behind them.
+// There a wave of 4 x 4 pixels skips four entries of five and takes the rest
+// four at a time.  The forward pass blends a pixel's entries one after
+// another in list order either way.  Forward, against one thread per pixel
+// walking the list entry by entry: 256k kernels on 247 tiles of a 512^2 view
+// (lists up to 7,500) 672 -> 97 us, 20k on 44 tiles 245 -> 44 us, 1M kernels
+// on 4096 tiles of which a pixel sees some hundred 78 -> 87 us.
+struct GsItem {
+  int tile, quarter;  // quarter < 0: the whole tile
+};
+
+__device__ __forceinline__ GsItem gs_item(const GsWs &w, int it, int nsplit) {
+  if (it >= 4 * nsplit) return GsItem{w.whole[it - 4 * nsplit], -1};
+  // the quarters of a tile to one XCD (workgroups are handed out round-robin
+  // over 8), where they share its list
+  const int group = it >> 5, in = min(8, nsplit - 8 * group), r = it & 31;
+  return GsItem{w.split[8 * group + r % in], r / in};
+}
+
+// workgroups of a raster launch: enough to fill the chip six times per CU
+// with quarters, at least one per tile
+static unsigned gs_raster_blocks(int64_t T) {
+  const int64_t most = T > 1536 ? T : 1536;
+  return (unsigned)(4 * T < most ? 4 * T : most);
+}
+
+__global__ __launch_bounds__(GS_THREADS) void k_gs_raster(CamDev K, GsWs w, const int32_t *__restrict__ pv,
+                                                         float *__restrict__ image) {
+  __shared__ GsBatch<GS_THREADS> s;
+  __shared__ int s_item;
+  if (gs_failed(w.hdr)) return;  // over capacity: the image is not written
+  const int nsplit = w.hdr[3], items = 4 * nsplit + w.hdr[2];
+  int it = blockIdx.x;
+  while (it < items) {
+    const GsItem t = gs_item(w, it, nsplit);
+    const int2 rg = w.range[t.tile];
+    if (t.quarter < 0) gs_raster_whole(K, s, t.tile, rg, pv, w.rec, image, w.last);
+    else gs_raster_split(K, s, t.tile, t.quarter, rg, w.hdr[6] != 0, pv, w.rec, image, w.last);
+    if (items <= (int)gridDim.x) return;
+    __syncthreads();
+    if (threadIdx.x == 0) s_item = (int)gridDim.x + atomicAdd(&w.hdr[4], 1);
+    __syncthreads();
+    it = s_item;
+  }
 }
 
 // ------------------------------------------------------- raster reverse
@@ -660,132 +965,246 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-// Sum over the 64 lanes of a wave whose lanes are all active: four DPP
-// steps give every lane its 16-lane row total (quad_perm [1,0,3,2] and
-// [2,3,0,1], then row rotations by 4 and 8), four lane reads add the rows.
-// The result is wave-uniform.
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v) {
-  return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));
+// Inclusive scans over the 16 lanes of every DPP row, four values at a time:
+// step s combines a lane with the lane s below it; lanes without one are not
+// written.  A DPP operand must be two wait states old: the s_nop covers the
+// inputs, the three other chains every later step.
+#define GS_SCAN4(OP, S)                                         \
+  OP " %0, %0, %0 row_shr:" S " row_mask:0xf bank_mask:0xf\n\t" \
+  OP " %1, %1, %1 row_shr:" S " row_mask:0xf bank_mask:0xf\n\t" \
+  OP " %2, %2, %2 row_shr:" S " row_mask:0xf bank_mask:0xf\n\t" \
+  OP " %3, %3, %3 row_shr:" S " row_mask:0xf bank_mask:0xf\n\t"
+
+__device__ __forceinline__ void row_scan_mul4(float (&v)[4]) {
+  asm volatile("s_nop 1\n\t" GS_SCAN4("v_mul_f32_dpp", "1") GS_SCAN4("v_mul_f32_dpp", "2") GS_SCAN4("v_mul_f32_dpp", "4")
+                   GS_SCAN4("v_mul_f32_dpp", "8")
+               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+}
+__device__ __forceinline__ void row_scan_add4(float (&v)[4]) {
+  asm volatile("s_nop 1\n\t" GS_SCAN4("v_add_f32_dpp", "1") GS_SCAN4("v_add_f32_dpp", "2") GS_SCAN4("v_add_f32_dpp", "4")
+                   GS_SCAN4("v_add_f32_dpp", "8")
+               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+}
+#undef GS_SCAN4
+
+// value of the lane below in the row (old in the row's first lane), and of
+// the row's last lane
+__device__ __forceinline__ float row_below(float old, float v) { return dpp_mov<0x111>(old, v); }
+__device__ __forceinline__ float row_last(float v) { return dpp_mov<0x15F>(v, v); }
+
+// 1 / m to about one rounding: the hardware reciprocal and a Newton step
+__device__ __forceinline__ float recip(float m) {
+  const float r = __builtin_amdgcn_rcpf(m);
+  return fmaf(r, fmaf(-m, r, 1.0f), r);
 }
 
-__device__ __forceinline__ float wave_total(float v) {
-  v = dpp_add<0xB1>(v);
-  v = dpp_add<0x4E>(v);
-  v = dpp_add<0x124>(v);
-  v = dpp_add<0x128>(v);
-  const int b = __float_as_int(v);
-  return (__int_as_float(__builtin_amdgcn_readlane(b, 0)) + __int_as_float(__builtin_amdgcn_readlane(b, 16))) +
-         (__int_as_float(__builtin_amdgcn_readlane(b, 32)) + __int_as_float(__builtin_amdgcn_readlane(b, 48)));
-}
+// A wave evaluates 16 entries x 4 x 4 pixels at a time: lane l holds entry
+// l % 16 and pixel column l / 16, the four pixel rows are four registers.
+// The transmittance in front of an entry and P are scans over the 16 lanes of
+// a DPP row, so the chain that a pixel's list imposes advances 16 entries at
+// a time, and a wave only takes the entries whose pixel box meets its pixels
+// (for kernels of a few pixels about a fifth of the tile's list).  In a
+// quarter a wave has 4 x 4 pixels, in a whole tile 8 x 8 as four blocks per
+// group of entries; the pixels' state waits in LDS meanwhile.
+// An entry's sums over the pixel rows are taken in its lanes (the column's dx
+// is one number), those over the four columns by 16x16x4 fp32 MFMAs whose
+// second operand has just this layout (lane l: k = column l / 16, n = entry
+// l % 16) and whose first operand holds ones in one row: the accumulator
+// collects the nine values, value r of entry n in row r.  (Moments about a
+// block's centre, moved to the kernel afterwards, need one MFMA less and lose
+// digits to cancellation where a kernel is smaller than a pixel.)  Every wave
+// leaves its sums in an LDS table of its own (an entry comes up once per wave
+// and batch: plain stores); for a whole tile the workgroup adds the tables of
+// the waves that met an entry.  One float atomic per value goes to memory,
+// the nine of a kernel side by side in one request.  (Float atomics in LDS
+// took 375 us at 1M kernels and 1024^2 pixels, one global atomic per wave and
+// value 532 us.)
+// Against one wave per tile walking the list entry by entry: 256k kernels,
+// 512^2 3,016 -> 113 us, 20k 1,768 -> 49 us, 1M kernels, 1024^2 357 -> 220 us
+// (there the vector units are busy two thirds of the time).
+constexpr int GS_ADJ_N = 128;  // list entries per batch
+struct GsPixel {
+  float T, P, G0, G1, G2, gC;
+  int used;
+  float pad;
+};
 
-// per-kernel adjoints in LDS for one batch: centre (2), conic (3), opacity,
-// colour (3)
-constexpr int GS_NB = 9;
-
-// One wave per tile, four pixels per lane (lane l: column l % 16, rows
-// 4 (l / 16) .. 4 (l / 16) + 3), so each list entry's per-kernel adjoints
-// are summed over the lane's pixels in registers and then over the wave
-// once (DPP), and lane 0 adds them to global memory.
-constexpr int GS_ADJ_PX = 4;
-
-__global__ __launch_bounds__(64) void k_gs_raster_adj(
-    CamDev K, const int32_t *__restrict__ hdr, const int2 *__restrict__ range,
-    const int32_t *__restrict__ pv, const float4 *__restrict__ rec, const int32_t *__restrict__ last,
-    const float *__restrict__ image, const float *__restrict__ image_bar, int n, float *__restrict__ gbar,
-    float *__restrict__ color_bar, float *__restrict__ opacity_bar) {
-  __shared__ GsRec s_r[64];
-  __shared__ int s_g[64];
-  if (gs_failed(hdr)) return;
-  const int tile = blockIdx.x;
-  const int tx = tile % K.tw, ty = tile / K.tw;
-  const int lane = threadIdx.x;
-  const int i = tx * GS_TILE + (lane % GS_TILE);
-  const int jb = ty * GS_TILE + GS_ADJ_PX * (lane / GS_TILE);
-  const int2 rg = range[tile];
+__global__ __launch_bounds__(GS_THREADS, 4) void k_gs_raster_adj(CamDev K, GsWs w, const int32_t *__restrict__ pv,
+                                                                const float *__restrict__ image,
+                                                                const float *__restrict__ image_bar) {
+  __shared__ GsBatch<GS_ADJ_N> s;
+  __shared__ __attribute__((aligned(16))) GsPixel px[GS_THREADS];
+  __shared__ float s_sum[GS_THREADS / 64][GS_ADJ_N * GS_NB];
+  __shared__ uint64_t s_hits[GS_THREADS / 64][GS_ADJ_N / 64];
+  __shared__ int s_id[GS_ADJ_N];
+  __shared__ int s_most, s_item;
+  if (gs_failed(w.hdr)) return;
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int e = lane & 15, g = lane >> 4;
   const int64_t HW = (int64_t)K.W * K.H;
-  const float x = i + 0.5f;
-  float G[GS_ADJ_PX][3], Ct[GS_ADJ_PX][3], T[GS_ADJ_PX], Acc[GS_ADJ_PX][3];
-  int used[GS_ADJ_PX];
-  int maxused = 0;
+  const int nsplit = w.hdr[3], items = 4 * nsplit + w.hdr[2];
+  // first operands: this lane's element of row e
+  float row[GS_NB];
 #pragma unroll
-  for (int k = 0; k < GS_ADJ_PX; ++k) {
-    const int j = jb + k;
-    const bool inside = i < K.W && j < K.H;
-    const int64_t pix = i + (int64_t)K.W * j;
-    used[k] = inside ? last[pix] : 0;
-    T[k] = 1.f;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      G[k][c] = inside ? image_bar[c * HW + pix] : 0.f;
-      Ct[k][c] = inside ? image[c * HW + pix] : 0.f;
-      Acc[k][c] = 0.f;
-    }
-    maxused = max(maxused, used[k]);
-  }
-  // the tile's furthest pixel bounds the traversal (wave maximum)
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) maxused = max(maxused, __shfl_xor(maxused, m, 64));
-  for (int b = 0; b < maxused; b += 64) {
-    const int nbatch = min(64, maxused - b);
+  for (int v = 0; v < GS_NB; ++v) row[v] = e == v ? 1.f : 0.f;
+  int it = blockIdx.x;
+  while (it < items) {
+    const GsItem t = gs_item(w, it, nsplit);
+    const int2 rg = w.range[t.tile];
+    const int X0 = (t.tile % K.tw) * GS_TILE, Y0 = (t.tile / K.tw) * GS_TILE;
+    const bool whole = t.quarter < 0;
+    if (threadIdx.x == 0) s_most = 0;
     __syncthreads();
-    if (lane < nbatch) {
-      const int g = pv[rg.x + b + lane];
-      s_g[lane] = g;
-      s_r[lane] = load_rec(rec, g);
+    if (whole || threadIdx.x < 64) {
+      // one pixel per thread (a quarter's 64 by the first wave)
+      const int n = threadIdx.x;
+      const int lx = whole ? n & 15 : 8 * (t.quarter & 1) + (n & 7);
+      const int ly = whole ? n >> 4 : 8 * (t.quarter >> 1) + (n >> 3);
+      const int i = X0 + lx, j = Y0 + ly;
+      const bool inside = i < K.W && j < K.H;
+      const int64_t pix = i + (int64_t)K.W * j;
+      GsPixel q;
+      q.T = 1.f;
+      q.P = 0.f;
+      q.G0 = inside ? image_bar[pix] : 0.f;
+      q.G1 = inside ? image_bar[HW + pix] : 0.f;
+      q.G2 = inside ? image_bar[2 * HW + pix] : 0.f;
+      q.gC = inside ? q.G0 * image[pix] + q.G1 * image[HW + pix] + q.G2 * image[2 * HW + pix] : 0.f;
+      q.used = inside ? w.last[pix] : 0;
+      q.pad = 0.f;
+      px[ly * GS_TILE + lx] = q;
+      // the furthest pixel bounds the traversal
+      int most = q.used;
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) most = max(most, __shfl_xor(most, m, 64));
+      if (lane == 0) atomicMax(&s_most, most);
     }
     __syncthreads();
-    for (int q = 0; q < nbatch; ++q) {
-      const GsRec r = s_r[q];
-      const float cc[3] = {r.c0, r.c1, r.c2};
-      float d[GS_NB];
+    GsFeed<GS_ADJ_N, true> feed(pv, w.rec, rg.x, rg.x + s_most);
+    const int nblk = whole ? 4 : 1;
+    const int lx = whole ? 8 * (wid & 1) : 8 * (t.quarter & 1) + 4 * (wid & 1);
+    const int ly = whole ? 8 * (wid >> 1) : 8 * (t.quarter >> 1) + 4 * (wid >> 1);
+    while (feed.more()) {
+      const int first = feed.pos - rg.x, n = feed.len;
+      feed.stage(s, s_id);
+      __syncthreads();
+      feed.advance();
+      const int cnt = gs_pick(s, wid, lane, n, X0 + lx, Y0 + ly, whole ? 7 : 3, s_hits[wid]);
+      for (int q = 0; q < cnt; q += 16) {
+        const bool has = q + e < cnt;
+        const int j = has ? (int)s.list[wid][q + e] : 0;
+        const GsRec r = gs_entry(s, j);
+        const int idx = has ? first + j : INT_MAX;
+        gs_floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < nblk; ++b) {
+          const int bx = lx + 4 * (b & 1), by = ly + 4 * (b >> 1);
+          const float x0 = (float)(X0 + bx), y0 = (float)(Y0 + by);
+          const float x = x0 + (float)g + 0.5f, y = y0 + 0.5f;
+          float ex[4], al[4], z[4], sc[4], v[4], wg[4], Tx[4], T[4], P[4], G[4][3], gC[4];
+          bool on[4];
 #pragma unroll
-      for (int v = 0; v < GS_NB; ++v) d[v] = 0.f;
-      bool any = false;
-#pragma unroll
-      for (int k = 0; k < GS_ADJ_PX; ++k) {
-        float dx, dy, e;
-        const float al = gs_alpha(r, x, (float)(jb + k) + 0.5f, dx, dy, e);
-        if ((b + q < used[k]) && al >= K.amin) {
-          any = true;
-          const float wgt = T[k] * al;
-          float dal = 0.f;
-          const float inv1m = 1.0f / (1.0f - al);
-#pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            Acc[k][c] += wgt * cc[c];
-            d[6 + c] += wgt * G[k][c];                                 // colour
-            dal += G[k][c] * (T[k] * cc[c] - (Ct[k][c] - Acc[k][c]) * inv1m);
+          for (int p = 0; p < 4; ++p) {
+            const gs_floatx4 *pq = reinterpret_cast<const gs_floatx4 *>(&px[(by + p) * GS_TILE + bx + g]);
+            const gs_floatx4 u0 = pq[0], u1 = pq[1];
+            T[p] = u0.x;
+            P[p] = u0.y;
+            gC[p] = u1.y;
+            const float a = gs_alpha(r, x, y + (float)p, ex[p]);
+            on[p] = idx < __float_as_int(u1.z) && a >= K.amin;
+            al[p] = on[p] ? a : 0.f;
+            z[p] = 1.0f - al[p];
+            G[p][0] = u0.z;
+            G[p][1] = u0.w;
+            G[p][2] = u1.x;
+            sc[p] = G[p][0] * r.c0 + G[p][1] * r.c1 + G[p][2] * r.c2;
           }
-          T[k] *= 1.0f - al;
-          d[5] += dal * e;                                             // opacity
-          const float dq = -0.5f * al * dal;                           // alpha = o exp(-q/2)
-          d[0] += -2.0f * dq * (r.A * dx + r.B * dy);                  // centre x
-          d[1] += -2.0f * dq * (r.B * dx + r.C * dy);                  // centre y
-          d[2] += dq * dx * dx;                                        // conic A
-          d[3] += dq * 2.0f * dx * dy;                                 // conic B (q has 2 B dx dy)
-          d[4] += dq * dy * dy;                                        // conic C
+          if (__ballot(on[0] || on[1] || on[2] || on[3]) == 0ull) continue;
+          row_scan_mul4(z);
+#pragma unroll
+          for (int p = 0; p < 4; ++p) {
+            const float Ti = T[p] * z[p];
+            Tx[p] = row_below(T[p], Ti);
+            T[p] = row_last(Ti);
+            wg[p] = Tx[p] * al[p];
+            v[p] = on[p] ? wg[p] * sc[p] : 0.f;
+          }
+          row_scan_add4(v);
+          const float dx = x - r.mx;
+          float m[GS_NB];
+#pragma unroll
+          for (int k = 0; k < GS_NB; ++k) m[k] = 0.f;
+#pragma unroll
+          for (int p = 0; p < 4; ++p) {
+            const float Pi = P[p] + v[p];
+            P[p] = row_last(Pi);
+            const float dal = Tx[p] * sc[p] - (gC[p] - Pi) * recip(1.0f - al[p]);
+            const float de = on[p] ? dal * ex[p] : 0.f, dy = y + (float)p - r.my;
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) m[ch] += wg[p] * G[p][ch];
+            m[3] += de;
+            m[8] += de * dy;
+            m[7] += de * dy * dy;
+          }
+          m[4] = m[3] * dx;
+          m[5] = m[4] * dx;
+          m[6] = m[8] * dx;
+          if (e == 0) {
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+              *reinterpret_cast<float2 *>(&px[(by + p) * GS_TILE + bx + g]) = make_float2(T[p], P[p]);
+          }
+#pragma unroll
+          for (int k = 0; k < GS_NB; ++k)
+            sum = __builtin_amdgcn_mfma_f32_16x16x4f32(row[k], m[k], sum, 0, 0, 0);
+        }
+        // lane: values 4 g .. 4 g + 3 of entry e
+        float *dst = s_sum[wid] + (whole ? j : e) * GS_NB;
+        if (has || !whole) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (4 * g + k < GS_NB) dst[4 * g + k] = sum[k];
+        }
+        if (!whole) {
+          // few waves meet an entry: straight to memory, 64 consecutive of the
+          // group's 16 x 9 values at a time
+          __builtin_amdgcn_wave_barrier();
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const int i = k * 64 + lane, m = i / GS_NB;
+            if (m < 16 && q + m < cnt) {
+              const float v = s_sum[wid][i];
+              if (v != 0.f) atomicAdd(w.gbar + (int64_t)s_id[s.list[wid][q + m]] * GS_NB + i % GS_NB, v);
+            }
+          }
+          __builtin_amdgcn_wave_barrier();
         }
       }
-      if (__ballot(any) == 0ull) continue;  // wave-uniform
-#pragma unroll
-      for (int v = 0; v < GS_NB; ++v) d[v] = wave_total(d[v]);
-      if (lane == 0) {
-        const int g = s_g[q];
-        if (d[0] != 0.f) atomicAdd(&gbar[g], d[0]);
-        if (d[1] != 0.f) atomicAdd(&gbar[(int64_t)n + g], d[1]);
-        if (d[2] != 0.f) atomicAdd(&gbar[2 * (int64_t)n + g], d[2]);
-        if (d[3] != 0.f) atomicAdd(&gbar[3 * (int64_t)n + g], d[3]);
-        if (d[4] != 0.f) atomicAdd(&gbar[4 * (int64_t)n + g], d[4]);
-        if (opacity_bar && d[5] != 0.f) atomicAdd(&opacity_bar[g], d[5]);
-        if (color_bar) {
-#pragma unroll
-          for (int c = 0; c < 3; ++c)
-            if (d[6 + c] != 0.f) atomicAdd(&color_bar[c * (int64_t)n + g], d[6 + c]);
-        }
+      if (!whole) {
+        __syncthreads();  // the next batch replaces the ids and the records
+        continue;
       }
+      __syncthreads();
+      // 16 lanes per entry, nine of them with a value
+      for (int j = threadIdx.x >> 4; j < n; j += GS_THREADS / 16) {
+        float sum = 0.f;
+#pragma unroll
+        for (int v = 0; v < GS_THREADS / 64; ++v)
+          if (e < GS_NB && (s_hits[v][j >> 6] >> (j & 63) & 1u)) sum += s_sum[v][j * GS_NB + e];
+        if (sum != 0.f) atomicAdd(w.gbar + (int64_t)s_id[j] * GS_NB + e, sum);
+      }
+      __syncthreads();  // the next batch replaces the ids and the records
     }
+    if (items <= (int)gridDim.x) return;
+    if (threadIdx.x == 0) s_item = (int)gridDim.x + atomicAdd(&w.hdr[5], 1);
+    __syncthreads();
+    it = s_item;
   }
+}
+
+__global__ __launch_bounds__(256) void k_gs_adj_begin(GsWs w, int64_t count) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) w.hdr[5] = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256)
+    reinterpret_cast<float4 *>(w.gbar)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 // Centre and conic adjoints back to mu and Sigma through the projection.
@@ -796,16 +1215,33 @@ __global__ __launch_bounds__(64) void k_gs_raster_adj(
 __global__ __launch_bounds__(256) void k_gs_project_adj(CamDev K, int n, const float *__restrict__ mu,
                                                         const float *__restrict__ sigma, const float *__restrict__ op,
                                                         const float *__restrict__ gbar, float *__restrict__ mu_bar,
-                                                        float *__restrict__ sigma_bar) {
+                                                        float *__restrict__ sigma_bar, float *__restrict__ color_bar,
+                                                        float *__restrict__ opacity_bar) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= n) return;
+  float b[GS_NB];
+  bool any = false;
+#pragma unroll
+  for (int v = 0; v < GS_NB; ++v) {
+    b[v] = gbar[(int64_t)g * GS_NB + v];
+    any = any || b[v] != 0.f;
+  }
+  if (!any) return;
+  if (color_bar) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) color_bar[c * (int64_t)n + g] += b[c];
+  }
+  if (opacity_bar) opacity_bar[g] += b[3];
   float S[6];
 #pragma unroll
   for (int e = 0; e < 6; ++e) S[e] = sigma[(int64_t)e * n + g];
   const Proj r = gs_proj(K, mu[g], mu[(int64_t)n + g], mu[2 * (int64_t)n + g], S, op[g]);
   if (!r.drawn) return;
-  const float mxb = gbar[g], myb = gbar[(int64_t)n + g];
-  const float Ab = gbar[2 * (int64_t)n + g], Bb = gbar[3 * (int64_t)n + g], Cb = gbar[4 * (int64_t)n + g];
+  // alpha = o exp(-q/2), q = A dx^2 + 2 B dx dy + C dy^2 with d = x - m:
+  // q_bar = -o/2 e, A_bar = sum q_bar dx^2, m_bar = -2 K sum q_bar d
+  const float h = -0.5f * op[g];
+  const float mxb = -2.0f * h * (r.A * b[4] + r.B * b[8]), myb = -2.0f * h * (r.B * b[4] + r.C * b[8]);
+  const float Ab = h * b[5], Bb = 2.0f * h * b[6], Cb = h * b[7];
   if (mxb == 0.f && myb == 0.f && Ab == 0.f && Bb == 0.f && Cb == 0.f) return;
   // Sigma2_bar = -K Kbar K, K = [[A, B], [B, C]], Kbar = [[Ab, Bb/2], [Bb/2, Cb]]
   const float kb01 = 0.5f * Bb;
@@ -1138,8 +1574,8 @@ extern "C" int gs_render(const dw_camera *cam, int n, const float *mu, const flo
     }
   }
   const int32_t *ids = pairs_in_b(T) ? w.pv_b : w.pv_a;
-  hipLaunchKernelGGL(k_gs_raster, dim3((unsigned)T), dim3(GS_THREADS), 0, s, K, w.hdr, w.range, ids, w.rec, image,
-                     w.last);
+  hipLaunchKernelGGL(k_gs_classify, dim3(grid_blocks(T, 64)), dim3(256), 0, s, K, w, ids);
+  hipLaunchKernelGGL(k_gs_raster, dim3(gs_raster_blocks(T)), dim3(GS_THREADS), 0, s, K, w, ids, image);
   return check_launch("gs_render");
 }
 
@@ -1155,13 +1591,12 @@ extern "C" int gs_render_adj(const dw_camera *cam, int n, const float *mu, const
   if (n == 0) return DW_OK;
   hipStream_t s = (hipStream_t)stream;
   const int64_t T = (int64_t)K.tw * K.th;
-  hipLaunchKernelGGL(k_fill_f32, dim3(grid_blocks(5 * (int64_t)n, 256 * 8)), dim3(256), 0, s, w.gbar, 5 * (int64_t)n,
-                     0.f);
+  const int64_t n4 = (GS_NB * (int64_t)n + 3) / 4;  // the section is padded to 256 bytes
+  hipLaunchKernelGGL(k_gs_adj_begin, dim3(grid_blocks(n4, 256)), dim3(256), 0, s, w, n4);
   const int32_t *ids = pairs_in_b(T) ? w.pv_b : w.pv_a;
-  hipLaunchKernelGGL(k_gs_raster_adj, dim3((unsigned)T), dim3(64), 0, s, K, w.hdr, w.range, ids, w.rec,
-                     w.last, image, image_bar, n, w.gbar, color_bar, opacity_bar);
+  hipLaunchKernelGGL(k_gs_raster_adj, dim3(gs_raster_blocks(T)), dim3(GS_THREADS), 0, s, K, w, ids, image, image_bar);
   hipLaunchKernelGGL(k_gs_project_adj, dim3(grid_blocks(n, 256)), dim3(256), 0, s, K, n, mu, sigma, opacity, w.gbar,
-                     mu_bar, sigma_bar);
+                     mu_bar, sigma_bar, color_bar, opacity_bar);
   return check_launch("gs_render_adj");
 }
 

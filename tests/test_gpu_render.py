@@ -296,3 +296,113 @@ def test_render_forward_and_reverse_replay_in_a_graph():
             assert (got - want).abs().max().item() <= 1e-5 * max(want.abs().max().item(), 1e-30), rep
         step()  # eager work between replays
         torch.cuda.synchronize()
+
+
+def _tile_classes(ws):
+    """(tiles rasterised by one workgroup, tiles by four) of the last render."""
+    hdr = ws.buf[:16].view(torch.int32).tolist()
+    return hdr[2], hdr[3]
+
+
+@pytest.mark.parametrize("n,scale,size,split", [(2600, 0.02, (41, 38), True),    # lists of several batches, small kernels
+                                                (190, 0.02, (17, 9), False),     # a list below the split length
+                                                (700, 0.02, (13, 16), True)])    # one tile, not whole blocks
+@pytest.mark.parametrize("t_min", [0.0, 1e-3])
+def test_raster_classes_match_oracle(n, scale, size, split, t_min):
+    """Tiles of one workgroup and of four, against the oracle's image and its
+    autograd.  Image: a float32 alpha within rounding of alpha_min, or a T
+    within rounding of t_min, flips one term of at most 1e-3, so every pixel
+    is held to that and 99 % to 2e-5; gradients to 1e-3 of the largest entry,
+    as above."""
+    W, H = size
+    g = scenes.random_gaussians(31 + n, n, width=W, height=H, scale=scale, opacity=(0.1, 0.9) if scale < 0.1 else (0.01, 0.05))
+    oc, gc = _cams(g.camera, alpha_min=1e-3, t_min=t_min)
+    dev = _dev(g)
+    img, ws, _ = _render_gpu(gc, dev)
+    whole, four = _tile_classes(ws)
+    assert whole + four == ((W + 15) // 16) * ((H + 15) // 16) and (four > 0) == split
+    leaves = [t.clone().requires_grad_(True) for t in _oracle_inputs(dev)]
+    ref = orender.render(*leaves, oc)
+    err = (img.double().cpu() - ref.detach()).abs()
+    assert err.max().item() < 1.1e-3 and torch.quantile(err.flatten(), 0.99).item() < 2e-5
+    ibar = torch.tensor(np.random.default_rng(n).standard_normal((3, H, W)), dtype=torch.float32, device="cuda")
+    bars = [torch.zeros(3, n, device="cuda"), torch.zeros(6, n, device="cuda"), torch.zeros(3, n, device="cuda"),
+            torch.zeros(n, device="cuda")]
+    api.gs_render_adj(gc, *dev, img, ibar, ws, *bars)
+    gmu, gS, gcol, gop = torch.autograd.grad(ref, leaves, ibar.double().cpu())
+    gS6 = torch.stack([gS[:, 0, 0], gS[:, 1, 1], gS[:, 2, 2], gS[:, 0, 1] + gS[:, 1, 0], gS[:, 0, 2] + gS[:, 2, 0],
+                       gS[:, 1, 2] + gS[:, 2, 1]])
+    for name, got, want in zip(("mu", "sigma", "color", "opacity"), bars, (gmu.T, gS6, gcol.T, gop)):
+        e = (got.double().cpu() - want).abs().max().item()
+        assert e <= 1e-3 * want.abs().max().item(), (name, e, want.abs().max().item())
+    # a second call on the same workspace adds the same again (atomics: last bits differ)
+    one = [b.clone() for b in bars]
+    api.gs_render_adj(gc, *dev, img, ibar, ws, *bars)
+    for b, o in zip(bars, one):
+        assert (b - 2 * o).abs().max().item() <= 1e-5 * o.abs().max().item()
+
+
+@pytest.mark.parametrize("size", [(41, 38), (16, 16)])
+def test_raster_gradients_over_several_batches(size):
+    """Lists of several batches rasterised by one workgroup per tile: with
+    alpha_min = t_min = 0 no decision depends on rounding.  Low opacities keep
+    every kernel in sight; gradients to 1e-3 of the largest entry, as above."""
+    W, H = size
+    n = 900
+    g = scenes.random_gaussians(41, n, width=W, height=H, scale=0.3, opacity=(0.005, 0.02))
+    oc, gc = _cams(g.camera)
+    dev = _dev(g)
+    img, ws, _ = _render_gpu(gc, dev)
+    assert _tile_classes(ws) == (((W + 15) // 16) * ((H + 15) // 16), 0)
+    leaves = [t.clone().requires_grad_(True) for t in _oracle_inputs(dev)]
+    ref = orender.render(*leaves, oc)
+    assert (img.double().cpu() - ref.detach()).abs().max().item() < 2e-5
+    ibar = torch.tensor(np.random.default_rng(n).standard_normal((3, H, W)), dtype=torch.float32, device="cuda")
+    bars = [torch.zeros(3, n, device="cuda"), torch.zeros(6, n, device="cuda"), torch.zeros(3, n, device="cuda"),
+            torch.zeros(n, device="cuda")]
+    api.gs_render_adj(gc, *dev, img, ibar, ws, *bars)
+    gmu, gS, gcol, gop = torch.autograd.grad(ref, leaves, ibar.double().cpu())
+    gS6 = torch.stack([gS[:, 0, 0], gS[:, 1, 1], gS[:, 2, 2], gS[:, 0, 1] + gS[:, 1, 0], gS[:, 0, 2] + gS[:, 2, 0],
+                       gS[:, 1, 2] + gS[:, 2, 1]])
+    for name, got, want in zip(("mu", "sigma", "color", "opacity"), bars, (gmu.T, gS6, gcol.T, gop)):
+        e = (got.double().cpu() - want).abs().max().item()
+        assert e <= 1e-3 * want.abs().max().item(), (name, e, want.abs().max().item())
+
+
+def test_raster_more_items_than_workgroups():
+    """506 tiles of long lists of small kernels: 2024 quarters, more than the
+    launch's workgroups, so some are drawn from the ticket.  Two renders give
+    the same bits; sampled pixels against the oracle as above."""
+    W, H, n = 368, 352, 130_000
+    g = scenes.random_gaussians(77, n, width=W, height=H, scale=0.003, opacity=(0.3, 0.9))
+    oc, gc = _cams(g.camera, alpha_min=1e-3, t_min=1e-3)
+    dev = _dev(g)
+    img, ws, _ = _render_gpu(gc, dev, max_pairs=16 * n)
+    assert 4 * _tile_classes(ws)[1] > 1536
+    again = torch.empty_like(img)
+    api.gs_render(gc, *dev, again, ws)
+    assert torch.equal(img, again)
+    rng = np.random.default_rng(8)
+    i, j = rng.integers(0, W, 96), rng.integers(0, H, 96)
+    ref = orender.render(*_oracle_inputs(dev), oc, pixels=torch.tensor(np.stack([i + 0.5, j + 0.5], axis=1)))
+    err = (img[:, j, i].double().cpu() - ref).abs()
+    assert err.max().item() < 1.1e-3 and torch.quantile(err.flatten(), 0.98).item() < 2e-5
+
+
+@pytest.mark.parametrize("n", [1500, 150])  # tiles of four workgroups and of one
+def test_nonfinite_colour_stays_in_its_pixels(n):
+    """A kernel with a non-finite colour spoils the pixels it is blended into
+    and no other: the pixels that change with its colour."""
+    g = scenes.random_gaussians(5, n, width=32, height=32, scale=0.02)
+    oc, gc = _cams(g.camera, alpha_min=1e-3, t_min=1e-3)
+    dev = list(_dev(g))
+    k = int(np.argmin(np.abs(dev[0][0].cpu().numpy()) + np.abs(dev[0][1].cpu().numpy())))
+    imgs = []
+    for c in (0.0, 1e4, float("nan")):
+        dev[2] = dev[2].clone()
+        dev[2][:, k] = c
+        imgs.append(_render_gpu(gc, dev)[0])
+    touched = imgs[0] != imgs[1]
+    assert touched.any() and not touched.all()
+    assert torch.equal(torch.isnan(imgs[2]), touched)
+    assert torch.equal(imgs[2][~touched], imgs[0][~touched])
