@@ -46,13 +46,13 @@ constexpr int GS_THREADS = 256;
 // [6] e dx dy, [7] e dy^2, [8] e dy
 constexpr int GS_NB = 9;
 constexpr int RS_THREADS = 256;
-constexpr int RS_ROUNDS = 16;
-constexpr int RS_CHUNK = RS_THREADS * RS_ROUNDS;  // keys per radix-sort block
+constexpr int RS_ROUNDS = 16, RS_SHORT = 4;       // keys per thread, large and small inputs
+constexpr int RS_CHUNK = RS_THREADS * RS_ROUNDS;  // keys per radix-sort block (at most)
+constexpr int RS_DIRECT = 64;                     // blocks whose histograms a block adds up by itself
 constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_PER = 8;
 constexpr int SCAN_CHUNK = SCAN_THREADS * SCAN_PER;
-constexpr int SCAN_TOP_THREADS = 1024;
-constexpr int SCAN_TOP_MAX = SCAN_TOP_THREADS * 16;  // block sums the top level scans
+constexpr int SCAN_TOP_MAX = 16384;  // blocks of the tile-count scan at most
 
 // workspace header: [0] status, [1] pair count, [2] tiles of one raster
 // workgroup, [3] tiles of four, [4] and [5] raster and reverse tickets, [6] a drawn kernel has a non-finite
@@ -74,18 +74,20 @@ struct CamDev {
 //   header [256] int32: status, pair count, 64 partial pair totals (u64)
 //   rec [n] 3 float4: (mx, my, A, B), (C, o, c0, c1), (c2, pixel box, -),
 //   the box as two words of two 16-bit numbers: first | last << 16 in x, y
-//   rect [n] int4 tile box (tx0, tx1, ty0, ty1); cnt [n] int32
+//   rect [n] tile box, two words of two 16-bit numbers: first | last << 16 in
+//   x, y; cnt [n] int32
 //   key_a, key_b [n] u32, id_a, id_b [n] int32   (depth sort)
 //   off [n + 1] int32 (tile-count scan in depth order)
 //   pk_a, pk_b [P] u32, pv_a, pv_b [P] int32      (pair sort)
-//   hist [256 * nblk(max(n, P))] int32, bsum [SCAN_TOP_MAX] int32
+//   hist [nblk(max(n, P))][256] int32 (radix sort), bsum [SCAN_TOP_MAX] int32
+//   (digit totals of a radix pass, block sums of the tile-count scan)
 //   range [T] int2, whole, split [T] int32 (tiles of one raster workgroup and
 //   of four), last [W * H] int32
 //   gbar [n][9] float (per-kernel sums of the reverse pass, GS_NB)
 struct GsWs {
   int32_t *hdr;
   float4 *rec;
-  int4 *rect;
+  uint2 *rect;
   int32_t *cnt;
   uint32_t *key_a, *key_b;
   int32_t *id_a, *id_b;
@@ -116,7 +118,7 @@ static GsWs gs_layout(char *base, int64_t n, int64_t P, int W, int H) {
   };
   w.hdr = (int32_t *)take(GS_HDR_INTS * 4);
   w.rec = (float4 *)take((size_t)n * 3 * sizeof(float4));
-  w.rect = (int4 *)take((size_t)n * sizeof(int4));
+  w.rect = (uint2 *)take((size_t)n * sizeof(uint2));
   w.cnt = (int32_t *)take((size_t)n * 4);
   w.key_a = (uint32_t *)take((size_t)n * 4);
   w.key_b = (uint32_t *)take((size_t)n * 4);
@@ -248,7 +250,7 @@ __global__ __launch_bounds__(256) void k_gs_project(CamDev K, int n, const float
                                             __uint_as_float((uint32_t)r.j0 | (uint32_t)r.j1 << 16), 0.f);
   }
   if (has) {
-    w.rect[g] = make_int4(r.tx0, r.tx1, r.ty0, r.ty1);
+    w.rect[g] = make_uint2((uint32_t)r.tx0 | (uint32_t)r.tx1 << 16, (uint32_t)r.ty0 | (uint32_t)r.ty1 << 16);
     w.cnt[g] = c;
     w.key_a[g] = key;
     w.id_a[g] = g;
@@ -303,171 +305,283 @@ __device__ __forceinline__ int64_t dev_len(const int32_t *m_dev, int64_t m_cap) 
   return m <= m_cap ? m : 0;
 }
 
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_sums(const int32_t *__restrict__ in, int64_t m_cap,
-                                                            const int32_t *m_dev, int32_t *__restrict__ bsum) {
+// Tile counts in depth order and their exclusive scan: the first kernel
+// gathers the counts and leaves a sum per block of SCAN_CHUNK, the second
+// adds up the sums before its own (a block-wide reduction of at most
+// SCAN_TOP_MAX values) and scans its counts.  Its last block has the total:
+// a 64-bit pair total (the partial counters of k_gs_project; the int32 scan is
+// only trusted when it fits) above the capacity sets status bit
+// DW_STATUS_RENDER_OVERFLOW and the pair count hdr[1] to 0: nothing is
+// emitted, sorted or drawn.
+__global__ __launch_bounds__(SCAN_THREADS) void k_gs_cnt_sums(int n, const int32_t *__restrict__ id,
+                                                              const int32_t *__restrict__ cnt,
+                                                              int32_t *__restrict__ off, int32_t *__restrict__ bsum) {
   __shared__ int s_w[SCAN_THREADS / 64];
-  const int64_t m = dev_len(m_dev, m_cap);
-  const int64_t b0 = (int64_t)blockIdx.x * SCAN_CHUNK + (int64_t)threadIdx.x * SCAN_PER;
-  int v = 0;
+  const int64_t b0 = (int64_t)blockIdx.x * SCAN_CHUNK;
+  int c[SCAN_PER], v = 0;
 #pragma unroll
-  for (int q = 0; q < SCAN_PER; ++q) v += b0 + q < m ? in[b0 + q] : 0;
+  for (int q = 0; q < SCAN_PER; ++q) {
+    const int64_t r = b0 + q * SCAN_THREADS + threadIdx.x;
+    c[q] = r < n ? cnt[id[r]] : 0;
+  }
+#pragma unroll
+  for (int q = 0; q < SCAN_PER; ++q) {
+    const int64_t r = b0 + q * SCAN_THREADS + threadIdx.x;
+    if (r < n) off[r] = c[q];
+    v += c[q];
+  }
   int tot;
   block_excl_scan(v, s_w, &tot);
   if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
 }
 
-// one 1024-thread block: exclusive scan of nb <= SCAN_TOP_MAX block sums in
-// place, the grand total to *total
-__global__ __launch_bounds__(SCAN_TOP_THREADS) void k_scan_top(int32_t *__restrict__ bsum, int nb,
-                                                               int32_t *__restrict__ total) {
-  __shared__ int s_w[SCAN_TOP_THREADS / 64];
-  constexpr int PER = SCAN_TOP_MAX / SCAN_TOP_THREADS;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int b0 = threadIdx.x * PER;
-  int v[PER], s = 0;
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    v[q] = b0 + q < nb ? bsum[b0 + q] : 0;
-    s += v[q];
-  }
-  const int inc = wave_incl_scan(s, lane);
-  if (lane == 63) s_w[wid] = inc;
-  __syncthreads();
-  int base = 0, tot = 0;
-#pragma unroll
-  for (int q = 0; q < SCAN_TOP_THREADS / 64; ++q) {
-    base += q < wid ? s_w[q] : 0;
-    tot += s_w[q];
-  }
-  int run = base + inc - s;
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    if (b0 + q < nb) bsum[b0 + q] = run;
-    run += v[q];
-  }
-  if (threadIdx.x == 0 && total) *total = tot;
-}
-
-// out[i] = bsum[block] + exclusive scan of in inside the block; out may alias in
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_apply(const int32_t *in, int64_t m_cap, const int32_t *m_dev,
-                                                             const int32_t *__restrict__ bsum, int32_t *out) {
+__global__ __launch_bounds__(SCAN_THREADS) void k_gs_cnt_scan(int n, const int32_t *__restrict__ bsum, int64_t cap,
+                                                              int32_t *__restrict__ off, int32_t *hdr) {
   __shared__ int s_w[SCAN_THREADS / 64];
-  const int64_t m = dev_len(m_dev, m_cap);
+  int before = 0;
+  for (int q = threadIdx.x; q < (int)blockIdx.x; q += SCAN_THREADS) before += bsum[q];
   const int64_t b0 = (int64_t)blockIdx.x * SCAN_CHUNK + (int64_t)threadIdx.x * SCAN_PER;
   int v[SCAN_PER], s = 0;
 #pragma unroll
   for (int q = 0; q < SCAN_PER; ++q) {
-    v[q] = b0 + q < m ? in[b0 + q] : 0;
+    v[q] = b0 + q < n ? off[b0 + q] : 0;
     s += v[q];
   }
-  int tot;
-  int run = bsum[blockIdx.x] + block_excl_scan(s, s_w, &tot);
+  int base, tot;
+  block_excl_scan(before, s_w, &base);
+  int run = base + block_excl_scan(s, s_w, &tot);
 #pragma unroll
   for (int q = 0; q < SCAN_PER; ++q) {
-    if (b0 + q < m) out[b0 + q] = run;
+    if (b0 + q < n) off[b0 + q] = run;
     run += v[q];
   }
-}
-
-// Exclusive scan of in[0, m) into out (may alias), m = min(*m_dev, m_cap)
-// when m_dev is set; *total (optional) receives the sum.
-static void scan_excl(const int32_t *in, int32_t *out, int64_t m_cap, const int32_t *m_dev, int32_t *bsum,
-                      int32_t *total, hipStream_t s) {
-  const int64_t nb = (m_cap + SCAN_CHUNK - 1) / SCAN_CHUNK;
-  const unsigned g = (unsigned)(nb < 1 ? 1 : nb);
-  hipLaunchKernelGGL(k_scan_sums, dim3(g), dim3(SCAN_THREADS), 0, s, in, m_cap, m_dev, bsum);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SCAN_TOP_THREADS), 0, s, bsum, (int)g, total);
-  hipLaunchKernelGGL(k_scan_apply, dim3(g), dim3(SCAN_THREADS), 0, s, in, m_cap, m_dev, bsum, out);
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x < 64) {
+    unsigned long long t = reinterpret_cast<const unsigned long long *>(hdr + GS_CNT0)[threadIdx.x];
+    static_assert(GS_NCNT == 64, "one counter per lane");
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) t += __shfl_xor(t, m, 64);
+    if (threadIdx.x == 0) {
+      const bool over = t > (unsigned long long)cap;
+      if (over) hdr[0] |= DW_STATUS_RENDER_OVERFLOW;
+      hdr[1] = over ? 0 : base + tot;
+    }
+  }
 }
 
 // -------------------------------------------------- stable LSD radix sort
 //
-// One pass sorts by the 8-bit digit at `shift`: per block of RS_CHUNK keys a
-// digit histogram (hist[digit][block]), an exclusive scan of the histogram
-// in that order, then each block places its keys in 16 rounds of 256: a
-// key's slot is its digit's running base in the block plus the same-digit
-// keys before it in the round (earlier waves from LDS counts, earlier lanes
-// of its wave from a 64-bit peer mask built with eight ballots).  Keys of
-// equal digit keep their input order, so the passes compose to a stable sort.
+// One pass sorts by a digit of at most 8 bits: a digit histogram per block of
+// RS_CHUNK keys (hist[block][256]), its exclusive scan over the blocks
+// (k_rs_scan; up to RS_DIRECT blocks the scatter adds the histograms up by
+// itself, which saves the launch), then k_rs_scatter.  There a wave ranks
+// 1024 consecutive keys in 16 rounds of 64 against counters of its own (a
+// key's rank is its digit's count in the wave so far plus the same-digit
+// lanes below it, from a 64-bit peer mask of ballots), so the rounds need no
+// barrier; the block's keys are put in order in LDS and stored in runs of
+// equal digits.  Keys of equal digit keep their input order, so the passes
+// compose to a stable sort.
+// Bound by latency for small inputs and by the 16 bytes moved per key and
+// pass for large ones.  A pass over 20k keys 31 -> 10 us, over 1M 39 -> 25
+// us; the two tile passes of 5.7M pairs 190 -> 76 us (before: three barriers
+// per round of 256 keys, stores scattered key by key, three scan kernels).
 
+template <int ROUNDS>
 __global__ __launch_bounds__(RS_THREADS) void k_rs_hist(const uint32_t *__restrict__ key, int64_t m_cap,
-                                                        const int32_t *m_dev, int shift, int32_t *__restrict__ hist,
-                                                        int nblk) {
-  __shared__ int s_h[256];
+                                                        const int32_t *m_dev, int shift, uint32_t mask,
+                                                        int32_t *__restrict__ hist) {
+  __shared__ int s_h[RS_THREADS / 64][256];
   const int64_t m = dev_len(m_dev, m_cap);
-  s_h[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t b0 = (int64_t)blockIdx.x * RS_CHUNK;
-  for (int r = 0; r < RS_ROUNDS; ++r) {
+  const int64_t b0 = (int64_t)blockIdx.x * (RS_THREADS * ROUNDS);
+  if (b0 >= m) return;  // block-uniform; no reader looks at this block's row
+  const int wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int w = 0; w < RS_THREADS / 64; ++w) s_h[w][threadIdx.x] = 0;
+  uint32_t k[ROUNDS];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
     const int64_t i = b0 + r * RS_THREADS + threadIdx.x;
-    if (i < m) atomicAdd(&s_h[(key[i] >> shift) & 255u], 1);
+    k[r] = i < m ? key[i] : 0u;
   }
   __syncthreads();
-  hist[(int64_t)threadIdx.x * nblk + blockIdx.x] = s_h[threadIdx.x];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r)
+    if (b0 + r * RS_THREADS + threadIdx.x < m) atomicAdd(&s_h[wid][(k[r] >> shift) & mask], 1);
+  __syncthreads();
+  int c = 0;
+#pragma unroll
+  for (int w = 0; w < RS_THREADS / 64; ++w) c += s_h[w][threadIdx.x];
+  hist[(int64_t)blockIdx.x * 256 + threadIdx.x] = c;
 }
 
+// exclusive scan of every digit over the blocks, in place, and the digit
+// totals: 16 digits (64 bytes of a row) x 64 groups of blocks per workgroup
+__global__ __launch_bounds__(1024) void k_rs_scan(int64_t m_cap, const int32_t *m_dev, int32_t *__restrict__ hist,
+                                                  int32_t *__restrict__ total) {
+  __shared__ int s_g[64][17];
+  const int nblk = (int)((dev_len(m_dev, m_cap) + RS_CHUNK - 1) / RS_CHUNK);
+  if (nblk <= RS_DIRECT) return;
+  const int d = blockIdx.x * 16 + (threadIdx.x & 15), g = threadIdx.x >> 4;
+  const int per = (nblk + 63) / 64, r0 = g * per, r1 = min(nblk, r0 + per);
+  int s = 0;
+#pragma unroll 8
+  for (int r = r0; r < r1; ++r) s += hist[(int64_t)r * 256 + d];
+  s_g[g][threadIdx.x & 15] = s;
+  __syncthreads();
+  int run = 0;
+  for (int q = 0; q < g; ++q) run += s_g[q][threadIdx.x & 15];
+  if (g == 63) total[d] = run + s;
+#pragma unroll 8
+  for (int r = r0; r < r1; ++r) {
+    const int c = hist[(int64_t)r * 256 + d];
+    hist[(int64_t)r * 256 + d] = run;
+    run += c;
+  }
+}
+
+template <int ROUNDS, int BITS>
 __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(const uint32_t *__restrict__ kin,
                                                            const int32_t *__restrict__ vin, int64_t m_cap,
                                                            const int32_t *m_dev, int shift,
-                                                           const int32_t *__restrict__ hist, int nblk,
+                                                           const int32_t *__restrict__ hist,
+                                                           const int32_t *__restrict__ total,
                                                            uint32_t *__restrict__ kout, int32_t *__restrict__ vout) {
-  __shared__ int s_base[256];
-  __shared__ int s_wc[RS_THREADS / 64][256];
+  constexpr int CHUNK = RS_THREADS * ROUNDS;
+  constexpr uint32_t mask = (1u << BITS) - 1u;
+  __shared__ int s_cnt[RS_THREADS / 64][256];  // per wave: keys of the digit, then their first slot in the block
+  __shared__ int s_delta[256];                 // slot in the block -> place in the output
+  __shared__ uint32_t s_k[CHUNK];
+  __shared__ int32_t s_v[CHUNK];
+  __shared__ int s_w[SCAN_THREADS / 64];
   const int64_t m = dev_len(m_dev, m_cap);
-  const int64_t b0 = (int64_t)blockIdx.x * RS_CHUNK;
+  const int64_t b0 = (int64_t)blockIdx.x * CHUNK;
   if (b0 >= m) return;  // block-uniform
+  const int nvalid = (int)min((int64_t)CHUNK, m - b0);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  s_base[threadIdx.x] = hist[(int64_t)threadIdx.x * nblk + blockIdx.x];
-  const uint64_t lt = (1ull << lane) - 1ull;
-  for (int r = 0; r < RS_ROUNDS; ++r) {
+  const int w0 = wid * (CHUNK / (RS_THREADS / 64)) + lane;  // this lane's key of round 0
+  uint32_t k[ROUNDS];
+  int32_t v[ROUNDS];
 #pragma unroll
-    for (int w = 0; w < RS_THREADS / 64; ++w) s_wc[w][threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t i = b0 + r * RS_THREADS + threadIdx.x;
-    const bool valid = i < m;
-    uint32_t k = 0;
-    int32_t v = 0;
-    if (valid) {
-      k = kin[i];
-      v = vin[i];
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int i = w0 + r * 64;
+    k[r] = i < nvalid ? kin[b0 + i] : 0u;
+    v[r] = i < nvalid ? vin[b0 + i] : 0;
+  }
+#pragma unroll
+  for (int w = 0; w < RS_THREADS / 64; ++w) s_cnt[w][threadIdx.x] = 0;
+  // thread d: keys of digit d in the blocks before this one, and in all
+  const int nblk = (int)((m + CHUNK - 1) / CHUNK);
+  int before = 0, all = 0;
+  if (nblk <= RS_DIRECT) {
+#pragma unroll 8
+    for (int q = 0; q < nblk; ++q) {
+      const int c = hist[(int64_t)q * 256 + threadIdx.x];
+      all += c;
+      before += q < (int)blockIdx.x ? c : 0;
     }
-    const uint32_t d = (k >> shift) & 255u;
+  } else {
+    before = hist[(int64_t)blockIdx.x * 256 + threadIdx.x];
+    all = threadIdx.x <= mask ? total[threadIdx.x] : 0;
+  }
+  __syncthreads();
+  const uint64_t lt = (1ull << lane) - 1ull;
+  int rank[ROUNDS];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const bool valid = w0 + r * 64 < nvalid;
+    const uint32_t d = (k[r] >> shift) & mask;
     uint64_t peers = __ballot(valid);
 #pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
-      const uint64_t bal = __ballot(valid && ((d >> bit) & 1u));
-      peers &= ((d >> bit) & 1u) ? bal : ~bal;
+    for (int bit = 0; bit < BITS; ++bit) {
+      const bool one = (d >> bit) & 1u;
+      const uint64_t bal = __ballot(one);
+      peers &= one ? bal : ~bal;
     }
-    const int rank = __popcll(peers & lt);
-    if (valid && (peers >> lane) == 1ull) s_wc[wid][d] = __popcll(peers);  // the highest lane of its digit
-    __syncthreads();
-    if (valid) {
-      int pos = s_base[d] + rank;
-      for (int w = 0; w < wid; ++w) pos += s_wc[w][d];
-      kout[pos] = k;
-      vout[pos] = v;
-    }
-    __syncthreads();
-    int add = 0;
-#pragma unroll
-    for (int w = 0; w < RS_THREADS / 64; ++w) add += s_wc[w][threadIdx.x];
-    s_base[threadIdx.x] += add;
-    // the next round's clear is ordered after these reads by its barrier
-    __syncthreads();
+    rank[r] = s_cnt[wid][d] + __popcll(peers & lt);
+    // LDS operations of a wave are in order: every lane has read its count
+    __builtin_amdgcn_wave_barrier();
+    if (valid && (peers >> lane) == 1ull) s_cnt[wid][d] = rank[r] + 1;  // the highest lane of its digit
+    __builtin_amdgcn_wave_barrier();
   }
+  __syncthreads();
+  // thread d: first slot of the digit in the block, then of each wave's keys
+  int c[RS_THREADS / 64], sum = 0, tot;
+#pragma unroll
+  for (int w = 0; w < RS_THREADS / 64; ++w) {
+    c[w] = s_cnt[w][threadIdx.x];
+    sum += c[w];
+  }
+  int slot = block_excl_scan(sum, s_w, &tot);
+  s_delta[threadIdx.x] = block_excl_scan(all, s_w, &tot) + before - slot;
+#pragma unroll
+  for (int w = 0; w < RS_THREADS / 64; ++w) {
+    s_cnt[w][threadIdx.x] = slot;
+    slot += c[w];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    if (w0 + r * 64 < nvalid) {
+      const int at = s_cnt[wid][(k[r] >> shift) & mask] + rank[r];
+      s_k[at] = k[r];
+      s_v[at] = v[r];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int i = r * RS_THREADS + threadIdx.x;
+    if (i < nvalid) {
+      const uint32_t key = s_k[i];
+      const int at = s_delta[(key >> shift) & mask] + i;
+      kout[at] = key;
+      vout[at] = s_v[i];
+    }
+  }
+}
+
+// bits of the digit when `bits` key bits are sorted in passes of at most 8: as
+// even as possible (fewer digits, longer runs to store)
+static int rs_passes(int bits) { return (bits + 7) / 8; }
+static int rs_digit(int bits) { return (bits + rs_passes(bits) - 1) / rs_passes(bits); }
+
+template <int ROUNDS, int BITS = 8>
+static void rs_scatter(int w, unsigned g, hipStream_t s, const uint32_t *kin, const int32_t *vin, int64_t m_cap,
+                       const int32_t *m_dev, int shift, const int32_t *hist, const int32_t *total, uint32_t *kout,
+                       int32_t *vout) {
+  if constexpr (BITS > 4) {
+    if (w < BITS)
+      return rs_scatter<ROUNDS, BITS - 1>(w, g, s, kin, vin, m_cap, m_dev, shift, hist, total, kout, vout);
+  }
+  hipLaunchKernelGGL((k_rs_scatter<ROUNDS, BITS>), dim3(g), dim3(RS_THREADS), 0, s, kin, vin, m_cap, m_dev, shift, hist,
+                     total, kout, vout);
 }
 
 // Sorts (key, value) pairs by key bits [0, bits) stably; the result ends in
 // *ka / *va (the pointers are swapped when it lands in the second buffer).
+// have_hist: hist already holds the first pass's histograms (blocks of
+// RS_CHUNK keys).  Inputs of up to RS_DIRECT short blocks are cut into short
+// ones: their passes are a chain of latencies that four rounds make shorter
+// (20k keys: 13 -> 8 us).
 static void radix_sort(uint32_t **ka, int32_t **va, uint32_t **kb, int32_t **vb, int64_t m_cap, const int32_t *m_dev,
-                       int bits, int32_t *hist, int32_t *bsum, hipStream_t s) {
-  const int64_t nb = rs_blocks(m_cap);
+                       int bits, bool have_hist, int32_t *hist, int32_t *total, hipStream_t s) {
+  const int w = rs_digit(bits) < 4 ? 4 : rs_digit(bits);  // digits below 4 bits: the key bits above are zero
+  const bool brief = !have_hist && m_cap <= RS_DIRECT * RS_THREADS * RS_SHORT;
+  const int64_t chunk = brief ? RS_THREADS * RS_SHORT : RS_CHUNK;
+  const int64_t nb = (m_cap + chunk - 1) / chunk;
   const unsigned g = (unsigned)(nb < 1 ? 1 : nb);
-  for (int shift = 0; shift < bits; shift += 8) {
-    hipLaunchKernelGGL(k_rs_hist, dim3(g), dim3(RS_THREADS), 0, s, *ka, m_cap, m_dev, shift, hist, (int)g);
-    scan_excl(hist, hist, (int64_t)256 * g, nullptr, bsum, nullptr, s);
-    hipLaunchKernelGGL(k_rs_scatter, dim3(g), dim3(RS_THREADS), 0, s, *ka, *va, m_cap, m_dev, shift, hist, (int)g, *kb,
-                       *vb);
+  for (int p = 0; p < rs_passes(bits); ++p) {
+    const int shift = p * w;
+    const uint32_t mask = (1u << w) - 1u;
+    if (p == 0 && have_hist) {
+    } else if (brief) {
+      hipLaunchKernelGGL(k_rs_hist<RS_SHORT>, dim3(g), dim3(RS_THREADS), 0, s, *ka, m_cap, m_dev, shift, mask, hist);
+    } else {
+      hipLaunchKernelGGL(k_rs_hist<RS_ROUNDS>, dim3(g), dim3(RS_THREADS), 0, s, *ka, m_cap, m_dev, shift, mask, hist);
+    }
+    if (nb > RS_DIRECT)
+      hipLaunchKernelGGL(k_rs_scan, dim3((1u << w) / 16), dim3(1024), 0, s, m_cap, m_dev, hist, total);
+    if (brief) rs_scatter<RS_SHORT>(w, g, s, *ka, *va, m_cap, m_dev, shift, hist, total, *kb, *vb);
+    else rs_scatter<RS_ROUNDS>(w, g, s, *ka, *va, m_cap, m_dev, shift, hist, total, *kb, *vb);
     uint32_t *tk = *ka;
     *ka = *kb;
     *kb = tk;
@@ -479,23 +593,11 @@ static void radix_sort(uint32_t **ka, int32_t **va, uint32_t **kb, int32_t **vb,
 
 // ---------------------------------------------------------- tile binning
 
-__global__ __launch_bounds__(256) void k_gs_cnt_by_rank(int n, const int32_t *__restrict__ id,
-                                                        const int32_t *__restrict__ cnt, int32_t *__restrict__ out) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < n) out[r] = cnt[id[r]];
-}
-
-// A pair total (64-bit, hdr[2..3]) above the capacity sets status bit
-// DW_STATUS_RENDER_OVERFLOW and the pair count hdr[1] to 0: nothing is
-// emitted, sorted or drawn.
-__global__ void k_gs_check(int64_t cap, int32_t *hdr) {
-  if (threadIdx.x != 0) return;
-  unsigned long long t = 0;
-  for (int q = 0; q < GS_NCNT; ++q) t += reinterpret_cast<const unsigned long long *>(hdr + GS_CNT0)[q];
-  if (t > (unsigned long long)cap) {
-    hdr[0] |= DW_STATUS_RENDER_OVERFLOW;
-    hdr[1] = 0;
-  }
+// header, and the tile ranges (empty)
+__global__ __launch_bounds__(256) void k_gs_begin(GsWs w, int64_t T) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < GS_HDR_INTS) w.hdr[i] = 0;
+  if (i < T) w.range[i] = make_int2(0, 0);
 }
 
 __global__ void k_gs_status(const int32_t *hdr, int32_t *out) {
@@ -505,99 +607,122 @@ __global__ void k_gs_status(const int32_t *hdr, int32_t *out) {
 __device__ __forceinline__ bool gs_failed(const int32_t *hdr) { return (hdr[0] & DW_STATUS_RENDER_OVERFLOW) != 0; }
 
 // Pairs in depth order.  Block b writes pairs [b E, (b + 1) E) of the list
-// (E = GS_EMIT): two threads find by binary search the depth ranks that own
-// its first and last pair (off is the exclusive scan of the tile counts in
-// depth order; every drawn kernel owns at least one pair and the kernels
-// that are not drawn sort last, so at most E ranks are involved); their
-// offsets and ids are staged in LDS; thread t fills pairs t*16 .. t*16 + 15
-// into an LDS copy of the block's slice, walking its kernels' tile boxes
-// incrementally from one binary search; the slice is then stored with
-// contiguous writes.  The work per block is fixed whatever the kernels'
-// sizes, so a kernel covering thousands of tiles does not hold up a wave.
-constexpr int GS_EMIT = 4096;
+// (E = GS_EMIT): two waves find the depth ranks that own its first and last
+// pair (off is the exclusive scan of the tile counts in depth order; every
+// drawn kernel owns at least one pair and the kernels that are not drawn sort
+// last, so at most E ranks are involved); their offsets, ids and tile boxes
+// are staged in LDS, each marks its first pair, and a running maximum over
+// the marks gives every pair its owner.  The work per block is fixed whatever
+// the kernels' sizes, so a kernel covering thousands of tiles does not hold
+// up a wave, and no load waits for another pair's.  A block's slice is a
+// block of the radix sort: its digit histogram for the first pass is taken
+// here.
+constexpr int GS_EMIT = RS_CHUNK;
 constexpr int GS_EMIT_PER = GS_EMIT / 256;
 
+// last rank whose first pair is at or before tgt, by a whole wave: 64 probes
+// at a time, log64 n dependent loads instead of log2 n
+__device__ __forceinline__ int rank_of_pair(const int32_t *__restrict__ off, int n, int64_t tgt, int lane) {
+  int lo = 0, hi = n;  // off[lo] <= tgt (off[0] = 0), off[hi] > tgt or hi = n
+  while (hi - lo > 1) {
+    const int step = (hi - lo + 63) / 64;
+    const int64_t q = lo + (int64_t)step * (lane + 1);
+    const int below = __popcll(__ballot(q < hi && off[q] <= tgt));  // off ascends: the first lanes
+    lo += step * below;
+    hi = min(hi, lo + step);
+  }
+  return lo;
+}
+
 __global__ __launch_bounds__(256) void k_gs_emit(int n, CamDev K, const int32_t *__restrict__ id,
-                                                 const int32_t *__restrict__ off, const int4 *__restrict__ rect,
-                                                 const int32_t *hdr, uint32_t *__restrict__ pk,
-                                                 int32_t *__restrict__ pv) {
+                                                 const int32_t *__restrict__ off, const uint2 *__restrict__ rect,
+                                                 const int32_t *hdr, uint32_t mask, uint32_t *__restrict__ pk,
+                                                 int32_t *__restrict__ pv, int32_t *__restrict__ hist) {
   __shared__ int s_off[GS_EMIT], s_g[GS_EMIT];
-  __shared__ uint32_t s_pk[GS_EMIT];
-  __shared__ int32_t s_pv[GS_EMIT];
-  __shared__ int s_r[2];
+  __shared__ uint2 s_rect[GS_EMIT];
+  __shared__ __attribute__((aligned(16))) uint16_t s_own[GS_EMIT];
+  __shared__ int s_h[256];
+  __shared__ int s_r[2], s_w[4];
   if (gs_failed(hdr)) return;  // grid-uniform
   const int64_t total = hdr[1];
   const int64_t P0 = (int64_t)blockIdx.x * GS_EMIT;
   if (P0 >= total) return;  // block-uniform
   const int m_pairs = (int)min((int64_t)GS_EMIT, total - P0);
-  if (threadIdx.x < 2) {
-    // last rank whose first pair is at or before the target pair
-    const int64_t tgt = threadIdx.x == 0 ? P0 : P0 + m_pairs - 1;
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (off[mid] <= tgt) lo = mid;
-      else hi = mid - 1;
-    }
-    s_r[threadIdx.x] = lo;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  s_h[threadIdx.x] = 0;
+  for (int q = threadIdx.x; q < GS_EMIT / 2; q += 256) reinterpret_cast<uint32_t *>(s_own)[q] = 0u;
+  if (wid < 2) {
+    const int r = rank_of_pair(off, n, wid == 0 ? P0 : P0 + m_pairs - 1, lane);
+    if (lane == 0) s_r[wid] = r;
   }
   __syncthreads();
   const int r_lo = s_r[0], m_ranks = s_r[1] - s_r[0] + 1;  // <= GS_EMIT
+#pragma unroll 4
   for (int k = threadIdx.x; k < m_ranks; k += 256) {
-    s_off[k] = (int)(off[r_lo + k] - P0);
-    s_g[k] = id[r_lo + k];
+    const int o = (int)(off[r_lo + k] - P0), g = id[r_lo + k];
+    s_off[k] = o;
+    s_g[k] = g;
+    s_rect[k] = rect[g];
+    if (k > 0) s_own[o] = (uint16_t)k;  // rank r_lo owns the slice's first pair
   }
   __syncthreads();
+  // running maximum: 16 consecutive pairs per thread, then over the threads
   const int j0 = threadIdx.x * GS_EMIT_PER;
-  if (j0 < m_pairs) {
-    int lo = 0, hi = m_ranks - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (s_off[mid] <= j0) lo = mid;
-      else hi = mid - 1;
-    }
-    int k = lo;
-    int g = s_g[k];
-    int4 b = rect[g];
-    int w = b.y - b.x + 1;
-    const int q0 = j0 - s_off[k];
-    int tx = q0 % w, ty = q0 / w;
-    int rows = b.w - b.z + 1;
-    const int j1 = min(j0 + GS_EMIT_PER, m_pairs);
-    for (int j = j0; j < j1; ++j) {
-      if (ty == rows) {  // next kernel (at least one pair each)
-        ++k;
-        g = s_g[k];
-        b = rect[g];
-        w = b.y - b.x + 1;
-        rows = b.w - b.z + 1;
-        tx = 0;
-        ty = 0;
-      }
-      s_pk[j] = (uint32_t)(b.x + tx + K.tw * (b.z + ty));
-      s_pv[j] = g;
-      if (++tx == w) {
-        tx = 0;
-        ++ty;
-      }
-    }
+  int own[GS_EMIT_PER], top = 0;
+#pragma unroll
+  for (int q = 0; q < GS_EMIT_PER; ++q) {
+    top = max(top, (int)s_own[j0 + q]);
+    own[q] = top;
+  }
+#pragma unroll
+  for (int sh = 1; sh < 64; sh <<= 1) {
+    const int t = __shfl_up(top, sh, 64);
+    if (lane >= sh) top = max(top, t);
+  }
+  if (lane == 63) s_w[wid] = top;
+  int before = __shfl_up(top, 1, 64);
+  if (lane == 0) before = 0;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 4; ++w) before = max(before, w < wid ? s_w[w] : 0);
+#pragma unroll
+  for (int q = 0; q < GS_EMIT_PER; ++q) s_own[j0 + q] = (uint16_t)max(own[q], before);
+  __syncthreads();
+#pragma unroll 4
+  for (int j = threadIdx.x; j < m_pairs; j += 256) {
+    const int k = s_own[j];
+    const uint2 b = s_rect[k];
+    const uint32_t x0 = b.x & 0xffffu, w = (b.x >> 16) - x0 + 1u, q = (uint32_t)(j - s_off[k]);
+    const uint32_t ty = q / w, t = x0 + (q - ty * w) + (uint32_t)K.tw * ((b.y & 0xffffu) + ty);
+    pk[P0 + j] = t;
+    pv[P0 + j] = s_g[k];
+    atomicAdd(&s_h[t & mask], 1);
   }
   __syncthreads();
-  for (int j = threadIdx.x; j < m_pairs; j += 256) {
-    pk[P0 + j] = s_pk[j];
-    pv[P0 + j] = s_pv[j];
-  }
+  hist[(int64_t)blockIdx.x * 256 + threadIdx.x] = s_h[threadIdx.x];
 }
 
 // grid-stride over the pairs actually present (the grid is sized for a
-// typical count, not for the capacity)
+// typical count, not for the capacity), four per thread: a pair whose tile
+// differs from its predecessor's ends that tile's range and starts its own
 __global__ __launch_bounds__(256) void k_gs_ranges(const uint32_t *__restrict__ pk, const int32_t *__restrict__ hdr,
                                                    int2 *__restrict__ range) {
   const int64_t m = hdr[1];
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
-    const uint32_t t = pk[i];
-    if (i == 0 || pk[i - 1] != t) range[t].x = (int)i;
-    if (i == m - 1 || pk[i + 1] != t) range[t].y = (int)(i + 1);
+  for (int64_t i = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x); i < m; i += 1024 * (int64_t)gridDim.x) {
+    uint4 q = i + 4 <= m ? *reinterpret_cast<const uint4 *>(pk + i)
+                         : make_uint4(pk[i], i + 1 < m ? pk[i + 1] : 0u, i + 2 < m ? pk[i + 2] : 0u, 0u);
+    const uint32_t t[4] = {q.x, q.y, q.z, q.w};
+    uint32_t prev = i > 0 ? pk[i - 1] : 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (i + k >= m) break;
+      if (i + k == 0 || t[k] != prev) {
+        range[t[k]].x = (int)(i + k);
+        if (i + k > 0) range[prev].y = (int)(i + k);
+      }
+      if (i + k == m - 1) range[t[k]].y = (int)m;
+      prev = t[k];
+    }
   }
 }
 
@@ -1553,23 +1678,23 @@ extern "C" int gs_render(const dw_camera *cam, int n, const float *mu, const flo
   DW_REQUIRE(image, DW_EINVAL, "gs_render: image is NULL");
   hipStream_t s = (hipStream_t)stream;
   const int64_t T = (int64_t)K.tw * K.th;
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, w.hdr, (int64_t)GS_HDR_INTS, 0);
-  hipLaunchKernelGGL(k_fill_i32, dim3(grid_blocks(2 * T, 256 * 4)), dim3(256), 0, s, (int32_t *)w.range, 2 * T, 0);
+  hipLaunchKernelGGL(k_gs_begin, dim3(grid_blocks(T > GS_HDR_INTS ? T : GS_HDR_INTS, 256)), dim3(256), 0, s, w, T);
   if (n > 0) {
     hipLaunchKernelGGL(k_gs_project, dim3(grid_blocks(n, 256)), dim3(256), 0, s, K, n, mu, sigma, color, opacity, w);
     uint32_t *ka = w.key_a, *kb = w.key_b;
     int32_t *va = w.id_a, *vb = w.id_b;
-    radix_sort(&ka, &va, &kb, &vb, n, nullptr, 32, w.hist, w.bsum, s);  // 4 passes: back in buffer a
-    hipLaunchKernelGGL(k_gs_cnt_by_rank, dim3(grid_blocks(n, 256)), dim3(256), 0, s, n, va, w.cnt, w.off);
-    scan_excl(w.off, w.off, n, nullptr, w.bsum, w.hdr + 1, s);
-    hipLaunchKernelGGL(k_gs_check, dim3(1), dim3(64), 0, s, max_pairs, w.hdr);
+    radix_sort(&ka, &va, &kb, &vb, n, nullptr, 32, false, w.hist, w.bsum, s);  // 4 passes: back in buffer a
+    const unsigned nsc = grid_blocks(n, SCAN_CHUNK);
+    hipLaunchKernelGGL(k_gs_cnt_sums, dim3(nsc), dim3(SCAN_THREADS), 0, s, n, va, w.cnt, w.off, w.bsum);
+    hipLaunchKernelGGL(k_gs_cnt_scan, dim3(nsc), dim3(SCAN_THREADS), 0, s, n, w.bsum, max_pairs, w.off, w.hdr);
     if (max_pairs > 0) {
+      const int bits = pair_bits(T), w0 = rs_digit(bits) < 4 ? 4 : rs_digit(bits);
       hipLaunchKernelGGL(k_gs_emit, dim3(grid_blocks(max_pairs, GS_EMIT)), dim3(256), 0, s, n, K, va, w.off, w.rect,
-                         w.hdr, w.pk_a, w.pv_a);
+                         w.hdr, (1u << w0) - 1u, w.pk_a, w.pv_a, w.hist);
       uint32_t *pa = w.pk_a, *pb = w.pk_b;
       int32_t *qa = w.pv_a, *qb = w.pv_b;
-      radix_sort(&pa, &qa, &pb, &qb, max_pairs, w.hdr + 1, pair_bits(T), w.hist, w.bsum, s);
-      hipLaunchKernelGGL(k_gs_ranges, dim3(grid_blocks(max_pairs < 8 * (int64_t)n ? max_pairs : 8 * (int64_t)n, 256)),
+      radix_sort(&pa, &qa, &pb, &qb, max_pairs, w.hdr + 1, bits, true, w.hist, w.bsum, s);
+      hipLaunchKernelGGL(k_gs_ranges, dim3(grid_blocks(max_pairs < 8 * (int64_t)n ? max_pairs : 8 * (int64_t)n, 1024)),
                          dim3(256), 0, s, pa, w.hdr, w.range);
     }
   }

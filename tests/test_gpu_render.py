@@ -332,14 +332,12 @@ def test_raster_classes_match_oracle(n, scale, size, split, t_min):
     gmu, gS, gcol, gop = torch.autograd.grad(ref, leaves, ibar.double().cpu())
     gS6 = torch.stack([gS[:, 0, 0], gS[:, 1, 1], gS[:, 2, 2], gS[:, 0, 1] + gS[:, 1, 0], gS[:, 0, 2] + gS[:, 2, 0],
                        gS[:, 1, 2] + gS[:, 2, 1]])
-    for name, got, want in zip(("mu", "sigma", "color", "opacity"), bars, (gmu.T, gS6, gcol.T, gop)):
-        e = (got.double().cpu() - want).abs().max().item()
-        assert e <= 1e-3 * want.abs().max().item(), (name, e, want.abs().max().item())
-    # a second call on the same workspace adds the same again (atomics: last bits differ)
-    one = [b.clone() for b in bars]
-    api.gs_render_adj(gc, *dev, img, ibar, ws, *bars)
-    for b, o in zip(bars, one):
-        assert (b - 2 * o).abs().max().item() <= 1e-5 * o.abs().max().item()
+    for calls in (1, 2):  # a second call on the same workspace adds the same again
+        for name, got, want in zip(("mu", "sigma", "color", "opacity"), bars, (gmu.T, gS6, gcol.T, gop)):
+            e = (got.double().cpu() - calls * want).abs().max().item()
+            assert e <= 1e-3 * calls * want.abs().max().item(), (name, calls, e, want.abs().max().item())
+        if calls == 1:
+            api.gs_render_adj(gc, *dev, img, ibar, ws, *bars)
 
 
 @pytest.mark.parametrize("size", [(41, 38), (16, 16)])
@@ -406,3 +404,26 @@ def test_nonfinite_colour_stays_in_its_pixels(n):
     assert touched.any() and not touched.all()
     assert torch.equal(torch.isnan(imgs[2]), touched)
     assert torch.equal(imgs[2][~touched], imgs[0][~touched])
+
+
+@pytest.mark.parametrize("n", [1, 2, 1023, 1025, 65_536, 65_537, 262_144, 262_145])
+def test_depth_and_tile_sort_sizes(n):
+    """Kernel counts at the edges of the sort's blocks and of its ways to add
+    up histograms (64 short blocks, 64 long ones, more), with depths on 64
+    levels only, so that most neighbours in the list are ties and the input
+    order decides.  Sampled pixels against the oracle, bounds as above."""
+    W, H = 150, 131
+    g = scenes.random_gaussians(n, n, width=W, height=H, scale=0.1 if n < 100 else 0.006, opacity=(0.3, 0.9),
+                                min_depth_gap=0.0)
+    z = np.round((g.mu[2] - 1.5) * 32) / 32 + 1.5
+    g.mu[:2] *= z / g.mu[2]
+    g.mu[2] = z
+    oc, gc = _cams(g.camera, alpha_min=1e-3, t_min=1e-3)
+    dev = _dev(g)
+    img, ws, _ = _render_gpu(gc, dev, max_pairs=90 if n < 100 else 16 * n)
+    rng = np.random.default_rng(n)
+    m = 24 if n > 100_000 else 96
+    i, j = rng.integers(0, W, m), rng.integers(0, H, m)
+    ref = orender.render(*_oracle_inputs(dev), oc, pixels=torch.tensor(np.stack([i + 0.5, j + 0.5], axis=1)))
+    err = (img[:, j, i].double().cpu() - ref).abs()
+    assert err.max().item() < 1.1e-3 and torch.quantile(err.flatten(), 0.95).item() < 2e-5
