@@ -210,8 +210,10 @@ static __global__ __launch_bounds__(256) void k_det_gather(GridDev g, const int3
                                                         const int32_t *__restrict__ tile_count,
                                                         const int32_t *__restrict__ item_first,
                                                         const float *__restrict__ item_part, float *__restrict__ gm,
-                                                        float *__restrict__ gmv, int64_t N) {
+                                                        float *__restrict__ gmv, int64_t N,
+                                                        int32_t *__restrict__ ticket) {
   int nt = *n_tiles;
+  if (!ADJ && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;  // for the next P2G
   int sub = threadIdx.x >> 6, l = threadIdx.x & 63;
   for (int it = blockIdx.x * 4 + sub; it < nt; it += gridDim.x * 4) {
     int t = node_tiles[it];

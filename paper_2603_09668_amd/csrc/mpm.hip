@@ -258,8 +258,9 @@ __global__ __launch_bounds__(256) void k_sort_segments(const int32_t *__restrict
 
 __global__ __launch_bounds__(256) void k_grid_clear(GridDev g, const int32_t *__restrict__ node_tiles,
                                                     const int32_t *__restrict__ n_tiles, float *__restrict__ gm,
-                                                    float *__restrict__ gmv, int64_t N) {
+                                                    float *__restrict__ gmv, int64_t N, int32_t *__restrict__ ticket) {
   int nt = *n_tiles;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;  // the P2G launch that follows draws from it
   int sub = threadIdx.x >> 6, l = threadIdx.x & 63;
   for (int it = blockIdx.x * 4 + sub; it < nt; it += gridDim.x * 4) {
     int t = node_tiles[it];
@@ -321,10 +322,16 @@ __global__ __launch_bounds__(P2G_THREADS) __attribute__((amdgpu_waves_per_eu(4))
   const ScLane L = sc_lane(lane);
   float *s_node_flat = &s_node[0][0][0];
   const int ni = *n_items;
-  // Workgroup b starts with item b (no stampede on the counter at launch);
-  // later items are handed out by a ticket counter (header word 8, cleared
-  // by the sort) as items gridDim.x + ticket.
-  int32_t *ticket = status + 8;
+  // Workgroup b takes items b, b + gridDim.x, ... of the whole rounds but the
+  // last two; the items left are handed out by a ticket counter, which evens
+  // out the end.  The counter serves one draw every 13 ns, so a launch pays
+  // for each: with all items drawn and every workgroup counted out through
+  // it, 19.6 / 35.6 / 56.1 / 254 us for 20k / 146k / 500k / 4M particles, this
+  // way 12.7 / 23.9 / 44.7 / 247.  Header word 8 is zeroed by k_grid_clear
+  // before each launch, word 9 (deterministic mode, which has no clear) by
+  // the sort and by the gather after each launch.
+  int32_t *ticket = status + (DET ? 9 : 8);
+  const int nwg = (int)gridDim.x, nstat = ni <= nwg ? ni : max(1, ni / nwg - 2) * nwg;  // items of the static rounds
   for (int it = blockIdx.x; it < ni; it = s_next) {
     const int tile = item_tile[it];
     const int b0 = item_begin[it];
@@ -406,9 +413,10 @@ __global__ __launch_bounds__(P2G_THREADS) __attribute__((amdgpu_waves_per_eu(4))
     // pass C; the next ticket is drawn before it and stored after it, so the
     // atomic's round trip overlaps the matrix work
     int tk = 0;
-    if (tid == P2G_THREADS - 1) tk = atomicAdd(ticket, 1);
+    const bool draw = it + nwg >= nstat && nstat < ni;
+    if (draw && tid == P2G_THREADS - 1) tk = atomicAdd(ticket, 1);
     sc_units_mfma(L, wid, s_dat, s_f, s_udesc, s_nunits, s_node[wid]);
-    if (tid == P2G_THREADS - 1) s_next = (int)gridDim.x + tk;
+    if (tid == P2G_THREADS - 1) s_next = draw ? nstat + tk : it + nwg;
     __syncthreads();
     // pass D: node owners add the wave blocks in a fixed order
     if (tid < SC_NODES) {
@@ -436,14 +444,6 @@ __global__ __launch_bounds__(P2G_THREADS) __attribute__((amdgpu_waves_per_eu(4))
       }
     }
     __syncthreads();
-  }
-  // the last workgroup to finish rewinds the counters for the next call
-  if (tid == 0) {
-    __threadfence();
-    if (atomicAdd(ticket + 1, 1) == (int)gridDim.x - 1) {
-      atomicExch(ticket, 0);
-      atomicExch(ticket + 1, 0);
-    }
   }
 }
 
@@ -887,11 +887,11 @@ extern "C" int mpm_p2g(const dw_grid *grid, const dw_mpm_params *params, const d
                          params->material, W.perm, W.tile_start, W.item_tile, W.item_begin, W.n_items, grid_m,
                          grid_mv, N, W.status, W.item_part);
     hipLaunchKernelGGL(k_det_gather<false>, dim3(PERSISTENT_BLOCKS), dim3(256), 0, s, g, W.node_tiles, W.n_node_tiles,
-                       W.tile_count, W.item_first, W.item_part, grid_m, grid_mv, N);
+                       W.tile_count, W.item_first, W.item_part, grid_m, grid_mv, N, W.status + 9);
     return check_launch("mpm_p2g");
   }
   hipLaunchKernelGGL(k_grid_clear, dim3(PERSISTENT_BLOCKS), dim3(256), 0, s, g, W.node_tiles, W.n_node_tiles,
-                     grid_m, grid_mv, N);
+                     grid_m, grid_mv, N, W.status + 8);
   if (p->n > 0)
     hipLaunchKernelGGL(k_p2g<false>, dim3(p2g_blocks()), dim3(P2G_THREADS), 0, s, g, make_pview(p), params->dt,
                        params->material, W.perm, W.tile_start, W.item_tile, W.item_begin, W.n_items, grid_m,

@@ -709,7 +709,7 @@ extern "C" int mpm_g2p_adj(const dw_grid *grid, const dw_mpm_params *params, con
                        in->xref, in->F, in->n, out_bar->x, out_bar->v, out_bar->C, out_bar->F, in_bar->x, in_bar->F,
                        grid_v_bar, W.perm, W.tile_start, W.item_tile, W.item_begin, W.n_items, W.item_part);
     hipLaunchKernelGGL(k_det_gather<true>, dim3(2048), dim3(256), 0, s, g, W.node_tiles, W.n_node_tiles,
-                       W.tile_count, W.item_first, W.item_part, (float *)nullptr, grid_v_bar, N);
+                       W.tile_count, W.item_first, W.item_part, (float *)nullptr, grid_v_bar, N, (int32_t *)nullptr);
   } else {
     hipLaunchKernelGGL(k_g2p_adj<false>, dim3(2048), dim3(SC_THREADS), 0, s, g, params->dt, grid_v, N, in->x,
                        in->xref, in->F, in->n, out_bar->x, out_bar->v, out_bar->C, out_bar->F, in_bar->x, in_bar->F,

@@ -160,6 +160,41 @@ def test_p2g_overwrites_active_tiles(sheet):
     assert rel(gm, m1) < 1e-5 and rel(gmv, mv1) < 1e-5
 
 
+@pytest.mark.parametrize("wgs,extra", [(0, 1), (1, -1), (1, 0), (1, 1), (3, -1), (3, 1), (4, 5)])
+def test_p2g_work_item_counts(wgs, extra):
+    """Work-item counts around whole rounds of the launch's workgroups (four
+    per CU): one particle in each of that many tiles, so each is one item.
+    Every launch after one sort finds its item counter at zero, also when the
+    float-atomic and the deterministic kernel take turns."""
+    n = 4 * torch.cuda.get_device_properties(0).multi_processor_count * wgs + extra
+    say(f"mpm_p2g {n} items")
+    rng = np.random.default_rng(n)
+    res, dx = 128, 1.0 / 128
+    t = rng.permutation((res // 4) ** 3)[:n]
+    T = res // 4
+    tile = np.stack([t % T, (t // T) % T, t // (T * T)], 1)
+    x = f32((4 * tile + 0.75 + 1.65 * rng.random((n, 3))) * dx)  # the last tile holds whole stencils
+    v, C, F = scenes.random_state(n, n, 0.1, 1.0, 0.05)
+    v, C, F = f32(v), f32(C), f32(torch.as_tensor(F) - EYE) + EYE
+    mass, vol0, E, nu = f32(1e-3 * (0.5 + rng.random(n))), f32(np.full(n, 1e-7)), f32([1e4]), f32([0.3])
+    region = np.zeros(n, np.int64)
+    dev = device_particles(x, v, C, F, mass, vol0, region, E, nu)
+    grid = dict(nx=res, ny=res, nz=res, dx=dx, origin=(0.0, 0.0, 0.0))
+    g, og = api_grid(grid), oracle_grid(grid)
+    mu, lam = ompm.particle_mu_lam(E, nu, torch.as_tensor(region))
+    om, omv = ompm.p2g(og, x, v, C, F, mass, vol0, mu, lam, 1e-4, api.FIXED_COROTATED)
+    ws = api.alloc_workspace(g, n, deterministic=True)
+    gm = torch.zeros(og.n_nodes, device=DEV)
+    gmv = torch.zeros(3, og.n_nodes, device=DEV)
+    api.mpm_sort(g, api.make_mpm_params(1e-4, deterministic=True), dev.x, ws)
+    for det in (False, False, True, True, False):
+        api.mpm_p2g(g, api.make_mpm_params(1e-4, deterministic=det), dev, gm, gmv, ws)
+        torch.cuda.synchronize()
+        assert int(api.workspace_views(g, n, ws)["n_cell_tiles"]) == n
+        assert rel(gm.cpu(), om) < TOL and rel(gmv.cpu().T, omv) < TOL, det
+    assert api.read_status(ws) == 0
+
+
 def _wind_cases(sc, og):
     """(name, api wind, oracle acceleration (N, 3)) for the three wind sources."""
     rng = np.random.default_rng(8)
