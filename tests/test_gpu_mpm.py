@@ -162,11 +162,11 @@ def test_p2g_overwrites_active_tiles(sheet):
 
 @pytest.mark.parametrize("wgs,extra", [(0, 1), (1, -1), (1, 0), (1, 1), (3, -1), (3, 1), (4, 5)])
 def test_p2g_work_item_counts(wgs, extra):
-    """Work-item counts around whole rounds of the launch's workgroups (four
+    """Work-item counts around whole rounds of the launch's workgroups (two
     per CU): one particle in each of that many tiles, so each is one item.
     Every launch after one sort finds its item counter at zero, also when the
     float-atomic and the deterministic kernel take turns."""
-    n = 4 * torch.cuda.get_device_properties(0).multi_processor_count * wgs + extra
+    n = 2 * torch.cuda.get_device_properties(0).multi_processor_count * wgs + extra
     say(f"mpm_p2g {n} items")
     rng = np.random.default_rng(n)
     res, dx = 128, 1.0 / 128
