@@ -152,6 +152,19 @@ int check_particles(const dw_particles *p, bool need_state) {
   return DW_OK;
 }
 
+// compute units of the current device (cached per device)
+int cu_count() {
+  static int cus[64] = {0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  if (cus[dev] == 0) {
+    int c = 0;
+    if (hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || c <= 0) c = 256;
+    cus[dev] = c;
+  }
+  return cus[dev];
+}
+
 }  // namespace dw
 
 extern "C" const char *dw_last_error(void) { return dw::g_err; }

@@ -11,6 +11,7 @@ namespace dw {
 // ------------------------------------------------------------ host errors
 int set_error(int code, const char *fmt, ...);
 int check_launch(const char *what);
+int cu_count();  // compute units of the current device
 
 #define DW_REQUIRE(cond, code, ...)                 \
   do {                                              \
@@ -262,8 +263,9 @@ __device__ __forceinline__ void polar_shift(const float *H, float *Y) {
 // Kirchhoff stress tau = P F^T from the shifted deformation gradient H = F - I.
 //   fixed-corotated: tau = 2 mu (F - R) F^T + lam (J - 1) J I, F - R = H - (R - I)
 //   Neo-Hookean:     tau = mu (F F^T - I) + lam log(J) I, F F^T - I = H + H^T + H H^T
+// Yout (optional): Y = R - I of the fixed-corotated stress.
 __device__ __forceinline__ void kirchhoff_shift(const float *H, float mu, float lam, int material, float *tau,
-                                                int32_t *status) {
+                                                int32_t *status, float *Yout = nullptr) {
   float Jm1 = det_shift(H);
   float J = 1.0f + Jm1;
   if (!(J > 0.f)) {
@@ -285,6 +287,7 @@ __device__ __forceinline__ void kirchhoff_shift(const float *H, float mu, float 
     polar_shift(H, Y);
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
+      if (Yout) Yout[i] = Y[i];
       D[i] = H[i] - Y[i];
       F[i] = H[i] + ((i % 4) == 0 ? 1.f : 0.f);
     }

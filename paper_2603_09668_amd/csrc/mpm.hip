@@ -768,19 +768,6 @@ namespace dw {
 
 constexpr int PERSISTENT_BLOCKS = 2048;
 
-// compute units of the current device (cached per device)
-static int cu_count() {
-  static int cus[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (cus[dev] == 0) {
-    int c = 0;
-    if (hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || c <= 0) c = 256;
-    cus[dev] = c;
-  }
-  return cus[dev];
-}
-
 // P2G grid: the workgroups that fit at once (two per compute unit), which
 // then draw work items from the ticket counter
 static unsigned p2g_blocks() { return (unsigned)(P2G_PER_CU * cu_count()); }

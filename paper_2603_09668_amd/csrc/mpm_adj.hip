@@ -13,7 +13,9 @@
 // affine matrix and Eq. deformation_update.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "dw_internal.h"
 #include "dw_kernels.h"
@@ -64,9 +66,9 @@ __device__ __forceinline__ void polar_vjp(const float *F, const float *R, const 
 //   fixed-corotated: tau = 2 mu (F - R) F^T + lam (J - 1) J I
 //     Fbar += 2 mu tb F + 2 mu tb^T (F - R) + polar_vjp(Rbar = -2 mu tb F)
 //             + lam (2J - 1) J tr(tb) F^{-T}
-// Also returns the cotangents of mu and lam.
-__device__ __forceinline__ void kirchhoff_vjp(const float *H, float mu, float lam, int material, const float *tb,
-                                              float *Fbar, float &mu_bar, float &lam_bar) {
+// Also returns the cotangents of mu and lam.  Y = R - I (fixed-corotated only).
+__device__ __forceinline__ void kirchhoff_vjp(const float *H, const float *Y, float mu, float lam, int material,
+                                              const float *tb, float *Fbar, float &mu_bar, float &lam_bar) {
   float F[9];
 #pragma unroll
   for (int q = 0; q < 9; ++q) F[q] = H[q] + ((q % 4) == 0 ? 1.f : 0.f);
@@ -91,8 +93,7 @@ __device__ __forceinline__ void kirchhoff_vjp(const float *H, float mu, float la
     mu_bar = mb;
     lam_bar = trt * log1pf(Jm1);
   } else {
-    float Y[9], R[9], D[9], TF[9], TtD[9], Rb[9], DFt[9];
-    polar_shift(H, Y);
+    float R[9], D[9], TF[9], TtD[9], Rb[9], DFt[9];
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
       D[q] = H[q] - Y[q];
@@ -116,6 +117,14 @@ __device__ __forceinline__ void kirchhoff_vjp(const float *H, float mu, float la
   }
 }
 
+// Weight and derivative of the wave-uniform offset oz alone: the z weights of
+// a layer loop need no registers between the layers.
+__device__ __forceinline__ void bspline_z(float f, int oz, float &w, float &dw) {
+  const float t = f - (1.5f - 0.5f * (float)oz), k = oz == 1 ? -1.0f : 0.5f;
+  w = (oz == 1 ? 0.75f : 0.0f) + k * t * t;
+  dw = 2.0f * k * t;
+}
+
 // three consecutive floats (the x-neighbours of a stencil row)
 struct AdjRow {
   float v[3];
@@ -128,6 +137,16 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+// Component q of a [rows][n] particle array at byte offset off = 4 p: a scalar
+// base and a 32-bit offset, so the many arrays take no vector address pairs
+// (n is below 2^31 / 9, the largest F index held in an int).
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(1))) T &at_particle(T *base, int q, int n, uint32_t off) {
+  uint64_t row = reinterpret_cast<uint64_t>(base + (size_t)q * n);
+  asm("" : "+s"(row));  // kept scalar
+  return *((__attribute__((address_space(1))) T *)row + (off >> 2));
+}
+
 struct PAdj {
   const float *x, *v, *C, *F, *mass, *vol0, *E, *nu;
   const float *xr;  // position reference or NULL
@@ -138,178 +157,272 @@ struct PAdj {
 };
 
 // ---------------------------------------------------------- reverse P2G
+// One particle per thread: 27 values in, 36 gathers of three x-neighbours, 24
+// adjoints read and written.  What bounds it is the chain of memory round
+// trips of a wave (256k particles are four waves per SIMD in all) and the
+// line lookups of the gathers (some 40 lines per wave and gather).  So the
+// round trips are few: the whole particle at once, the twelve rows of a
+// z-layer at once, the old adjoints at once (one += after the other costs a
+// round trip each); H and R - I wait in LDS meanwhile, which spares a second
+// polar decomposition, and E_bar takes one atomic per workgroup (one per wave
+// took 52 us of 4,000 waves).  256k particles 65 -> 34 us (77 MB of particle
+// data: 15 us), 20k 19.7 -> 15.5.
 // DET: the E adjoint is not added with atomics; every wave writes its
 // per-region sums (fixed-order wave reductions) to P.Epart and
 // k_ebar_reduce adds the waves in index order.
+constexpr int P2G_ADJ_THREADS = 512;  // largest workgroup (p2g_adj_threads chooses)
+
 template <bool DET>
-__global__ __launch_bounds__(256) void k_p2g_adj(GridDev g, PAdj P, float dt, int material,
-                                                 const float *__restrict__ mbar, const float *__restrict__ mvbar,
-                                                 int64_t N) {
-  int p = blockIdx.x * blockDim.x + threadIdx.x;
-  bool live = p < P.n;
+__global__ __launch_bounds__(P2G_ADJ_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_p2g_adj(
+    GridDev g, PAdj P, float dt, int material, const float *__restrict__ mbar, const float *__restrict__ mvbar,
+    int64_t N) {
+  // H and Y of every thread's particle over the row loop: [wave][18][64]
+  extern __shared__ float s_keep_all[];
+  float *s_keep = s_keep_all + (threadIdx.x >> 6) * (18 * 64) + (threadIdx.x & 63);
   const int n = P.n;
-  float Ebar_p = 0.f;
-  int r = 0;
-  if (live) {
-    const Coord cx = load_coord(P.xr, P.x, p, g.ox, g.inv_dx);
-    const Coord cy = load_coord(P.xr, P.x, (size_t)n + p, g.oy, g.inv_dx);
-    const Coord cz = load_coord(P.xr, P.x, 2 * (size_t)n + p, g.oz, g.inv_dx);
-    const float X = coord_sum(cx), Y = coord_sum(cy), Z = coord_sum(cz);
-    bool ok = isfinite(X) && isfinite(Y) && isfinite(Z) && fabsf(X) < 1e9f && fabsf(Y) < 1e9f && fabsf(Z) < 1e9f;
-    int bx = 0, by = 0, bz = 0;
-    if (ok) {
-      bx = base_of(X); by = base_of(Y); bz = base_of(Z);
-      ok = stencil_inside(g, bx, by, bz);
-    }
-    if (ok) {
-      float f[3] = {coord_frac(cx, bx), coord_frac(cy, by), coord_frac(cz, bz)};
-      float w[3][3], dw[3][3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        bspline_w(f[a], w[a]);
-        bspline_dw(f[a], dw[a]);
-      }
-      float F[9], Cm[9], tau[9], A[9];  // F holds H = F - I
+  int run_reg = -1;      // region of the wave's running E sum (float atomics)
+  float run_sum = 0.f;
+  for (int p = blockIdx.x * blockDim.x + threadIdx.x; (p & ~63) < n; p += gridDim.x * blockDim.x) {
+    const bool live = p < n;
+    const uint32_t off = 4u * (uint32_t)p;
+    float Ebar_p = 0.f;
+    int r = 0;
+    if (live) {
+      // all of the particle in one round trip
+      float F[9], Cm[9], vp[3];  // F holds H = F - I
 #pragma unroll
       for (int q = 0; q < 9; ++q) {
-        F[q] = P.F[q * n + p];
-        Cm[q] = P.C[q * n + p];
+        F[q] = at_particle(P.F, q, n, off);
+        Cm[q] = at_particle(P.C, q, n, off);
       }
-      float m = P.mass[p], V0 = P.vol0[p];
-      r = P.region[p];
-      float Er = P.E[r], nur = P.nu[r];
-      float mu, lam;
-      lame(Er, nur, mu, lam);
-      kirchhoff_shift(F, mu, lam, material, tau, nullptr);
-      float ks = dt * 4.0f * g.inv_dx * g.inv_dx;
 #pragma unroll
-      for (int q = 0; q < 9; ++q) A[q] = m * Cm[q] - ks * V0 * tau[q];
-      float mom[3] = {m * P.v[p], m * P.v[n + p], m * P.v[2 * n + p]};
-      const float dx = g.dx;
-      // Per node n (offset o, weight w_n, gradient gw_n, d_n = (o - f) dx):
-      //   v_bar += m w gb,  A_bar += w gb d^T,
-      //   x_bar += gw s - w A^T gb  with s = m mb + gb . (mom + A d).
-      // Sums that factor are taken once: G = sum w gb (v_bar = m G, and the
-      // A^T term is A^T G), O = sum w gb o^T (A_bar = dx (O - G f^T)), and
-      // mom + A d = c0 + dx A o with c0 = mom - dx A f, whose y/z part is
-      // constant along a stencil row.
-      float c0[3], Ax[3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        c0[a] = mom[a] - dx * (A[3 * a] * f[0] + A[3 * a + 1] * f[1] + A[3 * a + 2] * f[2]);
-        Ax[a] = dx * A[3 * a];
+      for (int a = 0; a < 3; ++a) vp[a] = at_particle(P.v, a, n, off);
+      const float m = at_particle(P.mass, 0, n, off), V0 = at_particle(P.vol0, 0, n, off);
+      const int rp = at_particle(P.region, 0, n, off);
+      const Coord cx = load_coord(P.xr, P.x, p, g.ox, g.inv_dx);
+      const Coord cy = load_coord(P.xr, P.x, (size_t)n + p, g.oy, g.inv_dx);
+      const Coord cz = load_coord(P.xr, P.x, 2 * (size_t)n + p, g.oz, g.inv_dx);
+      const float X = coord_sum(cx), Y = coord_sum(cy), Z = coord_sum(cz);
+      bool ok = isfinite(X) && isfinite(Y) && isfinite(Z) && fabsf(X) < 1e9f && fabsf(Y) < 1e9f && fabsf(Z) < 1e9f;
+      int bx = 0, by = 0, bz = 0;
+      if (ok) {
+        bx = base_of(X); by = base_of(Y); bz = base_of(Z);
+        ok = stencil_inside(g, bx, by, bz);
       }
-      float G[3] = {0.f, 0.f, 0.f}, X[3] = {0.f, 0.f, 0.f};
-      float O[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      // rows of the stencil one at a time (bounded register use), the three
-      // x-neighbours of a row read with one 12-byte load per array
+      if (ok) {
+        float f[3] = {coord_frac(cx, bx), coord_frac(cy, by), coord_frac(cz, bz)};
+        float tau[9], A[9];  // A holds dx A
+        r = rp;
+        float Er = P.E[r], nur = P.nu[r];
+        float mu, lam;
+        lame(Er, nur, mu, lam);
+        float Y[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        kirchhoff_shift(F, mu, lam, material, tau, nullptr, Y);
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+          s_keep[q * 64] = F[q];
+          s_keep[(9 + q) * 64] = Y[q];
+        }
+        float ks = dt * 4.0f * g.inv_dx * g.inv_dx;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) A[q] = g.dx * (m * Cm[q] - ks * V0 * tau[q]);
+        const float mom[3] = {m * vp[0], m * vp[1], m * vp[2]};
+        float w[2][3], dw[2][3];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          bspline_w(f[a], w[a]);
+          bspline_dw(f[a], dw[a]);
+        }
+        const float dx = g.dx;
+        // Per node n (offset o, weight w_n, gradient gw_n, d_n = (o - f) dx):
+        //   v_bar += m w gb,  A_bar += w gb d^T,
+        //   x_bar += gw s - w A^T gb  with s = m mb + gb . (mom + A d).
+        // Per row the x-neighbours reduce to Sw = sum w s, Sd = sum dw s, T = sum
+        // w gb and U = sum w (ox - fx) gb, which the y and z weights then scale
+        // (G = sum w gb: v_bar = m G, and the A^T term is A^T G).
+        float G[3] = {0.f, 0.f, 0.f}, X[3] = {0.f, 0.f, 0.f};
+        float O[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        // The three rows of a z-layer together: twelve 12-byte loads (the three
+        // x-neighbours of a row and array) in flight
 #pragma unroll 1
-      for (int r9 = 0; r9 < 9; ++r9) {
-        const int oy = r9 % 3, oz = r9 / 3;
-        const int64_t row = bx + (int64_t)g.nx * ((by + oy) + (int64_t)g.ny * (bz + oz));
-        AdjRow rm, r0, r1, r2;
-        __builtin_memcpy(&rm, mbar + row, sizeof(AdjRow));
-        __builtin_memcpy(&r0, mvbar + row, sizeof(AdjRow));
-        __builtin_memcpy(&r1, mvbar + N + row, sizeof(AdjRow));
-        __builtin_memcpy(&r2, mvbar + 2 * N + row, sizeof(AdjRow));
-        const float wyz = w[1][oy] * w[2][oz];
-        const float gwx = wyz * g.inv_dx, gwy = dw[1][oy] * w[2][oz] * g.inv_dx,
-                    gwz = w[1][oy] * dw[2][oz] * g.inv_dx;
-        float cy[3];
+        for (int oz = 0; oz < 3; ++oz) {
+          const int64_t row0 = bx + (int64_t)g.nx * (by + (int64_t)g.ny * (bz + oz));
+          AdjRow rm[3], rv[3][3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) cy[a] = c0[a] + dx * (A[3 * a + 1] * (float)oy + A[3 * a + 2] * (float)oz);
-        float RG[3] = {0.f, 0.f, 0.f};
+          for (int oy = 0; oy < 3; ++oy) {
+            const int64_t row = row0 + (int64_t)g.nx * oy;
+            __builtin_memcpy(&rm[oy], mbar + row, sizeof(AdjRow));
 #pragma unroll
-        for (int ox = 0; ox < 3; ++ox) {
-          const float wt = w[0][ox] * wyz;
-          const float gb[3] = {r0.v[ox], r1.v[ox], r2.v[ox]};
-          float s = m * rm.v[ox];
+            for (int a = 0; a < 3; ++a) __builtin_memcpy(&rv[oy][a], mvbar + a * N + row, sizeof(AdjRow));
+          }
+          float wz, dwz;
+          bspline_z(f[2], oz, wz, dwz);
+          const float dz = (float)oz - f[2];
+          float cz3[3], Gz[3] = {0.f, 0.f, 0.f};
 #pragma unroll
-          for (int a = 0; a < 3; ++a) s += gb[a] * (cy[a] + Ax[a] * (float)ox);
-          X[0] += dw[0][ox] * gwx * s;
-          X[1] += w[0][ox] * gwy * s;
-          X[2] += w[0][ox] * gwz * s;
+          for (int a = 0; a < 3; ++a) cz3[a] = mom[a] + A[3 * a + 2] * dz;
+#pragma unroll
+          for (int oy = 0; oy < 3; ++oy) {
+            float Sw = 0.f, Sd = 0.f, T[3] = {0.f, 0.f, 0.f}, U[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ox = 0; ox < 3; ++ox) {
+              float s = m * rm[oy].v[ox];
+#pragma unroll
+              for (int a = 0; a < 3; ++a) {
+                s += rv[oy][a].v[ox] * (cz3[a] + A[3 * a + 1] * ((float)oy - f[1]) + A[3 * a] * ((float)ox - f[0]));
+                const float t = w[0][ox] * rv[oy][a].v[ox];
+                T[a] += t;
+                U[a] += ((float)ox - f[0]) * t;
+              }
+              Sw += w[0][ox] * s;
+              Sd += dw[0][ox] * s;
+            }
+            const float wyz = w[1][oy] * wz;
+            X[0] += wyz * Sd;
+            X[1] += dw[1][oy] * wz * Sw;
+            X[2] += w[1][oy] * dwz * Sw;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+              const float t = wyz * T[a];
+              Gz[a] += t;
+              O[3 * a] += wyz * U[a];
+              O[3 * a + 1] += ((float)oy - f[1]) * t;
+            }
+          }
 #pragma unroll
           for (int a = 0; a < 3; ++a) {
-            const float t = wt * gb[a];
-            RG[a] += t;
-            O[3 * a] += (float)ox * t;
+            G[a] += Gz[a];
+            O[3 * a + 2] += dz * Gz[a];
           }
         }
+        // the old values of every adjoint in one round trip
+        float vo[3] = {0.f, 0.f, 0.f}, xo[3] = {0.f, 0.f, 0.f}, Co[9], Fo[9];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          G[a] += RG[a];
-          O[3 * a + 1] += (float)oy * RG[a];
-          O[3 * a + 2] += (float)oz * RG[a];
+        for (int q = 0; q < 9; ++q) Co[q] = Fo[q] = 0.f;
+        if (P.vb) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) vo[a] = at_particle(P.vb, a, n, off);
         }
-      }
-      float vbar[3], xbar[3], Abar[9];
+        if (P.xb) {
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        vbar[a] = m * G[a];
-        // d (A d) / d x = -A   ->   -A^T G
-        xbar[a] = X[a] - (A[a] * G[0] + A[3 + a] * G[1] + A[6 + a] * G[2]);
+          for (int a = 0; a < 3; ++a) xo[a] = at_particle(P.xb, a, n, off);
+        }
+        if (P.Cb) {
 #pragma unroll
-        for (int b = 0; b < 3; ++b) Abar[3 * a + b] = dx * (O[3 * a + b] - G[a] * f[b]);
-      }
-      if (P.vb) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) P.vb[a * n + p] += vbar[a];
-      }
-      if (P.xb) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) P.xb[a * n + p] += xbar[a];
-      }
-      if (P.Cb) {
-#pragma unroll
-        for (int q = 0; q < 9; ++q) P.Cb[q * n + p] += m * Abar[q];
-      }
-      if (P.Fb || P.Eb) {
-        float tb[9], Fb[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int q = 0; q < 9; ++q) tb[q] = -ks * V0 * Abar[q];
-        float mu_b, lam_b;
-        kirchhoff_vjp(F, mu, lam, material, tb, Fb, mu_b, lam_b);
+          for (int q = 0; q < 9; ++q) Co[q] = at_particle(P.Cb, q, n, off);
+        }
         if (P.Fb) {
 #pragma unroll
-          for (int q = 0; q < 9; ++q) P.Fb[q * n + p] += Fb[q];
+          for (int q = 0; q < 9; ++q) Fo[q] = at_particle(P.Fb, q, n, off);
         }
-        // Eq. young_poisson: d mu / d E = 1 / (2 (1 + nu)), d lam / d E = nu / ((1 + nu)(1 - 2 nu))
-        Ebar_p = mu_b / (2.f * (1.f + nur)) + lam_b * nur / ((1.f + nur) * (1.f - 2.f * nur));
+        float vbar[3], xbar[3], Abar[9];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          vbar[a] = m * G[a];
+          // d (A d) / d x = -A   ->   -A^T G
+          xbar[a] = g.inv_dx * (X[a] - (A[a] * G[0] + A[3 + a] * G[1] + A[6 + a] * G[2]));
+#pragma unroll
+          for (int b = 0; b < 3; ++b) Abar[3 * a + b] = dx * O[3 * a + b];
+        }
+        if (P.vb) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) at_particle(P.vb, a, n, off) = vo[a] + vbar[a];
+        }
+        if (P.xb) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) at_particle(P.xb, a, n, off) = xo[a] + xbar[a];
+        }
+        if (P.Cb) {
+#pragma unroll
+          for (int q = 0; q < 9; ++q) at_particle(P.Cb, q, n, off) = Co[q] + m * Abar[q];
+        }
+        if (P.Fb || P.Eb) {
+          float H[9], Yr[9], tb[9], Fb[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int q = 0; q < 9; ++q) {
+            tb[q] = -ks * V0 * Abar[q];
+            H[q] = s_keep[q * 64];
+            Yr[q] = s_keep[(9 + q) * 64];
+          }
+          float mu_b, lam_b;
+          kirchhoff_vjp(H, Yr, mu, lam, material, tb, Fb, mu_b, lam_b);
+          if (P.Fb) {
+#pragma unroll
+            for (int q = 0; q < 9; ++q) at_particle(P.Fb, q, n, off) = Fo[q] + Fb[q];
+          }
+          // Eq. young_poisson: d mu / d E = 1 / (2 (1 + nu)), d lam / d E = nu / ((1 + nu)(1 - 2 nu))
+          Ebar_p = mu_b / (2.f * (1.f + nur)) + lam_b * nur / ((1.f + nur) * (1.f - 2.f * nur));
+        }
       }
     }
-  }
-  if (P.Eb && DET) {
-    // lane l of the wave keeps the sum of region r0 + l; one store per entry
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    for (int r0 = 0; r0 < P.n_regions; r0 += 64) {
-      float mine_sum = 0.f;
-      unsigned long long pending = __ballot(live && r >= r0 && r < r0 + 64);
+    if (P.Eb && DET) {
+      // lane l of the wave keeps the sum of region r0 + l; one store per entry
+      const int lane = threadIdx.x & 63;
+      const int64_t wave = p >> 6;
+      for (int r0 = 0; r0 < P.n_regions; r0 += 64) {
+        float mine_sum = 0.f;
+        unsigned long long pending = __ballot(live && r >= r0 && r < r0 + 64);
+        while (pending) {
+          const int leader = __ffsll(pending) - 1;
+          const int rk = __shfl(r, leader, 64);
+          const bool mine = live && r == rk;
+          const float sum = wave_sum(mine ? Ebar_p : 0.f);
+          if (lane == rk - r0) mine_sum = sum;
+          pending &= ~__ballot(mine);
+        }
+        if (r0 + lane < P.n_regions) P.Epart[wave * P.n_regions + r0 + lane] = mine_sum;
+      }
+    } else if (P.Eb) {
+      // a wave holds few regions: it sums each over its lanes
+      unsigned long long pending = __ballot(live);
+      const int lane = threadIdx.x & 63;
+      if (!__ballot(live && r == run_reg)) {
+        if (run_reg >= 0 && lane == 0 && run_sum != 0.f) atomicAdd(&P.Eb[run_reg], run_sum);
+        run_reg = __builtin_amdgcn_readfirstlane(r);  // lane 0 of the loop is live
+        run_sum = 0.f;
+      }
       while (pending) {
         const int leader = __ffsll(pending) - 1;
         const int rk = __shfl(r, leader, 64);
         const bool mine = live && r == rk;
         const float sum = wave_sum(mine ? Ebar_p : 0.f);
-        if (lane == rk - r0) mine_sum = sum;
+        if (rk == run_reg) run_sum += sum;
+        else if (lane == leader && sum != 0.f) atomicAdd(&P.Eb[rk], sum);
         pending &= ~__ballot(mine);
       }
-      if (r0 + lane < P.n_regions) P.Epart[wave * P.n_regions + r0 + lane] = mine_sum;
-    }
-  } else if (P.Eb) {
-    // one atomic per (wave, region): a wave holds few regions, while
-    // per-lane atomics on a handful of addresses would serialise
-    unsigned long long pending = __ballot(live);
-    const int lane = threadIdx.x & 63;
-    while (pending) {
-      const int leader = __ffsll(pending) - 1;
-      const int rk = __shfl(r, leader, 64);
-      const bool mine = live && r == rk;
-      const float sum = wave_sum(mine ? Ebar_p : 0.f);
-      if (lane == leader && sum != 0.f) atomicAdd(&P.Eb[rk], sum);
-      pending &= ~__ballot(mine);
     }
   }
+  if (P.Eb && !DET) {
+    // the waves' running sums merged over the workgroup
+    __shared__ float s_sum[P2G_ADJ_THREADS / 64];
+    __shared__ int s_reg[P2G_ADJ_THREADS / 64];
+    const int nw = blockDim.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+      s_reg[threadIdx.x >> 6] = run_reg;
+      s_sum[threadIdx.x >> 6] = run_sum;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < nw && s_reg[threadIdx.x] >= 0) {
+      const int rk = s_reg[threadIdx.x];
+      bool lead = true;
+      float sum = 0.f;
+      for (int w = 0; w < nw; ++w) {
+        if (s_reg[w] != rk) continue;
+        lead = lead && w >= (int)threadIdx.x;
+        sum += s_sum[w];
+      }
+      if (lead && sum != 0.f) atomicAdd(&P.Eb[rk], sum);
+    }
+  }
+}
+
+// Workgroup size of the reverse P2G: the largest of 64 .. 512 that still
+// gives every CU one, so that a small set spreads over the chip and a large
+// one issues few E atomics.
+static int p2g_adj_threads(int n) {
+  int t = 64;
+  while (t < P2G_ADJ_THREADS && (int64_t)n >= (int64_t)2 * t * cu_count()) t *= 2;
+  return t;
 }
 
 // E adjoint of the deterministic reverse P2G: region r adds the per-wave sums
@@ -398,8 +511,8 @@ __global__ __launch_bounds__(256) void k_grid_update_adj(GridDev g, float dt, fl
 
 // Reverse G2P.  One workgroup per work item (a chunk of at most WORK_CHUNK
 // sorted particles of one cell tile), one particle per thread.  Each thread
-// redoes the forward gather of its particle (v_p and C_p), applies the
-// adjoints of the x, F and C updates and gathers x_bar; the scatter of the
+// applies the adjoints of the x, F and C updates and gathers the grid
+// velocities once, for C_p of the forward and for x_bar; the scatter of the
 // grid-velocity adjoint, v_bar_i += w_ip (vbt_p + kc Cbt_p (o - f_p)), has
 // the P2G form w (q + A o) with q = vbt - kc Cbt f, A = kc Cbt and runs as
 // the tile scatter of dw_scatter.h; node owners add the result into the
@@ -407,6 +520,11 @@ __global__ __launch_bounds__(256) void k_grid_update_adj(GridDev g, float dt, fl
 // their slots in index order and the node owners write the item's 6^3 block
 // to item_part instead, which k_det_gather<true> then adds to the grid
 // adjoint in a fixed order (bit-reproducible with a deterministic sort).
+// An item is a chain of phases with two workgroups per CU to overlap them
+// (128 registers, 66 KB of LDS): the particle is loaded in one round trip
+// ahead of the slot scan, one gather replaces two (v_p itself is not needed),
+// and the row sums factor.  256k particles (735 items) 60 -> 45 us, 20k 23.3
+// -> 19.
 template <bool DET>
 __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_g2p_adj(
     GridDev g, float dt, const float *__restrict__ gv, int64_t N, const float *__restrict__ x,
@@ -423,12 +541,13 @@ __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
   __shared__ int s_udesc[SC_MAX_UNITS];
   __shared__ int s_nunits;
   __shared__ float s_gv[3][SC_NODES];  // grid velocities of the item's 6^3 node region
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const ScLane L = sc_lane(lane);
   float *s_node_flat = &s_node[0][0][0];
   const int ni = *n_items;
   const float kc = 4.0f * g.inv_dx;
   for (int it = blockIdx.x; it < ni; it += gridDim.x) {
+    int tid = threadIdx.x;
+    asm("" : "+v"(tid));  // what depends on it is made in the item's own phases: held over the items it would spill
+    const int lane = tid & 63, wid = tid >> 6;
     const int tile = item_tile[it];
     const int b0 = item_begin[it];
     const int nb = min(WORK_CHUNK, tile_start[tile + 1] - b0);
@@ -437,7 +556,7 @@ __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
     for (int q = tid; q < SC_WAVES * SC_NODES; q += SC_THREADS)
       reinterpret_cast<float4 *>(s_node_flat)[q] = make_float4(0.f, 0.f, 0.f, 0.f);
     // every stencil of the item lies in the tile's 6^3 node region: stage its
-    // grid velocities once, for both gathers below
+    // grid velocities for the gather below
     if (tid < SC_NODES) {
       const int gx = 4 * tx + tid % SC_L, gy = 4 * ty + (tid / SC_L) % SC_L, gz = 4 * tz + tid / (SC_L * SC_L);
       float a0 = 0.f, a1 = 0.f, a2 = 0.f;
@@ -457,7 +576,33 @@ __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
     const int p = has ? perm[b0 + tid] : 0;
     Coord cx = {0.f, 0.f}, cy = {0.f, 0.f}, cz = {0.f, 0.f};
     int bx = 0, by = 0, bz = 0, c = -1;
+    // all of the particle in one round trip, which the slot scan hides
+    const uint32_t off = 4u * (uint32_t)p;
+    float Fp[9], Fo[9], Co[9], vo[3], xo[3];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) Fp[q] = Fo[q] = Co[q] = 0.f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) vo[a] = xo[a] = 0.f;
     if (has) {
+      if (Fob) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+          Fo[q] = at_particle(Fob, q, n, off);
+          Fp[q] = at_particle(F, q, n, off);
+        }
+      }
+      if (Cob) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) Co[q] = at_particle(Cob, q, n, off);
+      }
+      if (vob) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) vo[a] = at_particle(vob, a, n, off);
+      }
+      if (xob) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) xo[a] = at_particle(xob, a, n, off);
+      }
       cx = load_coord(xr, x, p, g.ox, g.inv_dx);
       cy = load_coord(xr, x, (size_t)n + p, g.oy, g.inv_dx);
       cz = load_coord(xr, x, 2 * (size_t)n + p, g.oz, g.inv_dx);
@@ -485,104 +630,29 @@ __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
         slot = atomicAdd(&s_cur[c], 1);
       }
       float f[3] = {coord_frac(cx, bx), coord_frac(cy, by), coord_frac(cz, bz)};
-      float w[3][3], dw[3][3];
+      float w[2][3], dw[2][3];
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
+      for (int a = 0; a < 2; ++a) {
         bspline_w(f[a], w[a]);
         bspline_dw(f[a], dw[a]);
       }
-      // forward gather: v_p and C_p
-      float vp[3] = {0.f, 0.f, 0.f};
-      float B[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-      for (int r9 = 0; r9 < 9; ++r9) {
-        const int oy = r9 % 3, oz = r9 / 3;
-        const int li = (bx - 4 * tx) + SC_L * ((by - 4 * ty + oy) + SC_L * (bz - 4 * tz + oz));
-        AdjRow r0, r1, r2;
-#pragma unroll
-        for (int ox = 0; ox < 3; ++ox) {
-          r0.v[ox] = s_gv[0][li + ox];
-          r1.v[ox] = s_gv[1][li + ox];
-          r2.v[ox] = s_gv[2][li + ox];
-        }
-#pragma unroll
-        for (int ox = 0; ox < 3; ++ox) {
-          const float wt = w[0][ox] * w[1][oy] * w[2][oz];
-          const float vi[3] = {r0.v[ox], r1.v[ox], r2.v[ox]};
-          const float o[3] = {(float)ox - f[0], (float)oy - f[1], (float)oz - f[2]};
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            vp[a] += wt * vi[a];
-#pragma unroll
-            for (int b = 0; b < 3; ++b) B[3 * a + b] += wt * vi[a] * o[b];
-          }
-        }
-      }
-      float Cn[9], Fp[9], Fo[9], Cbt[9], vbt[3];
-#pragma unroll
-      for (int q = 0; q < 9; ++q) {
-        Cn[q] = kc * B[q];
-        Fp[q] = F[q * n + p] + ((q % 4) == 0 ? 1.f : 0.f);  // stored as F - I
-        Fo[q] = Fob ? Fob[q * n + p] : 0.f;
-        Cbt[q] = Cob ? Cob[q * n + p] : 0.f;
-      }
       // F' = (I + dt C) F:  Fbar += (I + dt C)^T Fbar',  Cbar += dt Fbar' F^T
+      float Cbt[9], vbt[3];
       if (Fob) {
-        float G[9], GtFo[9], FoFt[9];
-#pragma unroll
-        for (int q = 0; q < 9; ++q) G[q] = dt * Cn[q];
-        G[0] += 1.f;
-        G[4] += 1.f;
-        G[8] += 1.f;
-        matmul3_atb(G, Fo, GtFo);
+        float FoFt[9];
+        Fp[0] += 1.f;  // stored as F - I
+        Fp[4] += 1.f;
+        Fp[8] += 1.f;
         matmul3_abt(Fo, Fp, FoFt);
-        if (Fb) {
 #pragma unroll
-          for (int q = 0; q < 9; ++q) Fb[q * n + p] += GtFo[q];
-        }
+        for (int q = 0; q < 9; ++q) Cbt[q] = Co[q] + dt * FoFt[q];
+      } else {
 #pragma unroll
-        for (int q = 0; q < 9; ++q) Cbt[q] += dt * FoFt[q];
+        for (int q = 0; q < 9; ++q) Cbt[q] = Co[q];
       }
       // x' = x + dt v_p
 #pragma unroll
-      for (int a = 0; a < 3; ++a) vbt[a] = (vob ? vob[a * n + p] : 0.f) + dt * (xob ? xob[a * n + p] : 0.f);
-      // x_bar: gradient of the gather through the weights and the offsets
-      float xbar[3] = {xob ? xob[p] : 0.f, xob ? xob[n + p] : 0.f, xob ? xob[2 * n + p] : 0.f};
-#pragma unroll 1
-      for (int r9 = 0; r9 < 9; ++r9) {
-        const int oy = r9 % 3, oz = r9 / 3;
-        const int li = (bx - 4 * tx) + SC_L * ((by - 4 * ty + oy) + SC_L * (bz - 4 * tz + oz));
-        AdjRow r0, r1, r2;
-#pragma unroll
-        for (int ox = 0; ox < 3; ++ox) {
-          r0.v[ox] = s_gv[0][li + ox];
-          r1.v[ox] = s_gv[1][li + ox];
-          r2.v[ox] = s_gv[2][li + ox];
-        }
-#pragma unroll
-        for (int ox = 0; ox < 3; ++ox) {
-          const float wt = w[0][ox] * w[1][oy] * w[2][oz];
-          const float gw[3] = {dw[0][ox] * w[1][oy] * w[2][oz] * g.inv_dx, w[0][ox] * dw[1][oy] * w[2][oz] * g.inv_dx,
-                               w[0][ox] * w[1][oy] * dw[2][oz] * g.inv_dx};
-          const float o[3] = {(float)ox - f[0], (float)oy - f[1], (float)oz - f[2]};
-          const float vi[3] = {r0.v[ox], r1.v[ox], r2.v[ox]};
-          float Co[3], CtV[3];
-#pragma unroll
-          for (int a = 0; a < 3; ++a) {
-            Co[a] = Cbt[3 * a] * o[0] + Cbt[3 * a + 1] * o[1] + Cbt[3 * a + 2] * o[2];
-            CtV[a] = Cbt[a] * vi[0] + Cbt[3 + a] * vi[1] + Cbt[6 + a] * vi[2];
-          }
-          const float sdot =
-              vi[0] * vbt[0] + vi[1] * vbt[1] + vi[2] * vbt[2] + kc * (vi[0] * Co[0] + vi[1] * Co[1] + vi[2] * Co[2]);
-          // d o / d x = -inv_dx I
-#pragma unroll
-          for (int a = 0; a < 3; ++a) xbar[a] += gw[a] * sdot - wt * kc * g.inv_dx * CtV[a];
-        }
-      }
-      if (xb) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) xb[a * n + p] += xbar[a];
-      }
+      for (int a = 0; a < 3; ++a) vbt[a] = vo[a] + dt * xo[a];
       // scatter features: q = vbt - kc Cbt f, A = kc Cbt
       float A[9], qv[3];
 #pragma unroll
@@ -590,11 +660,90 @@ __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 #pragma unroll
       for (int a = 0; a < 3; ++a) qv[a] = vbt[a] - (A[3 * a] * f[0] + A[3 * a + 1] * f[1] + A[3 * a + 2] * f[2]);
       sc_stage(s_dat, s_f, slot, f, 0.f, qv, A);
+      // One gather of the stencil's grid velocities v_i gives both C_p = kc
+      // sum w v (o - f)^T and the gradient of the gather through the weights
+      // and the offsets, x_bar += gw s - (w / dx) A^T v with s = v . (vbt + A (o - f))
+      // (d o / d x = -I / dx).  Per row the x-neighbours reduce to V = sum w v,
+      // D = sum w (ox - fx) v, Sw = sum w s and Sd = sum dw s.
+      float B[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      float X[3] = {0.f, 0.f, 0.f}, G[3] = {0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int oz = 0; oz < 3; ++oz) {
+        const int lz = (bx - 4 * tx) + SC_L * ((by - 4 * ty) + SC_L * (bz - 4 * tz + oz));
+        float wz, dwz;
+        bspline_z(f[2], oz, wz, dwz);
+        float qz[3], Gz[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) qz[a] = vbt[a] + A[3 * a + 2] * ((float)oz - f[2]);
+#pragma unroll
+        for (int oy = 0; oy < 3; ++oy) {
+          float Sw = 0.f, Sd = 0.f, V[3] = {0.f, 0.f, 0.f}, D[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+          for (int ox = 0; ox < 3; ++ox) {
+            float sd = 0.f;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+              const float vi = s_gv[a][lz + SC_L * oy + ox];
+              sd += vi * (qz[a] + A[3 * a + 1] * ((float)oy - f[1]) + A[3 * a] * ((float)ox - f[0]));
+              const float t = w[0][ox] * vi;
+              V[a] += t;
+              D[a] += ((float)ox - f[0]) * t;
+            }
+            Sw += w[0][ox] * sd;
+            Sd += dw[0][ox] * sd;
+          }
+          const float wyz = w[1][oy] * wz;
+          X[0] += wyz * Sd;
+          X[1] += dw[1][oy] * wz * Sw;
+          X[2] += w[1][oy] * dwz * Sw;
+#pragma unroll
+          for (int a = 0; a < 3; ++a) {
+            const float t = wyz * V[a];
+            Gz[a] += t;
+            B[3 * a] += wyz * D[a];
+            B[3 * a + 1] += ((float)oy - f[1]) * t;
+          }
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          G[a] += Gz[a];
+          B[3 * a + 2] += ((float)oz - f[2]) * Gz[a];
+        }
+      }
+      float Fbo[9], xbo[3];  // old values in one round trip
+      if (Fob && Fb) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) Fbo[q] = at_particle(Fb, q, n, off);
+      }
+      if (xb) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) xbo[a] = at_particle(xb, a, n, off);
+      }
+      if (Fob && Fb) {
+        float Gm[9], GtFo[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) Gm[q] = dt * (kc * B[q]) + ((q % 4) == 0 ? 1.f : 0.f);
+        matmul3_atb(Gm, Fo, GtFo);
+#pragma unroll
+        for (int q = 0; q < 9; ++q) at_particle(Fb, q, n, off) = Fbo[q] + GtFo[q];
+      }
+      if (xb) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+          at_particle(xb, a, n, off) =
+              xbo[a] + (xo[a] + g.inv_dx * (X[a] - (A[a] * G[0] + A[3 + a] * G[1] + A[6 + a] * G[2])));
+      }
     }
     __syncthreads();
+    int lane_now = lane;
+    asm("" : "+v"(lane_now));  // likewise the 30 constants of sc_lane
+    const ScLane L = sc_lane(lane_now);
     sc_units_mfma(L, wid, s_dat, s_f, s_udesc, s_nunits, s_node[wid]);
     __syncthreads();
-    if (tid < SC_NODES) {
+    int node_now = tid;
+    asm("" : "+v"(node_now));  // likewise
+    if (node_now < SC_NODES) {
+      const int tid = node_now;
       float s0 = 0.f, s1 = 0.f, s2 = 0.f;
 #pragma unroll
       for (int w = 0; w < SC_WAVES; ++w) {
@@ -646,8 +795,8 @@ extern "C" int mpm_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, con
   GridDev g = make_grid(grid);
   int64_t N = (int64_t)grid->nx * grid->ny * grid->nz;
   hipStream_t s = (hipStream_t)stream;
-  const unsigned blocks = grid_blocks(p->n, 256);
   if (params->deterministic && E_bar) {
+    const unsigned blocks = grid_blocks(p->n, 256);
     Workspace W;
     rc = bind_workspace(grid, p->n, ws, ws_bytes, &W, 1);
     if (rc) return rc;
@@ -655,13 +804,16 @@ extern "C" int mpm_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, con
     DW_REQUIRE(waves * p->n_regions <= W.item_part_floats, DW_EWORKSPACE,
                "mpm_p2g_adj: %d regions need more deterministic scratch than the workspace holds", p->n_regions);
     P.Epart = W.item_part;
-    hipLaunchKernelGGL(k_p2g_adj<true>, dim3(blocks), dim3(256), 0, s, g, P, params->dt, params->material,
-                       grid_m_bar, grid_mv_bar, N);
-    hipLaunchKernelGGL(k_ebar_reduce, dim3(grid_blocks(p->n_regions, 64)), dim3(64), 0, s, W.item_part, waves,
-                       p->n_regions, E_bar);
+    hipLaunchKernelGGL(k_p2g_adj<true>, dim3(blocks), dim3(256), 18 * 256 * sizeof(float), s, g, P, params->dt,
+                       params->material, grid_m_bar, grid_mv_bar, N);
+    hipLaunchKernelGGL(k_ebar_reduce, dim3(grid_blocks(p->n_regions, 64)), dim3(64), 0, s, W.item_part,
+                       ((int64_t)p->n + 63) / 64, p->n_regions, E_bar);
   } else {
-    hipLaunchKernelGGL(k_p2g_adj<false>, dim3(blocks), dim3(256), 0, s, g, P, params->dt, params->material,
-                       grid_m_bar, grid_mv_bar, N);
+    const int threads = p2g_adj_threads(p->n);
+    // at most the workgroups that fit at once: four waves per SIMD
+    const unsigned blocks = std::min(grid_blocks(p->n, threads), (unsigned)(1024 / threads * cu_count()));
+    hipLaunchKernelGGL(k_p2g_adj<false>, dim3(blocks), dim3(threads), 18 * threads * sizeof(float), s, g, P,
+                       params->dt, params->material, grid_m_bar, grid_mv_bar, N);
   }
   return check_launch("mpm_p2g_adj");
 }

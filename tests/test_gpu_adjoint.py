@@ -13,7 +13,7 @@ from oracle import mpm as ompm
 from oracle import wind as owind
 from paper_2603_09668_amd import api, scenes
 
-from gpu_util import (DEV, EYE, api_grid, f32, mat_from_dev, mat_to_dev, oracle_grid, say, scene_state,
+from gpu_util import (DEV, EYE, api_grid, device_particles, f32, mat_from_dev, mat_to_dev, oracle_grid, say, scene_state,
                       vec_from_dev, vec_to_dev)
 
 pytestmark = pytest.mark.gpu
@@ -75,6 +75,83 @@ def test_p2g_adj(scene, material, det):
     say("  " + " ".join(f"{k}={e:.2e}" for k, e in errs.items()))
     for k, e in errs.items():
         assert e < TOL, k
+
+
+def _p2g_adj_sizes():
+    """Particle counts around the workgroup sizes (64 .. 512 threads: a
+    workgroup per CU) and above what fits the chip at once."""
+    cu = torch.cuda.get_device_properties(0).multi_processor_count if torch.cuda.is_available() else 256
+    return [1, 65, 128 * cu - 1, 128 * cu, 512 * cu + 3, 1024 * cu, 1024 * cu + 1, 2500 * cu + 77]
+
+
+@pytest.mark.parametrize("regions", ["one", "blocks", "mixed"])
+@pytest.mark.parametrize("i", range(8))
+def test_p2g_adj_sizes(i, regions):
+    """A thousand particles repeated n times, with old values in the adjoint
+    arrays; E_bar against the oracle's contribution of each particle.  The
+    regions: one, runs of a few thousand particles, or mixed in every wave."""
+    n, n0 = _p2g_adj_sizes()[i], 1000
+    say(f"mpm_p2g_adj n={n} regions={regions}")
+    rng = np.random.default_rng(100 + i)
+    grid = dict(nx=32, ny=32, nz=32, dx=1.0 / 32, origin=(0.0, 0.0, 0.0))
+    og, g = oracle_grid(grid), api_grid(grid)
+    x = f32(0.1 + 0.8 * rng.random((n0, 3)))
+    v, C, F = (f32(a) for a in scenes.random_state(3, n0, 0.1, 1.0, 0.05))
+    F = f32(F - EYE) + EYE
+    mass, vol0 = f32(1e-3 * (0.5 + rng.random(n0))), f32(1e-5 * (0.5 + rng.random(n0)))
+    leaf = [t.clone().requires_grad_(True) for t in (x, v, C, F, torch.full((n0,), 1e4, dtype=torch.float64))]
+    nu = torch.full((n0,), f32(0.3).item(), dtype=torch.float64)
+    mu, lam = ompm.particle_mu_lam(leaf[4], nu, torch.arange(n0))
+    m, mv = ompm.p2g(og, *leaf[:4], mass, vol0, mu, lam, 1e-3, api.FIXED_COROTATED)
+    mbar, mvbar = f32(rng.standard_normal(og.n_nodes)), f32(rng.standard_normal((og.n_nodes, 3)))
+    grads = torch.autograd.grad((m * mbar).sum() + (mv * mvbar).sum(), leaf)
+    who = torch.arange(n) % n0
+    R = dict(one=1, blocks=5, mixed=70)[regions]
+    region = {"one": torch.zeros(n, dtype=torch.long), "blocks": (torch.arange(n) // 3000) % R,
+              "mixed": torch.as_tensor(rng.integers(0, R, n))}[regions]
+    dev = device_particles(x[who], v[who], C[who], F[who], mass[who], vol0[who], region, np.full(R, 1e4),
+                           np.full(R, 0.3))
+    old = [f32(rng.standard_normal((k, n))).float().to(DEV) for k in (3, 3, 9, 9)]
+    bars = [t.clone() for t in old]
+    Eb = torch.zeros(R, device=DEV)
+    api.mpm_p2g_adj(g, api.make_mpm_params(1e-3), dev, mbar.float().to(DEV), mvbar.T.contiguous().float().to(DEV),
+                    *bars, Eb)
+    torch.cuda.synchronize()
+    for name, b, o, gr in zip("xvCF", bars, old, grads):
+        want = gr.reshape(n0, -1)[who].T
+        err = (b.double().cpu() - o.double().cpu() - want).norm() / (want.norm() + o.double().cpu().norm())
+        assert err < TOL, name
+    want = torch.zeros(R, dtype=torch.float64).index_add_(0, region, grads[4][who])
+    size = torch.zeros(R, dtype=torch.float64).index_add_(0, region, grads[4][who].abs())
+    assert ((Eb.double().cpu() - want).abs() <= TOL * size).all()
+
+
+def test_g2p_adj_options(scene):
+    """The reverse G2P is linear in its four cotangents: single ones (the rest
+    NULL) add up to all of them, with and without x_bar and F_bar."""
+    st, dev = scene_state(scene, seed=17)
+    g, n = api_grid(scene.grid), scene.n
+    N = oracle_grid(scene.grid).n_nodes
+    rng = np.random.default_rng(18)
+    gv = f32(0.3 * rng.standard_normal((3, N))).float().to(DEV)
+    cot = [f32(rng.standard_normal((k, n))).float().to(DEV) for k in (3, 3, 9, 9)]
+    prm = api.make_mpm_params(1e-3)
+    ws = api.alloc_workspace(g, n)
+    api.mpm_sort(g, prm, dev.x, ws)
+
+    def run(c, xb, Fb):
+        gvb = torch.zeros(3, N, device=DEV)
+        api.mpm_g2p_adj(g, prm, gv, dev, *c, xb, Fb, gvb, ws)
+        return gvb.double()
+
+    xb, Fb = torch.zeros_like(dev.x), torch.zeros_like(dev.F)
+    whole = run(cot, xb, Fb)
+    xs, Fs = torch.zeros_like(dev.x), torch.zeros_like(dev.F)
+    parts = [run([c if k == j else None for k, c in enumerate(cot)], xs, Fs) for j in range(4)]
+    torch.cuda.synchronize()
+    assert rel2(sum(parts), whole) < TOL and rel2(xs, xb) < TOL and rel2(Fs, Fb) < TOL
+    for args in ((None, Fs), (xs, None), (None, None)):
+        assert rel2(run(cot, *args), whole) < TOL
 
 
 def test_grid_update_adj(scene):
