@@ -108,6 +108,11 @@ inline unsigned grid_blocks(int64_t work, int block) {
   return (unsigned)(b < 1 ? 1 : b);
 }
 
+// Workgroups (four waves, a node tile per wave at a time) of a kernel that
+// walks the active node tiles, of which the host knows only that they are at
+// most T.
+inline unsigned node_blocks(int64_t T) { return (unsigned)(T < 8192 ? (T + 3) / 4 : 2048); }
+
 // ---------------------------------------------------- device math helpers
 __device__ __forceinline__ float det3(const float *m) {
   return m[0] * (m[4] * m[8] - m[5] * m[7]) - m[1] * (m[3] * m[8] - m[5] * m[6]) +

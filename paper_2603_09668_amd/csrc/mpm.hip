@@ -85,17 +85,6 @@ __global__ void k_sort_keys(GridDev g, const float *__restrict__ x, const float 
   }
 }
 
-// wave64 inclusive scan
-__device__ __forceinline__ int wave_incl_scan(int v) {
-  int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int t = __shfl_up(v, o, 64);
-    if (lane >= o) v += t;
-  }
-  return v;
-}
-
 // Block-wide exclusive scans of the four tile rows at once (SCAN_BLOCK-thread
 // block, two barriers in all): ex[r] = sum of v[r] over the threads before
 // this one, tot[r] = the block's total.
@@ -106,7 +95,7 @@ __device__ __forceinline__ void block_excl_scan4(const int v[4], int ex[4], int 
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   int inc[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) inc[r] = wave_incl_scan(v[r]);
+  for (int r = 0; r < 4; ++r) inc[r] = sc_wave_scan(v[r]);
   if (lane == 63)
 #pragma unroll
     for (int r = 0; r < 4; ++r) lds[wid][r] = inc[r];
@@ -115,7 +104,7 @@ __device__ __forceinline__ void block_excl_scan4(const int v[4], int ex[4], int 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int t = lane < SCAN_WAVES ? lds[lane][r] : 0;
-      const int ti = wave_incl_scan(t);
+      const int ti = sc_wave_scan(t);
       if (lane < SCAN_WAVES) lds[SCAN_WAVES + lane][r] = ti - t;
       if (lane == SCAN_WAVES - 1) lds[2 * SCAN_WAVES][r] = ti;
     }
@@ -127,6 +116,12 @@ __device__ __forceinline__ void block_excl_scan4(const int v[4], int ex[4], int 
     tot[r] = lds[2 * SCAN_WAVES][r];
   }
 }
+
+// Up to this many blocks the final pass adds up the tiles before it itself
+// instead of reading block sums, which spares a launch.  Scan in all, without
+// and with it: 512 tiles 7.1 -> 2.8 us, 15,625 tiles (31 blocks) 9.3 -> 6.0;
+// at 32,768 tiles (64 blocks) the two passes' 8.0 are less than the one's 9.6.
+constexpr int64_t SCAN_DIRECT = 32;
 
 // the four rows of tile i: particle count, node-tile flag, occupied, work items
 __device__ __forceinline__ void tile_rows(const int32_t *__restrict__ count, const int32_t *__restrict__ flag,
@@ -149,9 +144,8 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_reduce(const int32_t *__res
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v[r] += __shfl_xor(v[r], o, 64);
-    if (lane == 0) s_red[wid][r] = v[r];
+    const int t = sc_wave_scan(v[r]);
+    if (lane == 63) s_red[wid][r] = t;
   }
   __syncthreads();
   if (threadIdx.x < 4) {
@@ -163,47 +157,56 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_reduce(const int32_t *__res
 
 // Final pass: tile offsets, the compacted active cell / node tile lists and
 // the work items (a cell tile cut into chunks of at most WORK_CHUNK sorted
-// particles: item = (tile, first particle)).  Each block adds up the block
-// sums of the blocks before it itself (there are few: T / SCAN_BLOCK per
-// row), and block 0 writes the four totals.
+// particles: item = (tile, first particle)).  Each block adds up what lies
+// before it itself: the block sums of k_scan_reduce, or with DIRECT the tiles
+// (SCAN_DIRECT says when).  The last block writes the four totals.  The
+// kernel is one chain of a few dependent steps; its wave sums and scans run
+// in registers (LDS shuffles took 2 of its 5 us).
+template <bool DIRECT>
 __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_final(
     const int32_t *__restrict__ count, const int32_t *__restrict__ flag, int64_t T,
     const int32_t *__restrict__ block_sums, int64_t NB, int32_t *__restrict__ tile_start,
     int32_t *__restrict__ cell_tiles, int32_t *__restrict__ node_tiles, int32_t *__restrict__ item_tile,
     int32_t *__restrict__ item_begin, int32_t *__restrict__ item_first, int32_t *__restrict__ totals /* [4] */) {
   __shared__ int lds[2 * SCAN_WAVES + 1][4];
-  __shared__ int s_red[SCAN_WAVES][8];
-  __shared__ int s_sum[8];
-  // per row: the sum over the blocks before this one (0..3) and over all (4..7),
-  // one block-wide reduction of the eight values
-  int acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int64_t b = threadIdx.x; b < NB; b += SCAN_BLOCK) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int v = block_sums[r * NB + b];
-      acc[4 + r] += v;
-      if (b < (int64_t)blockIdx.x) acc[r] += v;
-    }
-  }
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc[r] += __shfl_xor(acc[r], o, 64);
-    if (lane == 0) s_red[wid][r] = acc[r];
-  }
-  // the block's own rows are scanned while the reduction above settles
+  __shared__ int s_red[SCAN_WAVES][4];
+  __shared__ int s_sum[4];
   const int64_t i = (int64_t)blockIdx.x * SCAN_BLOCK + threadIdx.x;
   int v[4], ex[4], tot[4];
   tile_rows(count, flag, T, i, v);
+  int acc[4] = {0, 0, 0, 0};  // per row: the sum over the blocks before this one
+  if (DIRECT) {
+    // whole blocks: four tiles per load, both arrays 256-byte aligned
+    for (int q = threadIdx.x; q < (int)blockIdx.x * (SCAN_BLOCK / 4); q += SCAN_BLOCK) {
+      const int4 c4 = reinterpret_cast<const int4 *>(count)[q], f4 = reinterpret_cast<const int4 *>(flag)[q];
+      const int c[4] = {c4.x, c4.y, c4.z, c4.w}, fl[4] = {f4.x, f4.y, f4.z, f4.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc[0] += c[e];
+        acc[1] += fl[e] != 0;
+        acc[2] += c[e] > 0;
+        acc[3] += (c[e] + WORK_CHUNK - 1) / WORK_CHUNK;
+      }
+    }
+  } else {
+    for (int64_t b = threadIdx.x; b < (int64_t)blockIdx.x; b += SCAN_BLOCK)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] += block_sums[r * NB + b];
+  }
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int t = sc_wave_scan(acc[r]);
+    if (lane == 63) s_red[wid][r] = t;
+  }
   block_excl_scan4(v, ex, tot, lds);  // its barriers also publish s_red
-  if (threadIdx.x < 8) {
+  if (threadIdx.x < 4) {
     int t = 0;
     for (int w = 0; w < SCAN_WAVES; ++w) t += s_red[w][threadIdx.x];
     s_sum[threadIdx.x] = t;
+    if (blockIdx.x == gridDim.x - 1) totals[threadIdx.x] = t + lds[2 * SCAN_WAVES][threadIdx.x];
   }
   __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x < 4) totals[threadIdx.x] = s_sum[4 + threadIdx.x];
   if (i < T) {
     const int ec = ex[0] + s_sum[0], ef = ex[1] + s_sum[1], en = ex[2] + s_sum[2], eh = ex[3] + s_sum[3];
     const int c = v[0], ch = v[3];
@@ -793,11 +796,17 @@ int run_sort(const dw_grid *grid, int deterministic, const float *x, const float
   if (n > 0)
     hipLaunchKernelGGL(k_sort_keys, dim3(grid_blocks(n, 256)), dim3(256), 0, s, g, x, xref, n, W.key, W.rank,
                        W.tile_count, W.node_flag, W.status);
-  hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)NB), dim3(SCAN_BLOCK), 0, s, W.tile_count, W.node_flag, T,
-                     W.block_sums, NB);
-  hipLaunchKernelGGL(k_scan_final, dim3((unsigned)NB), dim3(SCAN_BLOCK), 0, s, W.tile_count, W.node_flag, T,
-                     W.block_sums, NB, W.tile_start, W.cell_tiles, W.node_tiles, W.item_tile, W.item_begin,
-                     W.item_first, W.status + 3);
+  if (NB <= SCAN_DIRECT) {
+    hipLaunchKernelGGL(k_scan_final<true>, dim3((unsigned)NB), dim3(SCAN_BLOCK), 0, s, W.tile_count, W.node_flag, T,
+                       (const int32_t *)nullptr, NB, W.tile_start, W.cell_tiles, W.node_tiles, W.item_tile,
+                       W.item_begin, W.item_first, W.status + 3);
+  } else {
+    hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)NB), dim3(SCAN_BLOCK), 0, s, W.tile_count, W.node_flag, T,
+                       W.block_sums, NB);
+    hipLaunchKernelGGL(k_scan_final<false>, dim3((unsigned)NB), dim3(SCAN_BLOCK), 0, s, W.tile_count, W.node_flag, T,
+                       W.block_sums, NB, W.tile_start, W.cell_tiles, W.node_tiles, W.item_tile, W.item_begin,
+                       W.item_first, W.status + 3);
+  }
   if (n > 0) {
     int32_t *dst = deterministic ? W.perm_tmp : W.perm;
     hipLaunchKernelGGL(k_sort_scatter, dim3(grid_blocks(n, 256)), dim3(256), 0, s, W.key, W.rank, n, W.tile_start,
@@ -873,11 +882,11 @@ extern "C" int mpm_p2g(const dw_grid *grid, const dw_mpm_params *params, const d
       hipLaunchKernelGGL(k_p2g<true>, dim3(p2g_blocks()), dim3(P2G_THREADS), 0, s, g, make_pview(p), params->dt,
                          params->material, W.perm, W.tile_start, W.item_tile, W.item_begin, W.n_items, grid_m,
                          grid_mv, N, W.status, W.item_part);
-    hipLaunchKernelGGL(k_det_gather<false>, dim3(PERSISTENT_BLOCKS), dim3(256), 0, s, g, W.node_tiles, W.n_node_tiles,
+    hipLaunchKernelGGL(k_det_gather<false>, dim3(node_blocks(W.n_tiles)), dim3(256), 0, s, g, W.node_tiles, W.n_node_tiles,
                        W.tile_count, W.item_first, W.item_part, grid_m, grid_mv, N, W.status + 9);
     return check_launch("mpm_p2g");
   }
-  hipLaunchKernelGGL(k_grid_clear, dim3(PERSISTENT_BLOCKS), dim3(256), 0, s, g, W.node_tiles, W.n_node_tiles,
+  hipLaunchKernelGGL(k_grid_clear, dim3(node_blocks(W.n_tiles)), dim3(256), 0, s, g, W.node_tiles, W.n_node_tiles,
                      grid_m, grid_mv, N, W.status + 8);
   if (p->n > 0)
     hipLaunchKernelGGL(k_p2g<false>, dim3(p2g_blocks()), dim3(P2G_THREADS), 0, s, g, make_pview(p), params->dt,
@@ -902,7 +911,7 @@ extern "C" int mpm_grid_update(const dw_grid *grid, const dw_mpm_params *params,
   if (rc) return rc;
   GridDev g = make_grid(grid);
   int64_t N = (int64_t)grid->nx * grid->ny * grid->nz;
-  hipLaunchKernelGGL(k_grid_update, dim3(PERSISTENT_BLOCKS), dim3(256), 0, (hipStream_t)stream, g, params->dt,
+  hipLaunchKernelGGL(k_grid_update, dim3(node_blocks(W.n_tiles)), dim3(256), 0, (hipStream_t)stream, g, params->dt,
                      params->gravity[0], params->gravity[1], params->gravity[2], params->bound, grid_m, grid_mv,
                      wd, pin, W.node_tiles, W.n_node_tiles, grid_v, N);
   return check_launch("mpm_grid_update");

@@ -833,7 +833,7 @@ extern "C" int mpm_grid_update_adj(const dw_grid *grid, const dw_mpm_params *par
   if (rc) return rc;
   GridDev g = make_grid(grid);
   int64_t N = (int64_t)grid->nx * grid->ny * grid->nz;
-  hipLaunchKernelGGL(k_grid_update_adj, dim3(2048), dim3(256), 0, (hipStream_t)stream, g, params->dt,
+  hipLaunchKernelGGL(k_grid_update_adj, dim3(node_blocks(W.n_tiles)), dim3(256), 0, (hipStream_t)stream, g, params->dt,
                      params->gravity[0], params->gravity[1], params->gravity[2], params->bound, grid_m, grid_mv, wd,
                      pin, W.node_tiles, W.n_node_tiles, grid_v_bar, grid_m_bar, grid_mv_bar, acc_bar, N);
   return check_launch("mpm_grid_update_adj");
@@ -856,14 +856,16 @@ extern "C" int mpm_g2p_adj(const dw_grid *grid, const dw_mpm_params *params, con
   GridDev g = make_grid(grid);
   int64_t N = (int64_t)grid->nx * grid->ny * grid->nz;
   hipStream_t s = (hipStream_t)stream;
+  // at most this many work items: a partial chunk per tile and the whole chunks
+  const unsigned blocks = (unsigned)std::min<int64_t>(2048, W.n_tiles + in->n / WORK_CHUNK);
   if (det) {
-    hipLaunchKernelGGL(k_g2p_adj<true>, dim3(2048), dim3(SC_THREADS), 0, s, g, params->dt, grid_v, N, in->x,
+    hipLaunchKernelGGL(k_g2p_adj<true>, dim3(blocks), dim3(SC_THREADS), 0, s, g, params->dt, grid_v, N, in->x,
                        in->xref, in->F, in->n, out_bar->x, out_bar->v, out_bar->C, out_bar->F, in_bar->x, in_bar->F,
                        grid_v_bar, W.perm, W.tile_start, W.item_tile, W.item_begin, W.n_items, W.item_part);
-    hipLaunchKernelGGL(k_det_gather<true>, dim3(2048), dim3(256), 0, s, g, W.node_tiles, W.n_node_tiles,
+    hipLaunchKernelGGL(k_det_gather<true>, dim3(node_blocks(W.n_tiles)), dim3(256), 0, s, g, W.node_tiles, W.n_node_tiles,
                        W.tile_count, W.item_first, W.item_part, (float *)nullptr, grid_v_bar, N, (int32_t *)nullptr);
   } else {
-    hipLaunchKernelGGL(k_g2p_adj<false>, dim3(2048), dim3(SC_THREADS), 0, s, g, params->dt, grid_v, N, in->x,
+    hipLaunchKernelGGL(k_g2p_adj<false>, dim3(blocks), dim3(SC_THREADS), 0, s, g, params->dt, grid_v, N, in->x,
                        in->xref, in->F, in->n, out_bar->x, out_bar->v, out_bar->C, out_bar->F, in_bar->x, in_bar->F,
                        grid_v_bar, W.perm, W.tile_start, W.item_tile, W.item_begin, W.n_items, (float *)nullptr);
   }

@@ -68,6 +68,44 @@ def test_sort_matches_definition(sheet, leaves, ref):
         assert V["node_tiles"][:nnode].cpu().tolist() == ompm.active_node_tiles(None, og, base=base)
 
 
+@pytest.mark.parametrize("dims", [(8, 8, 8), (32, 32, 32), (36, 32, 32), (128, 128, 64), (132, 128, 64), (100, 104, 104)])
+def test_sort_tile_scan_sizes(dims):
+    """Tile lists, offsets and work items at 8 to 16,900 tiles: one block of
+    the scan, whole and partial blocks, and both sides of the 32 blocks up to
+    which a block adds up the tiles before it itself."""
+    say(f"mpm_sort tiles of {dims}")
+    rng = np.random.default_rng(sum(dims))
+    nx, ny, nz = dims
+    grid = dict(nx=nx, ny=ny, nz=nz, dx=1.0 / 128, origin=(0.0, 0.0, 0.0))
+    g, og = api_grid(grid), oracle_grid(grid)
+    n = 20_000
+    # a dense corner (tiles of several items), the rest spread out, the last tile among them
+    cells = rng.random((n, 3)) * (np.array(dims) - 3.5) + 0.6
+    cells[: n // 3] = 0.6 + 3.0 * rng.random((n // 3, 3))
+    cells[-1] = np.array(dims) - 2.9
+    x = torch.as_tensor(cells / 128).T.contiguous().float().to(DEV)
+    ws = api.alloc_workspace(g, n)
+    api.mpm_sort(g, api.make_mpm_params(1e-4), x, ws)
+    torch.cuda.synchronize()
+    V = api.workspace_views(g, n, ws)
+    base = ompm.stencil_base_f32(x.T.double().cpu(), og)
+    keys = ompm.cell_tile_keys(None, og, base=base)
+    T = V["n_tiles"]
+    counts = torch.bincount(keys, minlength=T)
+    start = torch.cumsum(counts, 0) - counts
+    items = (counts + api.WORK_CHUNK - 1) // api.WORK_CHUNK
+    assert int(V["status"]) == 0 and int(V["n_sorted"]) == n and int(V["n_items"]) == int(items.sum())
+    assert torch.equal(V["tile_count"].cpu().long(), counts)
+    assert torch.equal(V["tile_start"].cpu().long(), torch.cat([start, torch.tensor([n])]))
+    assert torch.equal(V["cell_tiles"][:int(V["n_cell_tiles"])].cpu().long(), torch.nonzero(counts).flatten())
+    assert V["node_tiles"][:int(V["n_node_tiles"])].cpu().tolist() == ompm.active_node_tiles(None, og, base=base)
+    assert torch.equal(V["item_first"].cpu().long(), torch.cumsum(items, 0) - items)
+    tiles = torch.repeat_interleave(torch.arange(T), items)
+    chunk = torch.arange(len(tiles)) - (torch.cumsum(items, 0) - items)[tiles]
+    assert torch.equal(V["item_tile"][:len(tiles)].cpu().long(), tiles)
+    assert torch.equal(V["item_begin"][:len(tiles)].cpu().long(), start[tiles] + chunk * api.WORK_CHUNK)
+
+
 def test_reorder_is_the_sort_permutation(leaves):
     """mpm_reorder writes every per-particle array in the sort's order,
     bit for bit, and the result is grouped by cell tile; a substep of the
