@@ -313,6 +313,43 @@ int mpm_g2p_adj(const dw_grid *grid, const dw_mpm_params *params, const float *g
 int wind_to_grid_adj(const dw_grid *grid, const dw_wind *wind, const float *acc_bar,
                      float *out_bar, void *stream);
 
+/* A run of substeps of a rollout whose wind is one force grid per time slot:
+ * substep s of n_sub uses slot s * slots / n_sub of wind->W [slots][3][nw^3],
+ * slots slot_stride floats apart (in W_bar too).
+ * Substep first + i works on the grids m, mv, v [7][N] at grids + i *
+ * grid_stride floats and the workspace at ws + i * ws_stride bytes (a multiple
+ * of 256); a stride of 0 shares one between the substeps. */
+typedef struct {
+  int first, count, n_sub, slots;
+  int64_t slot_stride;
+  float *grids;
+  int64_t grid_stride;
+  void *ws;
+  int64_t ws_stride;
+  size_t ws_bytes;
+  float *states; /* kept states (see the calls), or NULL */
+} dw_segment;
+
+/* Forward substeps (mpm_sort, mpm_p2g, mpm_grid_update, mpm_g2p) from the
+ * state in p.  With seg->states NULL the state goes to `out` (which may be p's
+ * own arrays); else substep i writes seg->states + 24 n i (x, v, C, F packed),
+ * the last substep ends after its grid update, and out is not used.
+ * status_or (device int32 or NULL): the workspace status words are OR-ed in. */
+int mpm_rollout(const dw_grid *grid, const dw_mpm_params *params, const dw_particles *p,
+                const dw_particles_bar *out, const dw_wind *wind, const uint8_t *pin,
+                const dw_segment *seg, int32_t *status_or, void *stream);
+
+/* Reverse of the segment that mpm_rollout ran with the same seg (p: its first
+ * state; seg->states as written there): bars [2][24 n] holds the output adjoints
+ * in group `cur` and the input adjoints afterwards in group cur ^ (count & 1).
+ * grid_bar [10][N] is scratch whose first three arrays must be zero, and are
+ * again on return.  W_bar [slots][3][nw^3] and E_bar are added to.  A particle
+ * that the sort skipped (status OUT_OF_GRID or NONFINITE) leaves the adjoints
+ * undefined. */
+int mpm_rollout_adj(const dw_grid *grid, const dw_mpm_params *params, const dw_particles *p,
+                    const dw_wind *wind, const uint8_t *pin, const dw_segment *seg, float *bars,
+                    int cur, float *grid_bar, float *W_bar, float *E_bar, void *stream);
+
 /* ----------------------------------------------------- Gaussian kernels */
 
 /* Covariance of each Gaussian kernel after deformation (Sec. 3.2,

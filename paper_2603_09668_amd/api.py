@@ -30,6 +30,7 @@ STATUS_OUT_OF_GRID, STATUS_NONFINITE, STATUS_INVERTED, STATUS_RENDER_OVERFLOW = 
 SYMBOLS = [
     "dw_last_error", "mpm_workspace_bytes", "mpm_sort", "mpm_p2g", "mpm_grid_update", "mpm_g2p", "mpm_reorder",
     "wind_to_grid", "mpm_p2g_adj", "mpm_grid_update_adj", "mpm_g2p_adj", "wind_to_grid_adj",
+    "mpm_rollout", "mpm_rollout_adj",
     "lbm_step", "lbm_step_adj", "lbm_step_adj_static", "lbm_equilibrium", "lbm_home_step", "lbm_home_step_adj", "lbm_home_equilibrium",
     "lbm_solid_from_particles", "gaussian_covariance", "gaussian_covariance_adj",
     "gs_render_workspace_bytes", "gs_render", "gs_render_adj", "gs_render_status", "render_loss_workspace_bytes",
@@ -68,6 +69,12 @@ class Wind(ctypes.Structure):
     _fields_ = [("mode", c_int), ("nw", c_int * 3), ("lo", c_float * 3), ("hi", c_float * 3),
                 ("W", c_void_p), ("lat", Lattice), ("u", c_void_p), ("vel_scale", c_float),
                 ("k_drag", c_float), ("acc", c_void_p), ("deterministic", c_int)]
+
+
+class Segment(ctypes.Structure):
+    _fields_ = [("first", c_int), ("count", c_int), ("n_sub", c_int), ("slots", c_int),
+                ("slot_stride", ctypes.c_int64), ("grids", c_void_p), ("grid_stride", ctypes.c_int64),
+                ("ws", c_void_p), ("ws_stride", ctypes.c_int64), ("ws_bytes", c_size_t), ("states", c_void_p)]
 
 
 class LBMParams(ctypes.Structure):
@@ -113,6 +120,10 @@ def lib():
         "mpm_g2p_adj": ([POINTER(Grid), POINTER(MPMParams), P, POINTER(Particles), POINTER(ParticlesBar),
                          POINTER(ParticlesBar), P, P, c_size_t, P], c_int),
         "wind_to_grid_adj": ([POINTER(Grid), POINTER(Wind), P, P, P], c_int),
+        "mpm_rollout": ([POINTER(Grid), POINTER(MPMParams), POINTER(Particles), POINTER(ParticlesBar), POINTER(Wind),
+                         P, POINTER(Segment), P, P], c_int),
+        "mpm_rollout_adj": ([POINTER(Grid), POINTER(MPMParams), POINTER(Particles), POINTER(Wind), P,
+                             POINTER(Segment), P, c_int, P, P, P, P], c_int),
         "lbm_step": ([POINTER(Lattice), POINTER(LBMParams), P, P, P, P, P, P], c_int),
         "lbm_step_adj": ([POINTER(Lattice), POINTER(LBMParams), P, P, P, P, P, P, P], c_int),
         "lbm_step_adj_static": ([POINTER(Lattice), POINTER(LBMParams), P, P, P, P, P, P], c_int),
@@ -400,6 +411,36 @@ def mpm_g2p_adj(grid: Grid, params: MPMParams, grid_v, p_in: ParticleArrays, x_o
 def wind_to_grid_adj(grid: Grid, wind: Wind, acc_bar, out_bar):
     _check(lib().wind_to_grid_adj(ctypes.byref(grid), ctypes.byref(wind), _ptr(acc_bar, name="acc_bar"),
                                   _ptr(out_bar, name="out_bar"), _stream()), "wind_to_grid_adj")
+
+
+def rollout_segment(first, count, n_sub, slots, slot_stride, grids, ws, states=None) -> Segment:
+    """Substeps first .. first + count of a rollout.  With states (count - 1,
+    24 n), the kept states between them, grids (m, 7, N) and ws (m, bytes) hold
+    one per substep (m >= count); else one of each serves all of them."""
+    kept = states is not None
+    gs, wb = (int(grids.stride(0)), int(ws.shape[-1])) if kept else (0, ws.numel())
+    return Segment(int(first), int(count), int(n_sub), int(slots), int(slot_stride), _ptr(grids, name="grids"), gs,
+                   _ptr(ws, torch.uint8, "ws"), wb if kept else 0, wb, _ptr(states, name="states"))
+
+
+def mpm_rollout(grid: Grid, params: MPMParams, p: ParticleArrays, out, wind: Wind, pin, seg: Segment, status_or=None):
+    """Forward substeps of seg; out = (x, v, C, F), or None with kept states."""
+    ps = p.struct()
+    po = _bar_struct(p.n, *out) if out is not None else None
+    _check(lib().mpm_rollout(ctypes.byref(grid), ctypes.byref(params), ctypes.byref(ps),
+                             ctypes.byref(po) if po is not None else None, ctypes.byref(wind),
+                             _ptr(pin, torch.uint8, "pin"), ctypes.byref(seg),
+                             _ptr(status_or, torch.int32, "status_or"), _stream()), "mpm_rollout")
+
+
+def mpm_rollout_adj(grid: Grid, params: MPMParams, p: ParticleArrays, wind: Wind, pin, seg: Segment, bars, cur,
+                    grid_bar, W_bar, E_bar):
+    """bars (2, 24 n), grid_bar (10, N); see the header."""
+    ps = p.struct()
+    _check(lib().mpm_rollout_adj(ctypes.byref(grid), ctypes.byref(params), ctypes.byref(ps), ctypes.byref(wind),
+                                 _ptr(pin, torch.uint8, "pin"), ctypes.byref(seg), _ptr(bars, name="bars"), int(cur),
+                                 _ptr(grid_bar, name="grid_bar"), _ptr(W_bar, name="W_bar"),
+                                 _ptr(E_bar, name="E_bar"), _stream()), "mpm_rollout_adj")
 
 
 def lbm_step(lat: Lattice, params: LBMParams, f_in, f_out, solid=None, rho_out=None, u_out=None):

@@ -12,10 +12,10 @@ backward walks the segments in reverse; for each it re-runs the segment from
 its checkpoint, keeping every substep's particle state, sort workspace and
 grid (m, mv, v: about 28 B per grid node and 20 B per particle per substep),
 then for every substep (last first) applies the adjoints in reverse order:
-G2P adjoint (sorted scatter into the grid adjoint), grid-update adjoint, wind
-transpose into W_bar, P2G adjoint (per-particle gather, also giving E_bar).
-Every step runs in the library's HIP kernels; torch provides device memory,
-zero-fills (one per buffer group) and the final loss.
+G2P adjoint (sorted scatter into the grid adjoint), grid-update adjoint with
+the wind transpose into W_bar, P2G adjoint (per-particle gather, also giving
+E_bar).  The substep loops run in the library (mpm_rollout, mpm_rollout_adj);
+torch provides device memory and the final loss.
 
 With `deterministic` every reduction of the forward and reverse substeps
 runs in a fixed order (sort, P2G, the reverse G2P's grid scatter, the E and
@@ -57,24 +57,28 @@ class RolloutPlan:
         f = dict(dtype=torch.float32, device=device)
         self.device = device
         self.ws = api.alloc_workspace(self.grid, n, device, deterministic=self.deterministic)
-        self.gm = torch.zeros(self.N, **f)
-        self.gmv = torch.zeros(3, self.N, **f)
-        self.gv = torch.zeros(3, self.N, **f)
-        # grid adjoints in one buffer, cleared with one fill per substep
+        self._grids = torch.zeros(7, self.N, **f)
+        self.gm, self.gmv, self.gv = self._grids[0], self._grids[1:4], self._grids[4:7]
+        # grid adjoints in one buffer, cleared with one fill per substep_adjoint
         self._gbar = torch.zeros(10, self.N, **f)
         self.gvb, self.gmb, self.gmvb, self.accb = (self._gbar[0:3], self._gbar[3], self._gbar[4:7],
                                                     self._gbar[7:10])
-        self._seg = None  # per-substep workspaces and grids of a segment, made on first backward
+        self._seg = None  # workspaces and grids of a segment's substeps, made on first backward
         self._status = torch.zeros(1, dtype=torch.int32, device=device)  # OR of the substeps' status words
+
+    def _segment_store(self):
+        """Workspaces (ckpt, bytes) and grids (ckpt, 7, N) of a segment's substeps."""
+        if self._seg is None:
+            nb = self.ws.numel()
+            ws = torch.empty(self.ckpt * nb + 256, dtype=torch.uint8, device=self.device)
+            off = (-ws.data_ptr()) % 256
+            self._seg = (ws[off:off + self.ckpt * nb].view(self.ckpt, nb),
+                         torch.empty(self.ckpt, 7, self.N, dtype=torch.float32, device=self.device))
+        return self._seg
 
     def segment_buffers(self):
         """Sort workspaces and grids (m, mv, v) for the substeps of one segment."""
-        if self._seg is None:
-            f = dict(dtype=torch.float32, device=self.device)
-            self._seg = [(api.alloc_workspace(self.grid, self.n, self.device, deterministic=self.deterministic),
-                          torch.empty(self.N, **f),
-                          torch.empty(3, self.N, **f), torch.empty(3, self.N, **f)) for _ in range(self.ckpt)]
-        return self._seg
+        return [(ws, g[0], g[1:4], g[4:7]) for ws, g in zip(*self._segment_store())]
 
     def slot(self, s: int) -> int:
         return s * self.K // self.n_sub
@@ -95,6 +99,13 @@ class RolloutPlan:
     def wind(self, W, s):
         return api.wind_force_grid(W[self.slot(s)], self.nw, self.box_lo, self.box_hi,
                                    deterministic=self.deterministic)
+
+    def segment(self, W, s0: int, grids, ws, states=None) -> api.Segment:
+        """The checkpoint segment that starts at substep s0; with states its
+        substeps keep their own grids and workspaces."""
+        count = min(self.ckpt, self.n_sub - s0)
+        W[self.slot(s0 + count - 1)]  # an IndexError if W lacks a slot
+        return api.rollout_segment(s0, count, self.n_sub, self.K, W.stride(0), grids, ws, states)
 
     # --------------------------------------------------------------- forward
     def substep(self, p: api.ParticleArrays, W, s: int, out=None, bufs=None, g2p: bool = True):
@@ -140,10 +151,14 @@ class _RolloutFn(torch.autograd.Function):
         E = E.detach().contiguous()
         state = [t.detach().clone() for t in (x0, v0, C0, H0)]
         ckpts = []
-        for s in range(plan.n_sub):
-            if s % plan.ckpt == 0:
-                ckpts.append([t.clone() for t in state])
-            plan.substep(plan.particles(*state, E), W, s)
+        for s0 in range(0, plan.n_sub, plan.ckpt):
+            # a segment leaves its first state as it is: that is the checkpoint
+            ckpts.append(state)
+            out = [torch.empty_like(t) for t in state]
+            seg = plan.segment(W, s0, plan._grids, plan.ws)
+            api.mpm_rollout(plan.grid, plan.prm, plan.particles(*state, E), out, plan.wind(W, 0), plan.pin, seg,
+                            plan._status)
+            state = out
         plan.check_status("forward")
         ctx.plan = plan
         ctx.ckpts = ckpts
@@ -154,41 +169,29 @@ class _RolloutFn(torch.autograd.Function):
     def backward(ctx, xb, vb, Cb, Hb):
         plan = ctx.plan
         W, E = ctx.saved_tensors
-        bar = [torch.zeros_like(t) if b is None else b.contiguous().clone()
-               for b, t in zip((xb, vb, Cb, Hb), ctx.ckpts[0])]
         W_bar = torch.zeros_like(W)
         E_bar = torch.zeros_like(E)
-        seg_bufs = plan.segment_buffers()
-        # particle-state adjoints: two groups of (x, v, C, H) views, one fill each
+        ws, grids = plan._segment_store()
+        # particle-state adjoints: two groups of packed (x, v, C, H)
         shapes = [t.shape for t in ctx.ckpts[0]]
         sizes = [t.numel() for t in ctx.ckpts[0]]
         pair = torch.empty(2, sum(sizes), dtype=torch.float32, device=W.device)
         groups = [list(t.view(sh) for t, sh in zip(torch.split(pair[k], sizes), shapes)) for k in range(2)]
         cur = 0
-        for dst, b in zip(groups[cur], bar):
-            dst.copy_(b)
-        bar = groups[cur]
-        for seg in reversed(range(len(ctx.ckpts))):
-            s0 = seg * plan.ckpt
-            s1 = min(s0 + plan.ckpt, plan.n_sub)
+        for dst, b in zip(groups[cur], (xb, vb, Cb, Hb)):
+            dst.zero_() if b is None else dst.copy_(b)
+        states = torch.empty(max(plan.ckpt - 1, 1), sum(sizes), dtype=torch.float32, device=W.device)
+        plan.gvb.zero_()  # and zero again after each substep
+        wind = plan.wind(W, 0)
+        for k in reversed(range(len(ctx.ckpts))):
             # re-run the segment, keeping each substep's state, sort and grid
-            states = [[t.clone() for t in ctx.ckpts[seg]]]
-            for s in range(s0, s1):
-                last = s == s1 - 1
-                nxt = None if last else [torch.empty_like(t) for t in states[-1]]
-                plan.substep(plan.particles(*states[-1], E), W, s, out=nxt, bufs=seg_bufs[s - s0], g2p=not last)
-                if not last:
-                    states.append(nxt)
-            for s in reversed(range(s0, s1)):
-                st = states[s - s0]
-                nxt_group = groups[1 - cur]
-                pair[1 - cur].zero_()
-                plan.substep_adjoint(plan.particles(*st, E), W, s, bar, nxt_group, W_bar, E_bar,
-                                     bufs=seg_bufs[s - s0])
-                bar = nxt_group
-                cur = 1 - cur
+            seg = plan.segment(W, k * plan.ckpt, grids, ws, states)
+            p = plan.particles(*ctx.ckpts[k], E)
+            api.mpm_rollout(plan.grid, plan.prm, p, None, wind, plan.pin, seg, plan._status)
+            api.mpm_rollout_adj(plan.grid, plan.prm, p, wind, plan.pin, seg, pair, cur, plan._gbar, W_bar, E_bar)
+            cur ^= seg.count & 1
         plan.check_status("backward")
-        return (None, W_bar, E_bar, *[b.clone() for b in bar])
+        return (None, W_bar, E_bar, *[b.clone() for b in groups[cur]])
 
 
 def rollout(plan: RolloutPlan, W, E, x0, v0, C0, H0):

@@ -84,6 +84,24 @@ int check_particles(const dw_particles *p, bool need_state);
 // binds the workspace and checks its size
 int bind_workspace(const dw_grid *g, int n, const void *ws, size_t ws_bytes, Workspace *W, int deterministic = 0);
 
+// The entry points' launches with what the rollout adds to them:
+// status_or |= the workspace status; fresh: adjoint arrays that hold nothing
+// yet are written instead of added to (reverse G2P: x and F; reverse P2G: v
+// and C); fused: see k_grid_update_adj.
+int run_grid_update(const dw_grid *grid, const dw_mpm_params *params, const float *grid_m, const float *grid_mv,
+                    const dw_wind *wind, const uint8_t *pin, float *grid_v, const void *ws, size_t ws_bytes,
+                    void *stream, int32_t *status_or);
+int run_g2p_adj(const dw_grid *grid, const dw_mpm_params *params, const float *grid_v, const dw_particles *in,
+                const dw_particles_bar *out_bar, dw_particles_bar *in_bar, float *grid_v_bar, const void *ws,
+                size_t ws_bytes, void *stream, int fresh);
+int run_grid_update_adj_fused(const dw_grid *grid, const dw_mpm_params *params, const float *grid_m,
+                              const float *grid_mv, const dw_wind *wind, const uint8_t *pin, float *grid_v_bar,
+                              float *grid_m_bar, float *grid_mv_bar, float *W_bar, const void *ws, size_t ws_bytes,
+                              void *stream);
+int run_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, const dw_particles *p, const float *grid_m_bar,
+                const float *grid_mv_bar, dw_particles_bar *bar, float *E_bar, void *ws, size_t ws_bytes, void *stream,
+                int fresh);
+
 // fill kernels (a kernel rather than hipMemsetAsync, so the calls stay
 // capturable in HIP graphs); static: every translation unit launches its own
 // k_fill_i32 writes 16 bytes per store over the 16-byte aligned body of the

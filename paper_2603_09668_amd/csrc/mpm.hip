@@ -488,8 +488,10 @@ __global__ __launch_bounds__(256) void k_grid_update(GridDev g, float dt, float 
                                                      const uint8_t *__restrict__ pin,
                                                      const int32_t *__restrict__ node_tiles,
                                                      const int32_t *__restrict__ n_tiles, float *__restrict__ gv,
-                                                     int64_t N) {
+                                                     int64_t N, const int32_t *__restrict__ status,
+                                                     int32_t *__restrict__ status_or) {
   int nt = *n_tiles;
+  if (status_or && blockIdx.x == 0 && threadIdx.x == 0) *status_or |= *status;  // of the sort and P2G before it
   int sub = threadIdx.x >> 6, l = threadIdx.x & 63;
   for (int it = blockIdx.x * 4 + sub; it < nt; it += gridDim.x * 4) {
     int t = node_tiles[it];
@@ -895,9 +897,9 @@ extern "C" int mpm_p2g(const dw_grid *grid, const dw_mpm_params *params, const d
   return check_launch("mpm_p2g");
 }
 
-extern "C" int mpm_grid_update(const dw_grid *grid, const dw_mpm_params *params, const float *grid_m,
-                               const float *grid_mv, const dw_wind *wind, const uint8_t *pin, float *grid_v,
-                               const void *ws, size_t ws_bytes, void *stream) {
+int dw::run_grid_update(const dw_grid *grid, const dw_mpm_params *params, const float *grid_m, const float *grid_mv,
+                        const dw_wind *wind, const uint8_t *pin, float *grid_v, const void *ws, size_t ws_bytes,
+                        void *stream, int32_t *status_or) {
   int rc = check_grid(grid);
   if (rc) return rc;
   DW_REQUIRE(params, DW_EINVAL, "mpm_grid_update: params is NULL");
@@ -913,8 +915,14 @@ extern "C" int mpm_grid_update(const dw_grid *grid, const dw_mpm_params *params,
   int64_t N = (int64_t)grid->nx * grid->ny * grid->nz;
   hipLaunchKernelGGL(k_grid_update, dim3(node_blocks(W.n_tiles)), dim3(256), 0, (hipStream_t)stream, g, params->dt,
                      params->gravity[0], params->gravity[1], params->gravity[2], params->bound, grid_m, grid_mv,
-                     wd, pin, W.node_tiles, W.n_node_tiles, grid_v, N);
+                     wd, pin, W.node_tiles, W.n_node_tiles, grid_v, N, W.status, status_or);
   return check_launch("mpm_grid_update");
+}
+
+extern "C" int mpm_grid_update(const dw_grid *grid, const dw_mpm_params *params, const float *grid_m,
+                               const float *grid_mv, const dw_wind *wind, const uint8_t *pin, float *grid_v,
+                               const void *ws, size_t ws_bytes, void *stream) {
+  return dw::run_grid_update(grid, params, grid_m, grid_mv, wind, pin, grid_v, ws, ws_bytes, stream, nullptr);
 }
 
 extern "C" int mpm_g2p(const dw_grid *grid, const dw_mpm_params *params, const float *grid_v,

@@ -154,6 +154,7 @@ struct PAdj {
   int n, n_regions;
   float *xb, *vb, *Cb, *Fb, *Eb;
   float *Epart;     // deterministic mode: per-wave region sums [waves][n_regions]
+  int fresh;        // vb and Cb hold nothing yet: written, not added to
 };
 
 // ---------------------------------------------------------- reverse P2G
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(P2G_ADJ_THREADS) __attribute__((amdgpu_waves_per_eu
         float vo[3] = {0.f, 0.f, 0.f}, xo[3] = {0.f, 0.f, 0.f}, Co[9], Fo[9];
 #pragma unroll
         for (int q = 0; q < 9; ++q) Co[q] = Fo[q] = 0.f;
-        if (P.vb) {
+        if (P.vb && !P.fresh) {
 #pragma unroll
           for (int a = 0; a < 3; ++a) vo[a] = at_particle(P.vb, a, n, off);
         }
@@ -307,7 +308,7 @@ __global__ __launch_bounds__(P2G_ADJ_THREADS) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
           for (int a = 0; a < 3; ++a) xo[a] = at_particle(P.xb, a, n, off);
         }
-        if (P.Cb) {
+        if (P.Cb && !P.fresh) {
 #pragma unroll
           for (int q = 0; q < 9; ++q) Co[q] = at_particle(P.Cb, q, n, off);
         }
@@ -437,72 +438,179 @@ __global__ __launch_bounds__(64) void k_ebar_reduce(const float *__restrict__ pa
 }
 
 // --------------------------------------------------- reverse grid update
+
+// v + v of the lane CTRL names (a DPP move within the row of 16)
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+
+// W_bar += the force grid's trilinear transpose of the acceleration adjoints
+// ab that the lanes of a wave hold (the nodes of one tile; any may be zero).
+// A wind cell is usually wider than a node, so that a tile reaches at most four
+// wind nodes per axis: the transpose then runs axis by axis, the four lanes
+// along an axis adding their shares of each wind node and lane c keeping wind
+// node c, and each lane ends with one wind node's three sums.  (36 lane sums
+// in all; summing the 24 corner values of each wind cell over the wave took 7
+// us more.)  A finer wind grid's nodes add their own shares.  A share is
+// selected, not multiplied by zero: a NaN stays in its cell's corners.
+__device__ __forceinline__ void force_grid_transpose(const WindDev &w, const GridDev &g, int i, int j, int k,
+                                                     const float ab[3], float *__restrict__ Wbar) {
+  const bool on = ab[0] != 0.f || ab[1] != 0.f || ab[2] != 0.f;
+  if (!__ballot(on)) return;
+  const int lane = threadIdx.x & 63;
+  const float q[3] = {fminf(fmaxf((g.ox + g.dx * (float)i - w.lox) * w.sx, 0.f), (float)(w.nwx - 1)),
+                      fminf(fmaxf((g.oy + g.dx * (float)j - w.loy) * w.sy, 0.f), (float)(w.nwy - 1)),
+                      fminf(fmaxf((g.oz + g.dx * (float)k - w.loz) * w.sz, 0.f), (float)(w.nwz - 1))};
+  const int nw[3] = {w.nwx, w.nwy, w.nwz}, step[3] = {lane & 3, (lane >> 2) & 3, lane >> 4};
+  int ic[3], c0[3];
+  float t[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    lin_axis(q[d], nw[d], ic[d], t[d]);
+    c0[d] = __builtin_amdgcn_readlane(ic[d], 0);  // the tile's first wind node
+  }
+  if (__ballot(ic[0] - c0[0] > 2 || ic[1] - c0[1] > 2 || ic[2] - c0[2] > 2)) {
+    if (!on) return;
+    for (int e = 0; e < 8; ++e) {
+      const float wt = ((e & 1) ? t[0] : 1.f - t[0]) * ((e & 2) ? t[1] : 1.f - t[1]) * ((e & 4) ? t[2] : 1.f - t[2]);
+      const int64_t idx =
+          (ic[0] + (e & 1)) + (int64_t)w.nwx * ((ic[1] + ((e >> 1) & 1)) + (int64_t)w.nwy * (ic[2] + (e >> 2)));
+      for (int a = 0; a < 3; ++a) atomicAdd(&Wbar[a * w.nw3 + idx], wt * ab[a]);
+    }
+    return;
+  }
+  float v[3] = {ab[0], ab[1], ab[2]};
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    float keep[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int r = c - (ic[d] - c0[d]);  // 0: the cell's lower node, 1: its upper one
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        float u = r == 0 ? (1.f - t[d]) * v[a] : (r == 1 ? t[d] * v[a] : 0.f);
+        if (d == 0) {
+          u = dpp_add<0xB1>(u);  // quad_perm: the other one of the pair,
+          u = dpp_add<0x4E>(u);  // the other pair
+        } else if (d == 1) {
+          u = dpp_add<0x124>(u);  // row_ror by 4, by 8
+          u = dpp_add<0x128>(u);
+        } else {
+          u += __shfl_xor(u, 16, 64);
+          u += __shfl_xor(u, 32, 64);
+        }
+        if (step[d] == c) keep[a] = u;
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) v[a] = keep[a];
+  }
+  const int64_t idx = (c0[0] + step[0]) + (int64_t)w.nwx * ((c0[1] + step[1]) + (int64_t)w.nwy * (c0[2] + step[2]));
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+    if (v[a] != 0.f) atomicAdd(&Wbar[a * w.nw3 + idx], v[a]);
+}
+
+// One node per lane, a node tile per wave.  FUSED (a rollout's reverse
+// substep, force-grid wind): gmb and gmvb are written for every node of the
+// active tiles (zero where the node has no mass or is pinned) instead of added
+// to, gvb is cleared once read, which leaves it zero for the next substep's
+// scatter, and ab goes straight into Wbar: no clear of ten grid arrays, no
+// array accb and no pass over all nodes for the transpose (96^3 nodes, 16^3
+// wind grid: 8 + 15 us and the clear -> 11).
+template <bool FUSED>
 __global__ __launch_bounds__(256) void k_grid_update_adj(GridDev g, float dt, float gx, float gy, float gz,
                                                          int bound, const float *__restrict__ gm,
                                                          const float *__restrict__ gmv, WindDev wind,
                                                          const uint8_t *__restrict__ pin,
                                                          const int32_t *__restrict__ node_tiles,
                                                          const int32_t *__restrict__ n_tiles,
-                                                         const float *__restrict__ gvb, float *__restrict__ gmb,
+                                                         float *__restrict__ gvb, float *__restrict__ gmb,
                                                          float *__restrict__ gmvb, float *__restrict__ accb,
-                                                         int64_t N) {
+                                                         float *__restrict__ Wbar, int64_t N) {
   int nt = *n_tiles;
   int sub = threadIdx.x >> 6, l = threadIdx.x & 63;
   for (int it = blockIdx.x * 4 + sub; it < nt; it += gridDim.x * 4) {
     int t = node_tiles[it];
     int tx = t % g.tx, ty = (t / g.tx) % g.ty, tz = t / (g.tx * g.ty);
     int i = tx * 4 + (l & 3), j = ty * 4 + ((l >> 2) & 3), k = tz * 4 + (l >> 4);
-    if (i >= g.nx || j >= g.ny || k >= g.nz) continue;
-    int64_t node = i + (int64_t)g.nx * (j + (int64_t)g.ny * k);
-    float m = gm[node];
-    if (!(m > 0.f)) continue;
-    if (pin && pin[node]) continue;
-    float im = 1.0f / m;
-    float mv[3] = {gmv[node], gmv[N + node], gmv[2 * N + node]};
-    const float vs[3] = {mv[0] * im, mv[1] * im, mv[2] * im};
-    float ax, ay, az;
-    wind_at_node(wind, g, i, j, k, node, vs[0], vs[1], vs[2], ax, ay, az);
-    float v[3] = {vs[0] + dt * (gx + ax), vs[1] + dt * (gy + ay), vs[2] + dt * (gz + az)};
-    float vb[3] = {gvb[node], gvb[N + node], gvb[2 * N + node]};
-    if ((i < bound && v[0] < 0.f) || (i >= g.nx - bound && v[0] > 0.f)) vb[0] = 0.f;
-    if ((j < bound && v[1] < 0.f) || (j >= g.ny - bound && v[1] > 0.f)) vb[1] = 0.f;
-    if ((k < bound && v[2] < 0.f) || (k >= g.nz - bound && v[2] > 0.f)) vb[2] = 0.f;
-    // adjoint of the acceleration, and of the wind velocity U and of v* for
-    // the relative drag a = k |r| r, r = U - v*: with J = k (|r| I + r r^T / |r|)
-    // U_bar = J a_bar and v*_bar gets -J a_bar
-    float ab[3] = {dt * vb[0], dt * vb[1], dt * vb[2]};
-    float vsb[3] = {vb[0], vb[1], vb[2]};
-    if (wind.mode == DW_WIND_LBM_DRAG_REL) {
-      float U[3];
-      float r[3] = {0.f, 0.f, 0.f};
-      if (wind_velocity_at_node(wind, g, i, j, k, U[0], U[1], U[2])) {
-        r[0] = U[0] - vs[0];
-        r[1] = U[1] - vs[1];
-        r[2] = U[2] - vs[2];
-      }
-      const float sp = sqrtf(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
-      float Jab[3] = {0.f, 0.f, 0.f};
-      if (sp > 0.f) {
-        const float rb = (r[0] * ab[0] + r[1] * ab[1] + r[2] * ab[2]) / sp;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) Jab[a] = wind.k_drag * (sp * ab[a] + r[a] * rb);
-      }
+    const bool in_grid = i < g.nx && j < g.ny && k < g.nz;
+    if (!FUSED && !in_grid) continue;
+    const int64_t node = in_grid ? i + (int64_t)g.nx * (j + (int64_t)g.ny * k) : 0;
+    const float m = in_grid ? gm[node] : 0.f;
+    const bool on = m > 0.f && !(pin && pin[node]);
+    if (!FUSED && !on) continue;
+    float vb[3], mvb[3] = {0.f, 0.f, 0.f}, mb = 0.f, ab[3] = {0.f, 0.f, 0.f};
+    if (FUSED && in_grid) {
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        vsb[a] -= Jab[a];
-        ab[a] = Jab[a];
+        vb[a] = gvb[a * N + node];
+        gvb[a * N + node] = 0.f;
       }
     }
-    if (gmvb) {
-      gmvb[node] += vsb[0] * im;
-      gmvb[N + node] += vsb[1] * im;
-      gmvb[2 * N + node] += vsb[2] * im;
+    if (on) {
+      float im = 1.0f / m;
+      float mv[3] = {gmv[node], gmv[N + node], gmv[2 * N + node]};
+      const float vs[3] = {mv[0] * im, mv[1] * im, mv[2] * im};
+      float ax, ay, az;
+      wind_at_node(wind, g, i, j, k, node, vs[0], vs[1], vs[2], ax, ay, az);
+      float v[3] = {vs[0] + dt * (gx + ax), vs[1] + dt * (gy + ay), vs[2] + dt * (gz + az)};
+      if (!FUSED) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) vb[a] = gvb[a * N + node];
+      }
+      if ((i < bound && v[0] < 0.f) || (i >= g.nx - bound && v[0] > 0.f)) vb[0] = 0.f;
+      if ((j < bound && v[1] < 0.f) || (j >= g.ny - bound && v[1] > 0.f)) vb[1] = 0.f;
+      if ((k < bound && v[2] < 0.f) || (k >= g.nz - bound && v[2] > 0.f)) vb[2] = 0.f;
+      // adjoint of the acceleration, and of the wind velocity U and of v* for
+      // the relative drag a = k |r| r, r = U - v*: with J = k (|r| I + r r^T / |r|)
+      // U_bar = J a_bar and v*_bar gets -J a_bar
+      float vsb[3] = {vb[0], vb[1], vb[2]};
+#pragma unroll
+      for (int a = 0; a < 3; ++a) ab[a] = dt * vb[a];
+      if (wind.mode == DW_WIND_LBM_DRAG_REL) {
+        float U[3];
+        float r[3] = {0.f, 0.f, 0.f};
+        if (wind_velocity_at_node(wind, g, i, j, k, U[0], U[1], U[2])) {
+          r[0] = U[0] - vs[0];
+          r[1] = U[1] - vs[1];
+          r[2] = U[2] - vs[2];
+        }
+        const float sp = sqrtf(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+        float Jab[3] = {0.f, 0.f, 0.f};
+        if (sp > 0.f) {
+          const float rb = (r[0] * ab[0] + r[1] * ab[1] + r[2] * ab[2]) / sp;
+#pragma unroll
+          for (int a = 0; a < 3; ++a) Jab[a] = wind.k_drag * (sp * ab[a] + r[a] * rb);
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          vsb[a] -= Jab[a];
+          ab[a] = Jab[a];
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) mvb[a] = vsb[a] * im;
+      mb = -(vsb[0] * mv[0] + vsb[1] * mv[1] + vsb[2] * mv[2]) * im * im;
     }
-    if (gmb) gmb[node] += -(vsb[0] * mv[0] + vsb[1] * mv[1] + vsb[2] * mv[2]) * im * im;
-    if (accb) {
-      accb[node] += ab[0];
-      accb[N + node] += ab[1];
-      accb[2 * N + node] += ab[2];
+    if (FUSED) {
+      if (in_grid) {
+        gmb[node] = mb;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) gmvb[a * N + node] = mvb[a];
+      }
+      force_grid_transpose(wind, g, i, j, k, ab, Wbar);
+    } else {
+      if (gmvb) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) gmvb[a * N + node] += mvb[a];
+      }
+      if (gmb) gmb[node] += mb;
+      if (accb) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) accb[a * N + node] += ab[a];
+      }
     }
   }
 }
@@ -532,7 +640,7 @@ __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
     const float *__restrict__ Cob, const float *__restrict__ Fob, float *__restrict__ xb, float *__restrict__ Fb,
     float *__restrict__ gvb, const int32_t *__restrict__ perm, const int32_t *__restrict__ tile_start,
     const int32_t *__restrict__ item_tile, const int32_t *__restrict__ item_begin,
-    const int32_t *__restrict__ n_items, float *__restrict__ item_part) {
+    const int32_t *__restrict__ n_items, float *__restrict__ item_part, int fresh) {
   __shared__ float s_dat[SC_DAT][SC_PITCH];
   __shared__ unsigned char s_cell[WORK_CHUNK];
   __shared__ float4 s_f[SC_PITCH];                                  // staged f per particle
@@ -710,12 +818,16 @@ __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
           B[3 * a + 2] += ((float)oz - f[2]) * Gz[a];
         }
       }
-      float Fbo[9], xbo[3];  // old values in one round trip
-      if (Fob && Fb) {
+      float Fbo[9], xbo[3];  // old values in one round trip (fresh: there are none)
+#pragma unroll
+      for (int q = 0; q < 9; ++q) Fbo[q] = 0.f;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) xbo[a] = 0.f;
+      if (Fob && Fb && !fresh) {
 #pragma unroll
         for (int q = 0; q < 9; ++q) Fbo[q] = at_particle(Fb, q, n, off);
       }
-      if (xb) {
+      if (xb && !fresh) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) xbo[a] = at_particle(xb, a, n, off);
       }
@@ -773,9 +885,9 @@ __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 
 using namespace dw;
 
-extern "C" int mpm_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, const dw_particles *p,
-                           const float *grid_m_bar, const float *grid_mv_bar, dw_particles_bar *bar, float *E_bar,
-                           void *ws, size_t ws_bytes, void *stream) {
+int dw::run_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, const dw_particles *p, const float *grid_m_bar,
+                    const float *grid_mv_bar, dw_particles_bar *bar, float *E_bar, void *ws, size_t ws_bytes,
+                    void *stream, int fresh) {
   int rc = check_grid(grid);
   if (rc) return rc;
   DW_REQUIRE(params, DW_EINVAL, "mpm_p2g_adj: params is NULL");
@@ -792,6 +904,7 @@ extern "C" int mpm_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, con
   P.xb = bar->x; P.vb = bar->v; P.Cb = bar->C; P.Fb = bar->F; P.Eb = E_bar;
   P.n_regions = p->n_regions;
   P.Epart = nullptr;
+  P.fresh = fresh;
   GridDev g = make_grid(grid);
   int64_t N = (int64_t)grid->nx * grid->ny * grid->nz;
   hipStream_t s = (hipStream_t)stream;
@@ -818,10 +931,17 @@ extern "C" int mpm_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, con
   return check_launch("mpm_p2g_adj");
 }
 
-extern "C" int mpm_grid_update_adj(const dw_grid *grid, const dw_mpm_params *params, const float *grid_m,
-                                   const float *grid_mv, const dw_wind *wind, const uint8_t *pin,
-                                   const float *grid_v_bar, float *grid_m_bar, float *grid_mv_bar, float *acc_bar,
-                                   const void *ws, size_t ws_bytes, void *stream) {
+extern "C" int mpm_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, const dw_particles *p,
+                           const float *grid_m_bar, const float *grid_mv_bar, dw_particles_bar *bar, float *E_bar,
+                           void *ws, size_t ws_bytes, void *stream) {
+  return dw::run_p2g_adj(grid, params, p, grid_m_bar, grid_mv_bar, bar, E_bar, ws, ws_bytes, stream, 0);
+}
+
+// W_bar given: the fused form (grid_v_bar is then cleared on the active tiles)
+static int grid_update_adj(const dw_grid *grid, const dw_mpm_params *params, const float *grid_m, const float *grid_mv,
+                           const dw_wind *wind, const uint8_t *pin, float *grid_v_bar, float *grid_m_bar,
+                           float *grid_mv_bar, float *acc_bar, float *W_bar, const void *ws, size_t ws_bytes,
+                           void *stream) {
   int rc = check_grid(grid);
   if (rc) return rc;
   DW_REQUIRE(params && grid_m && grid_mv && grid_v_bar, DW_EINVAL, "mpm_grid_update_adj: missing argument");
@@ -833,15 +953,32 @@ extern "C" int mpm_grid_update_adj(const dw_grid *grid, const dw_mpm_params *par
   if (rc) return rc;
   GridDev g = make_grid(grid);
   int64_t N = (int64_t)grid->nx * grid->ny * grid->nz;
-  hipLaunchKernelGGL(k_grid_update_adj, dim3(node_blocks(W.n_tiles)), dim3(256), 0, (hipStream_t)stream, g, params->dt,
+  auto k = W_bar ? k_grid_update_adj<true> : k_grid_update_adj<false>;
+  hipLaunchKernelGGL(k, dim3(node_blocks(W.n_tiles)), dim3(256), 0, (hipStream_t)stream, g, params->dt,
                      params->gravity[0], params->gravity[1], params->gravity[2], params->bound, grid_m, grid_mv, wd,
-                     pin, W.node_tiles, W.n_node_tiles, grid_v_bar, grid_m_bar, grid_mv_bar, acc_bar, N);
+                     pin, W.node_tiles, W.n_node_tiles, grid_v_bar, grid_m_bar, grid_mv_bar, acc_bar, W_bar, N);
   return check_launch("mpm_grid_update_adj");
 }
 
-extern "C" int mpm_g2p_adj(const dw_grid *grid, const dw_mpm_params *params, const float *grid_v,
-                           const dw_particles *in, const dw_particles_bar *out_bar, dw_particles_bar *in_bar,
-                           float *grid_v_bar, const void *ws, size_t ws_bytes, void *stream) {
+extern "C" int mpm_grid_update_adj(const dw_grid *grid, const dw_mpm_params *params, const float *grid_m,
+                                   const float *grid_mv, const dw_wind *wind, const uint8_t *pin,
+                                   const float *grid_v_bar, float *grid_m_bar, float *grid_mv_bar, float *acc_bar,
+                                   const void *ws, size_t ws_bytes, void *stream) {
+  return grid_update_adj(grid, params, grid_m, grid_mv, wind, pin, const_cast<float *>(grid_v_bar), grid_m_bar,
+                         grid_mv_bar, acc_bar, nullptr, ws, ws_bytes, stream);
+}
+
+int dw::run_grid_update_adj_fused(const dw_grid *grid, const dw_mpm_params *params, const float *grid_m,
+                                  const float *grid_mv, const dw_wind *wind, const uint8_t *pin, float *grid_v_bar,
+                                  float *grid_m_bar, float *grid_mv_bar, float *W_bar, const void *ws,
+                                  size_t ws_bytes, void *stream) {
+  return grid_update_adj(grid, params, grid_m, grid_mv, wind, pin, grid_v_bar, grid_m_bar, grid_mv_bar, nullptr,
+                         W_bar, ws, ws_bytes, stream);
+}
+
+int dw::run_g2p_adj(const dw_grid *grid, const dw_mpm_params *params, const float *grid_v, const dw_particles *in,
+                    const dw_particles_bar *out_bar, dw_particles_bar *in_bar, float *grid_v_bar, const void *ws,
+                    size_t ws_bytes, void *stream, int fresh) {
   int rc = check_grid(grid);
   if (rc) return rc;
   DW_REQUIRE(params && grid_v && in && out_bar && in_bar && grid_v_bar, DW_EINVAL,
@@ -861,13 +998,19 @@ extern "C" int mpm_g2p_adj(const dw_grid *grid, const dw_mpm_params *params, con
   if (det) {
     hipLaunchKernelGGL(k_g2p_adj<true>, dim3(blocks), dim3(SC_THREADS), 0, s, g, params->dt, grid_v, N, in->x,
                        in->xref, in->F, in->n, out_bar->x, out_bar->v, out_bar->C, out_bar->F, in_bar->x, in_bar->F,
-                       grid_v_bar, W.perm, W.tile_start, W.item_tile, W.item_begin, W.n_items, W.item_part);
+                       grid_v_bar, W.perm, W.tile_start, W.item_tile, W.item_begin, W.n_items, W.item_part, fresh);
     hipLaunchKernelGGL(k_det_gather<true>, dim3(node_blocks(W.n_tiles)), dim3(256), 0, s, g, W.node_tiles, W.n_node_tiles,
                        W.tile_count, W.item_first, W.item_part, (float *)nullptr, grid_v_bar, N, (int32_t *)nullptr);
   } else {
     hipLaunchKernelGGL(k_g2p_adj<false>, dim3(blocks), dim3(SC_THREADS), 0, s, g, params->dt, grid_v, N, in->x,
                        in->xref, in->F, in->n, out_bar->x, out_bar->v, out_bar->C, out_bar->F, in_bar->x, in_bar->F,
-                       grid_v_bar, W.perm, W.tile_start, W.item_tile, W.item_begin, W.n_items, (float *)nullptr);
+                       grid_v_bar, W.perm, W.tile_start, W.item_tile, W.item_begin, W.n_items, (float *)nullptr, fresh);
   }
   return check_launch("mpm_g2p_adj");
+}
+
+extern "C" int mpm_g2p_adj(const dw_grid *grid, const dw_mpm_params *params, const float *grid_v,
+                           const dw_particles *in, const dw_particles_bar *out_bar, dw_particles_bar *in_bar,
+                           float *grid_v_bar, const void *ws, size_t ws_bytes, void *stream) {
+  return dw::run_g2p_adj(grid, params, grid_v, in, out_bar, in_bar, grid_v_bar, ws, ws_bytes, stream, 0);
 }

@@ -128,3 +128,56 @@ def test_rollout_deterministic_gradient_is_bit_reproducible():
     eE = ((gEa - gEo).norm() / gEo.norm()).item()
     say(f"  rel err dL/dW {eW:.2e} dL/dE {eE:.2e}")
     assert eW < 1e-3 and eE < 1e-3
+
+
+@pytest.mark.parametrize("res,nw,ckpt,n_sub,K,det", [(16, 4, 4, 12, 2, False), (18, 5, 5, 7, 3, False),
+                                                     (16, 24, 3, 6, 1, False), (22, 2, 1, 3, 5, False),
+                                                     (18, 5, 4, 6, 2, True)])
+def test_rollout_loop_matches_single_calls(res, nw, ckpt, n_sub, K, det):
+    """The rollout's substep loops against the entry points called one by one
+    (RolloutPlan.substep and substep_adjoint): wind grids coarser and finer than
+    the simulation grid (more wind cells per node tile than are summed in the
+    wave), grids with partial tiles, ragged and single-substep segments.  The
+    same products summed in another order: 1e-5; equal in the deterministic mode."""
+    say(f"rollout loop res={res} nw={nw} ckpt={ckpt} n_sub={n_sub} K={K} det={det}")
+    rng = np.random.default_rng(res + nw)
+    n = 900
+    dev = dict(dtype=torch.float32, device=DEV)
+    x0 = torch.as_tensor(0.3 + 0.4 * rng.random((3, n))).float().to(DEV)
+    v0 = torch.as_tensor(0.1 * rng.standard_normal((3, n))).float().to(DEV)
+    z9 = torch.zeros(9, n, **dev)
+    E, nu = torch.tensor([30.0, 60.0], **dev), torch.tensor([0.3, 0.25], **dev)
+    region = torch.as_tensor(rng.integers(0, 2, n)).to(torch.int32).to(DEV)
+    W = torch.as_tensor(2.0 * rng.standard_normal((K, 3, nw ** 3))).float().to(DEV)
+    pin = torch.as_tensor(rng.random(res ** 3) < 0.05).to(torch.uint8).to(DEV)
+    plan = RolloutPlan(dict(nx=res, ny=res, nz=res, dx=1.0 / res, origin=(0.0, 0.0, 0.0)), n, torch.full((n,), 1.0 / n, **dev),
+                       torch.full((n,), 1.0 / n, **dev), region, nu, pin, 1e-3, (0.0, -2.0, 0.0), api.FIXED_COROTATED, 2,
+                       (nw,) * 3, (0, 0, 0), (1, 1, 1), K, n_sub, ckpt, deterministic=det)
+    cot = [torch.as_tensor(rng.standard_normal((k, n))).float().to(DEV) for k in (3, 3, 9, 9)]
+    # one call per entry point
+    states = [[x0.clone(), v0.clone(), z9.clone(), z9.clone()]]
+    for s in range(n_sub):
+        nxt = [torch.empty_like(t) for t in states[-1]]
+        plan.substep(plan.particles(*states[-1], E), W, s, out=nxt)
+        states.append(nxt)
+    bar, W_bar, E_bar = [c.clone() for c in cot], torch.zeros_like(W), torch.zeros_like(E)
+    for s in reversed(range(n_sub)):
+        new = [torch.zeros_like(b) for b in bar]
+        plan.substep_adjoint(plan.particles(*states[s], E), W, s, bar, new, W_bar, E_bar)
+        bar = new
+    want = [W_bar, E_bar, *bar]
+    # the rollout, twice: every buffer it keeps is used again
+    leaves = [t.clone().requires_grad_(True) for t in (W, E, x0, v0, z9, z9)]
+    for _ in range(2):
+        out = rollout(plan, *leaves)
+        got = torch.autograd.grad(out, leaves, cot)
+        for a, b in zip(list(out) + list(got), states[-1] + want):
+            if det:
+                assert torch.equal(a, b)
+            else:
+                assert ((a.double() - b.double()).norm() / b.double().norm()).item() < 1e-5
+    # cotangents left out are zero
+    got = torch.autograd.grad(rollout(plan, *leaves)[1], leaves, cot[1])
+    ref = torch.autograd.grad(rollout(plan, *leaves), leaves, [torch.zeros_like(c) if k != 1 else c for k, c in enumerate(cot)])
+    for a, b in zip(got, ref):
+        assert ((a.double() - b.double()).norm() <= 1e-5 * b.double().norm()).item()
