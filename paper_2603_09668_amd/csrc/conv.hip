@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_bf16.h>
 
+#include <algorithm>
 #include <climits>
 
 #include "dw_internal.h"
@@ -61,8 +62,16 @@ struct ConvGeom {
 // (channels-last, 16-byte chunks of 8 channels), then:
 //  * 32-channel inputs: tiles of FX x FY x CZ = 16 x 4 x 4 outputs; a
 //    workgroup walks a column of tiles along z, the patch planes in a ring
-//    of RING slots, and copies the next tile's CZ new planes into the slots
-//    the current tile does not read while its MFMAs run.  Wave w computes a
+//    of RING slots; each wave copies one of the next tile's CZ new planes
+//    into a slot the current tile does not read while its MFMAs run.  The
+//    copies are asynchronous (copy_to_lds) from per-lane offsets made once per
+//    column, and what the epilogue reads (the gradient's gates, the output
+//    layer's field) is requested ahead of the MFMAs too, so that one wait per
+//    tile is all that memory costs; with copies that the compiler waited for
+//    and gates read in the epilogue, 16 x 64^3 voxels took 220 (32 -> 32), 150
+//    (32 -> 3) and 322 us (data gradient), now 200, 118 and 226.  The matrix
+//    cores need 92 us of the first at 2.4 GHz, the memory 55 of the second and
+//    160 of the third.  Wave w computes a
 //    4 (y) x RZ (z) block of output rows for one 16-channel m-tile, holding
 //    that m-tile's 27 weight fragments in registers for the life of the
 //    kernel.  For each x-shift it walks the (RZ+2) x 6 input rows; every
@@ -70,9 +79,12 @@ struct ConvGeom {
 //    map it onto an output row).
 //  * 8-channel inputs (3 channels padded): tiles of FX x FY x FZ = 16 x 4 x 8
 //    outputs, one patch per tile; K = 32 spans 4 taps; each wave computes 8
-//    whole rows, all m-tiles, two rows at a time.
+//    whole rows, all m-tiles, two rows at a time, and stores whole voxels
+//    (out_channel).  Bound by the 268 MB that the 16 x 64^3 voxels write: 110
+//    -> 96 us (3 -> 32), and by as much again read by the data gradient, 195 ->
+//    141 (with four workgroups per CU instead of two).
 // The 4 chunks of a voxel's 32 channels are stored permuted by swz(x) so the
-// 16 lanes of a fragment read (16 consecutive x) spread over the LDS banks.
+// fragment reads spread over the LDS banks.
 
 constexpr int FX = 16, FY = 4, FZ = 8;                 // output tile
 constexpr int QX = FX + 2, QY = FY + 2, QZ = FZ + 2;   // input patch
@@ -81,7 +93,7 @@ constexpr int QVOX = QX * QY * QZ;
 // 32-channel inputs: tiles of FX x FY x CZ outputs, walked along z; the
 // patch planes live in a ring of RING slots of CPLANE elements in LDS
 constexpr int CZ = 4, CQZ = CZ + 2, RING = QZ;
-constexpr int CPLANE = QX * QY * 32;
+constexpr int CPLANE = (QX * QY * 4 + 63) / 64 * 64 * 8;  // whole waves of chunks
 static_assert(RING >= CQZ + CZ, "the next tile's new planes need slots of their own");
 
 struct FwdTiles {
@@ -106,10 +118,11 @@ __device__ __forceinline__ TileOrigin fwd_tile(const FwdTiles &T, int t) {
 }
 
 // chunk c of a patch voxel with x index xx is stored at position c ^ swz(xx).
-// A 16-byte LDS read is served 16 lanes (256 bytes) at a time; the 16 lanes
-// of a fragment read take 16 consecutive x, whose voxels lie 64 bytes apart,
-// so x and x + 4, x + 8, x + 12 would share banks without the permutation.
-__device__ __forceinline__ int swz(int xx) { return (xx >> 2) & 3; }
+// The 64 lanes of a fragment read take 16 consecutive x and all four chunks.
+// Of the 1,024 linear maps of x's bits to two bits this is one of those whose
+// reads are free of bank conflicts at every x shift (6.4 cycles per read of
+// two workgroups against 9.8 with bits 2 and 3 of x).
+__device__ __forceinline__ int swz(int xx) { return (xx & 1) | ((xx >> 1) & 2); }
 
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
@@ -163,43 +176,47 @@ __device__ __forceinline__ void stage_patch(const ConvGeom &G, const uint16_t *_
   }
 }
 
-// Copy planes zi0 .. zi0 + np - 1 of the zero-padded input patch of tile o
-// (patch-relative z) into LDS at dst (np consecutive plane slots of
-// QX * QY voxels).  Lanes past the range issue no copy, so the slots after
-// the range are left as they are.
-template <int CINP>
-__device__ __forceinline__ void stage_planes(const ConvGeom &G, const uint16_t *__restrict__ x, const TileOrigin &o,
-                                             uint16_t *dst, int zi0, int np) {
-  constexpr int VEC = CINP / 8;
-  constexpr int D = 256 / VEC;
-  constexpr int DX = D % QX, DY = (D / QX) % QY, DZ = D / (QX * QY);
-  static_assert(256 % VEC == 0, "a lane keeps its channel chunk across iterations");
-  const int nch = np * QX * QY * VEC;
-  const uint16_t *field = x + (int64_t)o.b * G.L * CINP;
-  __amdgpu_buffer_rsrc_t rsrc =
-      __builtin_amdgcn_make_buffer_rsrc((void *)field, (short)0, (int)(G.L * CINP * 2), 0x00020000);
-  const int wid = threadIdx.x >> 6;
-  int lane = threadIdx.x & 63;
-  asm volatile("" : "+v"(lane));
-  const int ql = wid * 64 + lane;
-  const int p = ql % VEC;
-  const int v = ql / VEC;
-  int xx = v % QX, yy = (v / QX) % QY;
-  int gx = o.x0 + xx - 1, gy = o.y0 + yy - 1, gz = o.z0 + zi0 + v / (QX * QY) - 1;
-  const int sy = G.nx, sz = G.nx * G.ny;
-  int lin = gx + sy * gy + sz * gz;
-  for (int q0 = wid * 64; q0 < nch; q0 += 256) {
-    const int q = q0 + lane;
-    const int c = VEC == 4 ? (p ^ swz(xx)) : p;
-    const bool in = (unsigned)gx < (unsigned)G.nx && (unsigned)gy < (unsigned)G.ny && (unsigned)gz < (unsigned)G.nz;
-    const unsigned off = in ? (unsigned)((lin * CINP + c * 8) * 2) : 0x80000000u;
-    if (q < nch) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(dst + q0 * 8), 16, off, 0, 0, 0);
-    xx += DX; gx += DX; lin += DX;
-    if (xx >= QX) { xx -= QX; gx -= QX; yy += 1; gy += 1; lin += sy - QX; }
-    yy += DY; gy += DY; lin += DY * sy;
-    if (yy >= QY) { yy -= QY; gy -= QY; gz += 1; lin += sz - QY * sy; }
-    gz += DZ; lin += DZ * sz;
+// one 16-byte chunk per lane from `off` of the buffer into LDS at `lds` +
+// 16 lane; completion is counted in vmcnt only.  Written in assembly because
+// the compiler cannot tell which LDS bytes the copy writes and would wait
+// for it (and for every store before it) ahead of the next LDS read.  The
+// caller waits (s_waitcnt vmcnt) and passes a barrier before reading.  m0 is
+// set here and used by nothing else in these kernels.
+__device__ __forceinline__ void copy_to_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t lds, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(off), "s"(rsrc)
+               : "memory");
+}
+
+typedef __attribute__((address_space(3))) char *lds_bytes_t;
+
+// Byte offsets, within a z plane of the field, of the PCH chunks per lane that
+// make a plane of the patch of a column (32 channels): chunk 64 j + lane of
+// the plane; out of the buffer (zeros) outside the field and past the plane.
+constexpr int PCH = (QX * QY * 4 + 63) / 64;
+__device__ __forceinline__ void plane_offsets(const ConvGeom &G, int x0, int y0, uint32_t (&off)[PCH]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int j = 0; j < PCH; ++j) {
+    const int q = j * 64 + lane, vox = q / 4, xx = vox % QX, yy = vox / QX;
+    const int gx = x0 + xx - 1, gy = y0 + yy - 1, c = (q % 4) ^ swz(xx);
+    const bool in = yy < QY && (unsigned)gx < (unsigned)G.nx && (unsigned)gy < (unsigned)G.ny;
+    off[j] = in ? (uint32_t)((gx + G.nx * gy) * 64 + c * 16) : 0x80000000u;
   }
+}
+
+// Issue the copies of plane gz of field `field` (32 channels) into LDS at
+// `lds`; a plane outside the field is zeros.  All of it wave-uniform.
+__device__ __forceinline__ void copy_plane(const ConvGeom &G, const uint16_t *field, int gz, uint32_t lds,
+                                           const uint32_t (&off)[PCH]) {
+  const bool in = gz >= 0 && gz < G.nz;
+  const uint32_t plane = (uint32_t)(G.nx * G.ny) * 64u;
+  const uint64_t base = (uint64_t)field + (in ? (uint64_t)gz * plane : 0ull);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base), hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)),
+                 size = __builtin_amdgcn_readfirstlane(in ? plane : 0u), dst = __builtin_amdgcn_readfirstlane(lds);
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(((uint64_t)hi << 32) | lo), (short)0,
+                                                                        (int)size, 0x00020000);
+#pragma unroll
+  for (int j = 0; j < PCH; ++j) copy_to_lds(rsrc, dst + j * 1024, off[j]);
 }
 
 // Work item v of the column plan: column v % ncol, z segment v / ncol.
@@ -225,8 +242,8 @@ template <int COUTP, int EPI>
 __device__ __forceinline__ void conv_epilogue(const ConvGeom &G, const TileOrigin &o, bool live, uint32_t vi,
                                               int co0, floatx4 acc, const float *s_bias, int cout,
                                               uint16_t *__restrict__ y, uint16_t *__restrict__ zpre,
-                                              const uint16_t *__restrict__ zgate, const float *__restrict__ u,
-                                              float sb, float *__restrict__ u_out) {
+                                              uint2 zg, const float *__restrict__ u, float sb,
+                                              float *__restrict__ u_out) {
   if (!live) return;
   const uint32_t ei = vi * COUTP + co0;  // element offset in the field's activations
   const size_t fb = (size_t)o.b * G.L * COUTP;
@@ -248,7 +265,6 @@ __device__ __forceinline__ void conv_epilogue(const ConvGeom &G, const TileOrigi
       }
     }
   } else {  // DW_CONV_DGRAD: gradient through the previous layer's silu
-    const uint2 zg = *reinterpret_cast<const uint2 *>(zgate + fb + ei);
     const float zf[4] = {bf2f((uint16_t)(zg.x & 0xffff)), bf2f((uint16_t)(zg.x >> 16)), bf2f((uint16_t)(zg.y & 0xffff)),
                          bf2f((uint16_t)(zg.y >> 16))};
     float ob[4];
@@ -258,15 +274,52 @@ __device__ __forceinline__ void conv_epilogue(const ConvGeom &G, const TileOrigi
   }
 }
 
+// 8-channel inputs: a wave computes both 16-channel m-tiles, so their rows are
+// dealt to the output channels such that a lane's four rows of each make eight
+// adjacent channels 8 g .. 8 g + 7, and a wave stores 16 whole voxels (1 KB)
+// with one instruction.
+template <int MT>
+__device__ __forceinline__ int out_channel(int m, int row) {
+  return MT == 2 ? 8 * (row >> 2) + 4 * m + (row & 3) : row;
+}
+
+template <int EPI>
+__device__ __forceinline__ void wide_epilogue(uint32_t vi, int g, const floatx4 (&acc)[2], const float *s_bias,
+                                              uint16_t *__restrict__ y, uint16_t *__restrict__ zpre,
+                                              const uint16_t *__restrict__ zgate) {
+  const uint32_t ei = vi * 32 + 8 * g;
+  uint32_t out[4];
+  if (EPI == DW_CONV_HIDDEN) {
+    uint32_t z[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float a = acc[q >> 1][(2 * q) & 3] + s_bias[8 * g + 2 * q],
+                  b = acc[q >> 1][(2 * q + 1) & 3] + s_bias[8 * g + 2 * q + 1];
+      out[q] = f2bf2(silu(a), silu(b));
+      z[q] = f2bf2(a, b);
+    }
+    if (zpre) *reinterpret_cast<uint4 *>(zpre + ei) = make_uint4(z[0], z[1], z[2], z[3]);
+  } else {  // DW_CONV_DGRAD: gradient through the previous layer's silu
+    const uint4 zg = *reinterpret_cast<const uint4 *>(zgate + ei);
+    const uint32_t z[4] = {zg.x, zg.y, zg.z, zg.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      out[q] = f2bf2(acc[q >> 1][(2 * q) & 3] * silu_grad(bf2f((uint16_t)(z[q] & 0xffff))),
+                     acc[q >> 1][(2 * q + 1) & 3] * silu_grad(bf2f((uint16_t)(z[q] >> 16))));
+  }
+  *reinterpret_cast<uint4 *>(y + ei) = make_uint4(out[0], out[1], out[2], out[3]);
+}
+
 // Packed weights: [chunk][COUTP][32] bf16, see conv_pack_weights.
 template <int CINP, int COUTP, int EPI>
-__global__ __launch_bounds__(256, 2) void k_conv(ConvGeom G, FwdTiles T, const uint16_t *__restrict__ x,
+__global__ __launch_bounds__(256, CINP == 32 ? 2 : 4) void k_conv(ConvGeom G, FwdTiles T, const uint16_t *__restrict__ x,
                                                  const uint16_t *__restrict__ wk, const float *__restrict__ bias,
                                                  int cout, uint16_t *__restrict__ y, uint16_t *__restrict__ zpre,
                                                  const uint16_t *__restrict__ zgate, const float *__restrict__ u,
                                                  const float *__restrict__ scale, float *__restrict__ u_out) {
   constexpr int MT = COUTP / 16;
-  constexpr int PATCH = (QVOX * CINP / 8 + 63) / 64 * 64 * 8;  // bf16 elements, whole waves of chunks
+  // bf16 elements, whole waves of chunks
+  constexpr int PATCH = CINP == 32 ? RING * CPLANE : (QVOX * CINP / 8 + 63) / 64 * 64 * 8;
   __shared__ __attribute__((aligned(16))) uint16_t s_in[PATCH];
   __shared__ float s_bias[32];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -299,6 +352,9 @@ __global__ __launch_bounds__(256, 2) void k_conv(ConvGeom G, FwdTiles T, const u
     }
     floatx4 acc[RZ][FY];
     float uin[RZ][FY][3];
+    uint2 zin[RZ][FY];
+    uint32_t off[PCH];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes_t)s_in;
     TileOrigin op{};
     bool have_prev = false;
     auto epilogue = [&](const TileOrigin &oe) {
@@ -323,15 +379,17 @@ __global__ __launch_bounds__(256, 2) void k_conv(ConvGeom G, FwdTiles T, const u
             }
           } else {
             conv_epilogue<COUTP, EPI>(G, oe, live, v00 + yo * sy + zo * sz, mt * 16 + 4 * g, acc[zo][yo], s_bias,
-                                      cout, y, zpre, zgate, u, sb, u_out);
+                                      cout, y, zpre, zin[zo][yo], u, sb, u_out);
           }
         }
     };
     while (v < T.nitems) {
       const TileOrigin o{ci.b, ci.x0, ci.y0, zt * CZ};
+      const uint16_t *field = x + (int64_t)o.b * G.L * CINP;
       if (fresh) {
+        plane_offsets(G, o.x0, o.y0, off);
         __syncthreads();  // every wave is done with the previous tile's planes
-        stage_planes<CINP>(G, x, o, s_in, 0, CQZ);
+        for (int zi = wid; zi < CQZ; zi += 4) copy_plane(G, field, o.z0 - 1 + zi, lds0 + zi * CPLANE * 2, off);
         rot = 0;
         fresh = false;
       }
@@ -339,12 +397,9 @@ __global__ __launch_bounds__(256, 2) void k_conv(ConvGeom G, FwdTiles T, const u
       __syncthreads();  // every wave's have, and every wave is done with the previous tile
       const bool more = zt + 1 < ci.zt1;
       if (more) {
-        // planes 2 .. CQZ-1 of the next tile into slots rot + CQZ .. rot + RING - 1
-        const TileOrigin on{ci.b, ci.x0, ci.y0, (zt + 1) * CZ};
-        const int s0 = rot + CQZ >= RING ? rot + CQZ - RING : rot + CQZ;
-        const int n1 = RING - s0 < CZ ? RING - s0 : CZ;
-        stage_planes<CINP>(G, x, on, s_in + s0 * CPLANE, 2, n1);
-        if (n1 < CZ) stage_planes<CINP>(G, x, on, s_in, 2 + n1, CZ - n1);
+        // one new plane per wave: planes 2 .. CQZ-1 of the next tile's patch
+        const int sl = rot + CQZ + wid;
+        copy_plane(G, field, o.z0 + CZ + 1 + wid, lds0 + (sl >= RING ? sl - RING : sl) * CPLANE * 2, off);
       }
       // epilogue of the previous tile: its stores are issued before this
       // tile's MFMAs and complete while they run, so the next barrier does
@@ -352,6 +407,20 @@ __global__ __launch_bounds__(256, 2) void k_conv(ConvGeom G, FwdTiles T, const u
       if (have_prev) epilogue(op);
       // output layer: the input field's values at this wave's outputs are
       // requested now and arrive during the MFMAs
+      // (data gradient: likewise the pre-activations that gate it)
+      if constexpr (EPI == DW_CONV_DGRAD) {
+        const int gx = o.x0 + r16;
+        const uint32_t sy = (uint32_t)G.nx, sz = (uint32_t)G.nx * (uint32_t)G.ny;
+        const uint32_t v00 = (uint32_t)gx + sy * (uint32_t)o.y0 + sz * (uint32_t)(o.z0 + zb);
+        const uint16_t *zf = zgate + (size_t)o.b * G.L * COUTP + mt * 16 + 4 * g;
+#pragma unroll
+        for (int zo = 0; zo < RZ; ++zo)
+#pragma unroll
+          for (int yo = 0; yo < FY; ++yo) {
+            const bool live = gx < G.nx && o.y0 + yo < G.ny && o.z0 + zb + zo < G.nz;
+            zin[zo][yo] = live ? *reinterpret_cast<const uint2 *>(zf + (v00 + yo * sy + zo * sz) * COUTP) : uint2{};
+          }
+      }
       if constexpr (EPI == DW_CONV_OUTPUT) {
         const int gx = o.x0 + r16;
         const uint32_t sy = (uint32_t)G.nx, sz = (uint32_t)G.nx * (uint32_t)G.ny;
@@ -436,14 +505,13 @@ __global__ __launch_bounds__(256, 2) void k_conv(ConvGeom G, FwdTiles T, const u
     for (int c = 0; c < 7; ++c)
 #pragma unroll
       for (int m = 0; m < MT; ++m)
-        wf[c][m] = *reinterpret_cast<const bf16x8 *>(wk + ((c * COUTP + m * 16 + r16) * 32 + g * 8));
+        wf[c][m] = *reinterpret_cast<const bf16x8 *>(wk + ((c * COUTP + out_channel<MT>(m, r16)) * 32 + g * 8));
     for (int t = blockIdx.x; t < T.n; t += gridDim.x) {
       const TileOrigin o = fwd_tile(T, t);
       __syncthreads();
       stage_patch<CINP>(G, x, o, s_in);
       __builtin_amdgcn_s_waitcnt(0x0f70);
       __syncthreads();
-      const float sb = EPI == DW_CONV_OUTPUT ? scale[o.b] : 0.f;
 #pragma unroll
       for (int pr = 0; pr < 4; ++pr) {
         floatx4 acc[2][MT];
@@ -471,16 +539,14 @@ __global__ __launch_bounds__(256, 2) void k_conv(ConvGeom G, FwdTiles T, const u
         }
         const int gx = o.x0 + r16;
         const uint32_t sy = (uint32_t)G.nx, sz = (uint32_t)G.nx * (uint32_t)G.ny;
+        const size_t fb = (size_t)o.b * G.L * COUTP;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
           const int row = wid * 8 + pr * 2 + i;
           const int gy = o.y0 + row % FY, gz = o.z0 + row / FY;
           const bool live = gx < G.nx && gy < G.ny && gz < G.nz;
           const uint32_t vi = (uint32_t)gx + sy * (uint32_t)gy + sz * (uint32_t)gz;
-#pragma unroll
-          for (int m = 0; m < MT; ++m)
-            conv_epilogue<COUTP, EPI>(G, o, live, vi, m * 16 + 4 * g, acc[i][m], s_bias, cout, y, zpre, zgate, u, sb,
-                                      u_out);
+          if (live) wide_epilogue<EPI>(vi, g, acc[i], s_bias, y + fb, zpre ? zpre + fb : nullptr, zgate + fb);
         }
       }
     }
@@ -575,18 +641,6 @@ struct WgPlan {
   int cin, cout;
 };
 
-// one 16-byte chunk per lane from `off` of the buffer into LDS at `lds` +
-// 16 lane; completion is counted in vmcnt only.  Written in assembly because
-// the compiler cannot tell which LDS bytes the copy writes and would wait
-// for it (and for every store before it) ahead of the next LDS read.  The
-// caller waits (s_waitcnt vmcnt) and passes a barrier before reading.  m0 is
-// set here and used by nothing else in these kernels.
-__device__ __forceinline__ void copy_to_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t lds, uint32_t off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(off), "s"(rsrc)
-               : "memory");
-}
-
-typedef __attribute__((address_space(3))) char *lds_bytes_t;
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) bf16x4 *lds_bf16x4_t;
 
@@ -1027,19 +1081,29 @@ static FwdTiles fwd_tiles(const ConvGeom &G) {
   T.ty = (G.ny + FY - 1) / FY;
   T.tz = (G.nz + FZ - 1) / FZ;
   T.n = T.tx * T.ty * T.tz * G.B;
-  // columns, split into z segments when there are fewer columns than the
-  // 512 resident workgroups
+  // columns, cut into the z segments that leave the fullest of the 512
+  // resident workgroups the fewest tiles, counting one more per segment for
+  // its first patch (nothing runs beside that copy): 12 fields of 64^3 are 768
+  // columns of 16 tiles, two rounds of whole columns or three of halves
+  // (32 -> 32: 184 us as the former, 148 as the latter)
   T.tzc = (G.nz + CZ - 1) / CZ;
   T.ncol = T.tx * T.ty * G.B;
-  int segs = T.ncol >= 512 ? 1 : (512 + T.ncol - 1) / T.ncol;
-  segs = segs < T.tzc ? segs : T.tzc;
-  T.zlen = (T.tzc + segs - 1) / segs;
-  T.nitems = T.ncol * ((T.tzc + T.zlen - 1) / T.zlen);
+  int64_t best = INT64_MAX;
+  const int most = std::min(T.tzc, std::max(32, 1024 / T.ncol));
+  for (int segs = 1; segs <= most; ++segs) {
+    const int len = (T.tzc + segs - 1) / segs;
+    const int64_t items = (int64_t)T.ncol * ((T.tzc + len - 1) / len), cost = (items + 511) / 512 * (len + 1);
+    if (cost < best) {
+      best = cost;
+      T.zlen = len;
+      T.nitems = (int)items;
+    }
+  }
   return T;
 }
 
-// persistent grid: two workgroups per CU
-static unsigned fwd_blocks(const FwdTiles &T) { return (unsigned)(T.n < 512 ? T.n : 512); }
+// persistent grids: four (8-channel inputs) and two workgroups per CU
+static unsigned fwd_blocks(const FwdTiles &T) { return (unsigned)(T.n < 1024 ? T.n : 1024); }
 static unsigned col_blocks(const FwdTiles &T) { return (unsigned)(T.nitems < 512 ? T.nitems : 512); }
 
 }  // namespace dw

@@ -137,6 +137,17 @@ def test_data_gradient(dims, cout):
     _check("dgrad", _from_dev_act(y, dims, 32, 32), ref, U_BF * ref.abs() + 2 * ACC * da * gate.abs())
 
 
+@pytest.mark.parametrize("dims", [(1, 1, 1, 1), (1, 17, 3, 4), (1, 15, 5, 5), (2, 33, 4, 8), (1, 16, 4, 9), (5, 128, 64, 6)])
+def test_layer_tile_edges(dims):
+    """One voxel, tiles one short of and past whole ones on each axis, columns
+    of one to three tiles, and more columns than workgroups, cut in z (the last
+    size): every layer form with the bounds of the tests above."""
+    for c in (3, 32):
+        test_hidden_layer_forward(dims, c)
+        test_data_gradient(dims, c)
+    test_output_layer_forward(dims)
+
+
 @pytest.mark.parametrize("dims", DIMS)
 @pytest.mark.parametrize("cin,cout", [(3, 32), (32, 32), (32, 3)])
 def test_weight_and_bias_gradient(dims, cin, cout):
