@@ -1537,9 +1537,11 @@ __global__ __launch_bounds__(256) void k_loss_final(int nblk, int64_t count, flo
                                                     const float *__restrict__ part, float *__restrict__ loss) {
   __shared__ float s_m[256], s_l[256];
   float m = 0.f, l = 0.f;
+#pragma unroll 8
   for (int q = threadIdx.x; q < nblk; q += 256) {
-    m += part[2 * q];
-    l += part[2 * q + 1];
+    const float2 p = reinterpret_cast<const float2 *>(part)[q];
+    m += p.x;
+    l += p.y;
   }
   s_m[threadIdx.x] = m;
   s_l[threadIdx.x] = l;
