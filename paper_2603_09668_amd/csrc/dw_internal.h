@@ -435,6 +435,17 @@ __device__ __forceinline__ Coord make_coord(bool ref, float xr, float x, float o
 }
 
 // element idx of the position arrays (xr may be NULL: absolute positions)
+// Component q of a [rows][n] particle array at byte offset off = 4 p: a scalar
+// base and a 32-bit offset, so the many arrays take no vector address pairs
+// (n is below 2^31 / 9, the largest F index held in an int).
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(1))) T &at_particle(T *base, int q, int n, uint32_t off) {
+  uint64_t row = reinterpret_cast<uint64_t>(base + (size_t)q * n);
+  row = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(row >> 32)) << 32) |
+        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)row);  // kept scalar
+  return *((__attribute__((address_space(1))) T *)row + (off >> 2));
+}
+
 __device__ __forceinline__ Coord load_coord(const float *xr, const float *x, size_t idx, float o, float inv_dx) {
   return make_coord(xr != nullptr, xr ? xr[idx] : 0.f, x[idx], o, inv_dx);
 }

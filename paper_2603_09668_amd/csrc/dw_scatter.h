@@ -5,15 +5,24 @@
 // base_p + o of the tile's 6^3 node region, with f_p the particle's position
 // in its base cell (in cells), w_o the quadratic B-spline weight, q_p a
 // 3-vector and A_p a 3x3 matrix (P2G also adds w_o m_p as a fourth value).
-// A workgroup stages its particles in LDS in cell order (f as one 16-byte
-// record per particle, read with one instruction; m, q, A row-major as 13
-// feature rows), cuts each cell into units of at most SC_UNIT
-// particles, and per unit forms Feat (13 x n) W (n x 27) with fp32 MFMA
-// 16x16x4 (four particles per step, offsets in two 16-column tiles), the
-// rows ordered so that the four result rows a lane holds give one node
-// value: (1, ox, oy, oz) . rows.  Every wave adds its units' 27 x 4 values
-// into its own 6^3 node block in LDS (a unit's 27 offsets reach 27 distinct
-// nodes: plain adds); the node owners then add the wave blocks.
+// A workgroup stages its particles in LDS in cell order (m, q, A row-major as
+// 13 feature rows; the weights as 3 rows w_x and 9 rows w_y w_z), cuts each
+// cell into units of at most SC_UNIT particles, and per unit forms Feat (13 x
+// n) W (n x 27) with fp32 MFMA 16x16x4 (four particles per step, offsets in
+// two 16-column tiles), the rows ordered so that the four result rows a lane
+// holds give one node value: (1, ox, oy, oz) . rows.  Every wave adds its
+// units' 27 x 4 values into its own 6^3 node block in LDS (a unit's 27 offsets
+// reach 27 distinct nodes: plain adds); the node owners then add the wave
+// blocks.
+// What bounds a scatter is no one unit: of 4M particles' P2G the matrix phase is
+// 70 us, its read-modify-writes of the node blocks 20 of them, the stresses 9,
+// and the rest the particle loads and the phases between barriers.  Three
+// things were worth their while: the staging thread evaluates its particle's
+// weights once (every lane of a step evaluated the polynomials of its column
+// anew: 22 % of all vector instructions), both tiles' old node values are
+// read together, and the units are ordered by steps instead of lengths.  P2G
+// of 4M / 500k / 20k particles 246 / 44.7 / 12.7 -> 234 / 42.6 / 12.0 us, reverse G2P of
+// 256k 45 -> 41.
 #pragma once
 
 #include "dw_internal.h"
@@ -22,32 +31,29 @@ namespace dw {
 
 constexpr int SC_L = 6;           // local node extent of a cell tile's stencils
 constexpr int SC_NODES = 216;     // 6^3
-constexpr int SC_DAT = 13;        // staged feature rows per particle: m, q(3), A(9)
+constexpr int SC_DAT = 13;        // staged feature rows per particle: m (P2G only), q(3), A(9)
+constexpr int SC_WGT = 12;        // staged weight rows: w_x(3), w_y w_z(9)
 constexpr int SC_UNIT = 16;       // particles per unit (4 MFMA steps): a dense cell spreads over waves
 constexpr int SC_MAX_UNITS = 64 + WORK_CHUNK / SC_UNIT;  // bounds the sum over cells of ceil(count / unit)
 constexpr int SC_THREADS = WORK_CHUNK;
 constexpr int SC_WAVES = SC_THREADS / 64;
-constexpr int SC_PITCH = WORK_CHUNK + 4;  // staged rows padded: the 13 feature rows of one operand hit distinct banks
+constexpr int SC_PITCH = WORK_CHUNK + 4;  // staged rows padded: the rows one read touches hit distinct banks
+constexpr int SC_TAIL = SC_UNIT;  // floats after the last row: a step reads (and drops) up to these past a unit's end
 
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
-// Stencil weight polynomial of offset component oo: w = a + b f + c f^2,
-// w0 = (3/2 - f)^2 / 2, w1 = 3/4 - (f - 1)^2, w2 = (f - 1/2)^2 / 2.
-__device__ __forceinline__ void sc_coef(int oo, float &a, float &b, float &c) {
-  if (oo == 0) { a = 1.125f; b = -1.5f; c = 0.5f; }
-  else if (oo == 1) { a = -0.25f; b = 2.0f; c = -1.0f; }
-  else { a = 0.125f; b = -0.5f; c = 0.5f; }
-}
-
 // Per-lane constants of the MFMA 16x16x4 roles: r16 = row of the feature
 // operand / column (offset within a 16-wide tile) of the weight operand,
-// kq = particle slot of the step.
+// kq = particle slot of the step.  MASS: the features have a mass row.
 struct ScLane {
-  int kq, feat;
+  int kq;
+  int at_f;                // element of the lane's feature row, slot kq
+  int at_x[2], at_yz[2];   // elements of its columns' weight rows, slot kq
   int oo[2], onode[2];
-  float cfa[2][3], cfb[2][3], cfc[2][3], fo[2][3];
+  float fo[2][3];
 };
 
+template <bool MASS>
 __device__ __forceinline__ ScLane sc_lane(int lane) {
   ScLane L;
   const int r16 = lane & 15;
@@ -55,7 +61,9 @@ __device__ __forceinline__ ScLane sc_lane(int lane) {
   // staged feature of operand row r16, grouped so that result rows 4 kq ..
   // 4 kq + 3 (held by lane group kq) all feed node value kq:
   //   rows 0-3: m, -, -, -;  rows 4 + 4d .. 7 + 4d: q_d, A_d0, A_d1, A_d2
-  L.feat = r16 == 0 ? 0 : (r16 < 4 ? -1 : ((r16 & 3) == 0 ? (r16 >> 2) : 4 + 3 * ((r16 >> 2) - 1) + (r16 & 3) - 1));
+  // (rows without a feature repeat the first one; group 0 drops them below)
+  const int feat = r16 < 4 ? 0 : ((r16 & 3) == 0 ? (r16 >> 2) : 4 + 3 * ((r16 >> 2) - 1) + (r16 & 3) - 1);
+  L.at_f = (MASS || feat == 0 ? feat : feat - 1) * SC_PITCH + L.kq;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int o = t * 16 + r16;
@@ -63,12 +71,11 @@ __device__ __forceinline__ ScLane sc_lane(int lane) {
     const int oc = o < 27 ? o : 0;
     const int ox = oc % 3, oy = (oc / 3) % 3, oz = oc / 9;
     L.onode[t] = ox + SC_L * (oy + SC_L * oz);
-    sc_coef(ox, L.cfa[t][0], L.cfb[t][0], L.cfc[t][0]);
-    sc_coef(oy, L.cfa[t][1], L.cfb[t][1], L.cfc[t][1]);
-    sc_coef(oz, L.cfa[t][2], L.cfb[t][2], L.cfc[t][2]);
-    L.fo[t][0] = (float)ox;
-    L.fo[t][1] = (float)oy;
-    L.fo[t][2] = (float)oz;
+    L.at_x[t] = ox * SC_PITCH + L.kq;
+    L.at_yz[t] = (3 + oc / 3) * SC_PITCH + L.kq;
+    L.fo[t][0] = L.kq ? (float)ox : 0.f;
+    L.fo[t][1] = L.kq ? (float)oy : 0.f;
+    L.fo[t][2] = L.kq ? (float)oz : 0.f;
   }
   return L;
 }
@@ -98,8 +105,8 @@ __device__ __forceinline__ int sc_wave_scan(int v) {
 // Wave 0: exclusive scan of the 64 cell counts into s_off / s_cur and the
 // unit descriptors (first slot | count << 10 | node base << 17).  The units
 // are listed whole ones first, then the partial ones (each cell's last) by
-// decreasing length, so that the two units a wave takes at a time have
-// nearly the same length and the matrix core idles less on the shorter.
+// decreasing number of four-particle steps, so that the two units a wave takes
+// at a time mostly have as many.
 // The order depends only on the counts.
 __device__ __forceinline__ void sc_scan_units(int lane, const int *s_cnt, int *s_off, int *s_cur, int *s_udesc,
                                               int *s_nunits) {
@@ -114,39 +121,60 @@ __device__ __forceinline__ void sc_scan_units(int lane, const int *s_cnt, int *s
   for (int q = 0; q < nf; ++q) s_udesc[finc - nf + q] = (inc - v + q * SC_UNIT) | (SC_UNIT << 10) | (nbase << 17);
   const uint64_t below = (1ull << lane) - 1ull;
   int pos = nfull;
-  for (int len = SC_UNIT - 1; len > 0; --len) {
-    const uint64_t m = __ballot(pl == len);
-    if (pl == len) s_udesc[pos + __popcll(m & below)] = (inc - v + nf * SC_UNIT) | (len << 10) | (nbase << 17);
+#pragma unroll
+  for (int steps = SC_UNIT / 4; steps > 0; --steps) {
+    const uint64_t m = __ballot((pl + 3) / 4 == steps);
+    if ((pl + 3) / 4 == steps)
+      s_udesc[pos + __popcll(m & below)] = (inc - v + nf * SC_UNIT) | (pl << 10) | (nbase << 17);
     pos += __popcll(m);
   }
   if (lane == 63) *s_nunits = pos;
 }
 
-// Stage one particle at `slot`: f, then m, q, A (A row-major).
-__device__ __forceinline__ void sc_stage(float (*s_dat)[SC_PITCH], float4 *s_f, int slot, const float f[3], float m,
+// Stage one particle at `slot`: its weights and features (A row-major).
+template <bool MASS>
+__device__ __forceinline__ void sc_stage(float *s_dat, float *s_wgt, int slot, const float f[3], float m,
                                          const float q[3], const float A[9]) {
-  s_f[slot] = make_float4(f[0], f[1], f[2], 0.f);
-  s_dat[0][slot] = m;
-  s_dat[1][slot] = q[0];
-  s_dat[2][slot] = q[1];
-  s_dat[3][slot] = q[2];
+  float w[3][3];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) s_dat[4 + k][slot] = A[k];
+  for (int a = 0; a < 3; ++a) bspline_w(f[a], w[a]);
+#pragma unroll
+  for (int o = 0; o < 3; ++o) {
+    s_wgt[o * SC_PITCH + slot] = w[0][o];
+#pragma unroll
+    for (int oy = 0; oy < 3; ++oy) s_wgt[(3 + oy + 3 * o) * SC_PITCH + slot] = w[1][oy] * w[2][o];
+  }
+  float *d = s_dat + slot;
+  if (MASS) {
+    *d = m;
+    d += SC_PITCH;
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) d[k * SC_PITCH] = q[k];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) d[(3 + k) * SC_PITCH] = A[k];
 }
 
 // Pass over the units on the matrix cores; wave `wid` adds into wnode.
 // Two adjacent units of the list (nearly equal lengths) per wave at a time.
-__device__ __forceinline__ void sc_units_mfma(const ScLane &L, int wid, const float (*s_dat)[SC_PITCH],
-                                              const float4 *s_f, const int *s_udesc, int nunits, float (*wnode)[4]) {
+__device__ __forceinline__ void sc_units_mfma(const ScLane &L, int wid, const float *s_dat, const float *s_wgt,
+                                              const int *s_udesc, int nunits, float (*wnode)[4]) {
   for (int u = 2 * wid; u < nunits; u += 2 * SC_WAVES) {
-    int k0[2], kn[2], cb[2];
+    int kn[2], cb[2];
+    const float *pf[2], *px[2][2], *py[2][2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       const int ue = u + e;
-      const int d = ue < nunits ? s_udesc[ue] : 0;
-      k0[e] = d & 1023;
+      const int d = __builtin_amdgcn_readfirstlane(ue < nunits ? s_udesc[ue] : 0);
+      const int k0 = d & 1023;
       kn[e] = (d >> 10) & 127;
       cb[e] = d >> 17;
+      pf[e] = s_dat + L.at_f + k0;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        px[e][t] = s_wgt + L.at_x[t] + k0;
+        py[e][t] = s_wgt + L.at_yz[t] + k0;
+      }
     }
     floatx4_t acc[2][2];
 #pragma unroll
@@ -154,44 +182,50 @@ __device__ __forceinline__ void sc_units_mfma(const ScLane &L, int wid, const fl
 #pragma unroll
       for (int t = 0; t < 2; ++t) acc[e][t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
     const int len = max(kn[0], kn[1]);
-    for (int kk = 0; kk < len; kk += 4) {
-      // LDS reads of both units' next four particles first
-      float f3[2][3], av[2];
-      bool live[2];
+#pragma unroll
+    for (int kk = 0; kk < SC_UNIT; kk += 4) {
+      if (kk >= len) break;
+      float av[2], w[2][2];
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
-        const int r = kk + L.kq;
-        live[e] = r < kn[e];
-        const int jj = k0[e] + (live[e] ? r : 0);
-        const float4 fv = s_f[jj];
-        f3[e][0] = fv.x;
-        f3[e][1] = fv.y;
-        f3[e][2] = fv.z;
-        av[e] = (live[e] && L.feat >= 0) ? s_dat[L.feat < 0 ? 0 : L.feat][jj] : 0.f;
+        av[e] = pf[e][kk];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) w[e][t] = px[e][t][kk] * py[e][t][kk];
       }
+      // slots past a unit's end hold other particles or nothing: both
+      // operands zero there
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+        if (kn[e] < kk + 4) {
+          const bool live = L.kq < kn[e] - kk;
+          av[e] = live ? av[e] : 0.f;
+          w[e][0] = live ? w[e][0] : 0.f;
+          w[e][1] = live ? w[e][1] : 0.f;
+        }
 #pragma unroll
       for (int e = 0; e < 2; ++e)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          // no mask on w: a padding particle's feature operand is zero, a
-          // padding column (offset >= 27) is dropped below, and w is finite
-          // for both (f of a staged particle, the coefficients of offset 0)
-          float w = 1.f;
-#pragma unroll
-          for (int d = 0; d < 3; ++d) w *= L.cfa[t][d] + f3[e][d] * (L.cfb[t][d] + L.cfc[t][d] * f3[e][d]);
-          acc[e][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], w, acc[e][t], 0, 0, 0);
-        }
+        for (int t = 0; t < 2; ++t)
+          acc[e][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], w[e][t], acc[e][t], 0, 0, 0);
     }
     // lane (kq, r16) holds rows 4 kq + i of column r16 (offset o) of each
-    // tile: node value kq of node cell + o is row 4 kq + (1, ox, oy, oz).
+    // tile: node value kq of node cell + o is row 4 kq + (1, ox, oy, oz).  A
+    // unit's nodes are distinct, so both tiles' old values are read before
+    // either is written.
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       if (kn[e] == 0) continue;
+      float *p[2], old[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        p[t] = &wnode[cb[e] + L.onode[t]][L.kq];
+        old[t] = *p[t];
+      }
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const floatx4_t a4 = acc[e][t];
         const float v = a4[0] + L.fo[t][0] * a4[1] + L.fo[t][1] * a4[2] + L.fo[t][2] * a4[3];
-        if (L.oo[t] < 27) wnode[cb[e] + L.onode[t]][L.kq] += v;
+        if (L.oo[t] < 27) *p[t] = old[t] + v;
       }
     }
   }

@@ -298,7 +298,7 @@ constexpr int P2G_PER_CU = 1024 / P2G_THREADS;  // resident workgroups per compu
 // Pass B: exclusive scan of the 64 cell counts; cells cut into units.
 // Pass A2: the thread computes the stress (the polar decomposition), the
 //   MLS affine matrix A and the momentum and stages, at its particle's slot
-//   in cell order, f, m, q = m v - A f dx and A dx.
+//   in cell order, the weights, m, q = m v - A f dx and A dx.
 // Pass C: the units on the matrix cores into per-wave node blocks (the tile
 //   scatter of dw_scatter.h).
 // Pass D: the thread owning node n of the 6^3 region adds the 8 wave blocks
@@ -311,8 +311,8 @@ __global__ __launch_bounds__(P2G_THREADS) __attribute__((amdgpu_waves_per_eu(4))
     const int32_t *__restrict__ item_begin, const int32_t *__restrict__ n_items, float *__restrict__ gm,
     float *__restrict__ gmv, int64_t N, int32_t *__restrict__ status, float *__restrict__ item_part) {
   static_assert(WORK_CHUNK == P2G_THREADS, "one staged particle per thread");
-  __shared__ float s_dat[SC_DAT][SC_PITCH];                       // staged particles in cell order
-  __shared__ float4 s_f[SC_PITCH];                                  // staged f per particle
+  __shared__ float s_dat[SC_DAT * SC_PITCH + SC_TAIL];  // staged features in cell order
+  __shared__ float s_wgt[SC_WGT * SC_PITCH + SC_TAIL];  // and weights
   __shared__ __attribute__((aligned(16))) float s_node[SC_WAVES][SC_NODES][4];  // per-wave node sums
   __shared__ int s_cnt[64], s_off[64], s_cur[64];
   __shared__ int s_udesc[SC_MAX_UNITS];
@@ -322,17 +322,19 @@ __global__ __launch_bounds__(P2G_THREADS) __attribute__((amdgpu_waves_per_eu(4))
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const float kstress = dt * 4.0f * g.inv_dx * g.inv_dx;
   const float dx = g.dx;
-  const ScLane L = sc_lane(lane);
+  const ScLane L = sc_lane<true>(lane);
   float *s_node_flat = &s_node[0][0][0];
   const int ni = *n_items;
   // Workgroup b takes items b, b + gridDim.x, ... of the whole rounds but the
   // last two; the items left are handed out by a ticket counter, which evens
-  // out the end.  The counter serves one draw every 13 ns, so a launch pays
-  // for each: with all items drawn and every workgroup counted out through
-  // it, 19.6 / 35.6 / 56.1 / 254 us for 20k / 146k / 500k / 4M particles, this
-  // way 12.7 / 23.9 / 44.7 / 247.  Header word 8 is zeroed by k_grid_clear
-  // before each launch, word 9 (deterministic mode, which has no clear) by
-  // the sort and by the gather after each launch.
+  // out the end (none drawn: 27 against 23.5 us at 256k particles, 251 against
+  // 241 at 4M).  The counter serves one draw every 13 ns, so a launch pays for
+  // each: all items drawn and every workgroup counted out through it cost 7,
+  // 12, 11 and 8 us more at 20k, 146k, 500k and 4M particles.  Header word 8 is
+  // zeroed by k_grid_clear before each launch, word 9 (deterministic mode,
+  // which has no clear) by the sort and by the gather after each launch.
+  // (Loading the next item's particles during the matrix phase shortened the
+  // loads' wait to an eighth and lengthened that phase by as much.)
   int32_t *ticket = status + (DET ? 9 : 8);
   const int nwg = (int)gridDim.x, nstat = ni <= nwg ? ni : max(1, ni / nwg - 2) * nwg;  // items of the static rounds
   for (int it = blockIdx.x; it < ni; it = s_next) {
@@ -410,7 +412,7 @@ __global__ __launch_bounds__(P2G_THREADS) __attribute__((amdgpu_waves_per_eu(4))
       const float qv[3] = {m * vx - (A[0] * f[0] + A[1] * f[1] + A[2] * f[2]),
                            m * vy - (A[3] * f[0] + A[4] * f[1] + A[5] * f[2]),
                            m * vz - (A[6] * f[0] + A[7] * f[1] + A[8] * f[2])};
-      sc_stage(s_dat, s_f, slot, f, m, qv, A);
+      sc_stage<true>(s_dat, s_wgt, slot, f, m, qv, A);
     }
     __syncthreads();
     // pass C; the next ticket is drawn before it and stored after it, so the
@@ -418,7 +420,7 @@ __global__ __launch_bounds__(P2G_THREADS) __attribute__((amdgpu_waves_per_eu(4))
     int tk = 0;
     const bool draw = it + nwg >= nstat && nstat < ni;
     if (draw && tid == P2G_THREADS - 1) tk = atomicAdd(ticket, 1);
-    sc_units_mfma(L, wid, s_dat, s_f, s_udesc, s_nunits, s_node[wid]);
+    sc_units_mfma(L, wid, s_dat, s_wgt, s_udesc, s_nunits, s_node[wid]);
     if (tid == P2G_THREADS - 1) s_next = draw ? nstat + tk : it + nwg;
     __syncthreads();
     // pass D: node owners add the wave blocks in a fixed order

@@ -15,7 +15,6 @@
 
 #include <algorithm>
 #include <climits>
-#include <type_traits>
 
 #include "dw_internal.h"
 #include "dw_kernels.h"
@@ -135,16 +134,6 @@ __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
-}
-
-// Component q of a [rows][n] particle array at byte offset off = 4 p: a scalar
-// base and a 32-bit offset, so the many arrays take no vector address pairs
-// (n is below 2^31 / 9, the largest F index held in an int).
-template <typename T>
-__device__ __forceinline__ __attribute__((address_space(1))) T &at_particle(T *base, int q, int n, uint32_t off) {
-  uint64_t row = reinterpret_cast<uint64_t>(base + (size_t)q * n);
-  asm("" : "+s"(row));  // kept scalar
-  return *((__attribute__((address_space(1))) T *)row + (off >> 2));
 }
 
 struct PAdj {
@@ -629,10 +618,10 @@ __global__ __launch_bounds__(256) void k_grid_update_adj(GridDev g, float dt, fl
 // to item_part instead, which k_det_gather<true> then adds to the grid
 // adjoint in a fixed order (bit-reproducible with a deterministic sort).
 // An item is a chain of phases with two workgroups per CU to overlap them
-// (128 registers, 66 KB of LDS): the particle is loaded in one round trip
+// (128 registers, 80 KB of LDS): the particle is loaded in one round trip
 // ahead of the slot scan, one gather replaces two (v_p itself is not needed),
-// and the row sums factor.  256k particles (735 items) 60 -> 45 us, 20k 23.3
-// -> 19.
+// and the row sums factor.  256k particles (735 items) 60 -> 41 us, 20k 23.3
+// -> 15.5.
 template <bool DET>
 __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_g2p_adj(
     GridDev g, float dt, const float *__restrict__ gv, int64_t N, const float *__restrict__ x,
@@ -641,9 +630,9 @@ __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
     float *__restrict__ gvb, const int32_t *__restrict__ perm, const int32_t *__restrict__ tile_start,
     const int32_t *__restrict__ item_tile, const int32_t *__restrict__ item_begin,
     const int32_t *__restrict__ n_items, float *__restrict__ item_part, int fresh) {
-  __shared__ float s_dat[SC_DAT][SC_PITCH];
+  __shared__ float s_dat[(SC_DAT - 1) * SC_PITCH + SC_TAIL];  // staged features in cell order
+  __shared__ float s_wgt[SC_WGT * SC_PITCH + SC_TAIL];  // and weights
   __shared__ unsigned char s_cell[WORK_CHUNK];
-  __shared__ float4 s_f[SC_PITCH];                                  // staged f per particle
   __shared__ __attribute__((aligned(16))) float s_node[SC_WAVES][SC_NODES][4];
   __shared__ int s_cnt[64], s_off[64], s_cur[64];
   __shared__ int s_udesc[SC_MAX_UNITS];
@@ -767,7 +756,7 @@ __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
       for (int q = 0; q < 9; ++q) A[q] = kc * Cbt[q];
 #pragma unroll
       for (int a = 0; a < 3; ++a) qv[a] = vbt[a] - (A[3 * a] * f[0] + A[3 * a + 1] * f[1] + A[3 * a + 2] * f[2]);
-      sc_stage(s_dat, s_f, slot, f, 0.f, qv, A);
+      sc_stage<false>(s_dat, s_wgt, slot, f, 0.f, qv, A);
       // One gather of the stencil's grid velocities v_i gives both C_p = kc
       // sum w v (o - f)^T and the gradient of the gather through the weights
       // and the offsets, x_bar += gw s - (w / dx) A^T v with s = v . (vbt + A (o - f))
@@ -849,8 +838,8 @@ __global__ __launch_bounds__(SC_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
     __syncthreads();
     int lane_now = lane;
     asm("" : "+v"(lane_now));  // likewise the 30 constants of sc_lane
-    const ScLane L = sc_lane(lane_now);
-    sc_units_mfma(L, wid, s_dat, s_f, s_udesc, s_nunits, s_node[wid]);
+    const ScLane L = sc_lane<false>(lane_now);
+    sc_units_mfma(L, wid, s_dat, s_wgt, s_udesc, s_nunits, s_node[wid]);
     __syncthreads();
     int node_now = tid;
     asm("" : "+v"(node_now));  // likewise
