@@ -100,7 +100,12 @@ int run_grid_update_adj_fused(const dw_grid *grid, const dw_mpm_params *params, 
                               void *stream);
 int run_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, const dw_particles *p, const float *grid_m_bar,
                 const float *grid_mv_bar, dw_particles_bar *bar, float *E_bar, void *ws, size_t ws_bytes, void *stream,
-                int fresh);
+                int fresh, float *e_slots);
+// E adjoint over several reverse P2Gs: with e_slots (zeroed, e_slot_floats
+// floats) each workgroup of run_p2g_adj adds to its own row instead of E_bar
+// (float atomics only); run_e_slots adds the rows into E_bar.
+int64_t e_slot_floats(const dw_particles *p);
+int run_e_slots(const dw_particles *p, const float *e_slots, float *E_bar, void *stream);
 
 // fill kernels (a kernel rather than hipMemsetAsync, so the calls stay
 // capturable in HIP graphs); static: every translation unit launches its own

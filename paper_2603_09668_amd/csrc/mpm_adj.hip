@@ -144,6 +144,7 @@ struct PAdj {
   float *xb, *vb, *Cb, *Fb, *Eb;
   float *Epart;     // deterministic mode: per-wave region sums [waves][n_regions]
   int fresh;        // vb and Cb hold nothing yet: written, not added to
+  int slots;        // Eb is [workgroups][n_regions]: each workgroup adds to its own row
 };
 
 // ---------------------------------------------------------- reverse P2G
@@ -155,8 +156,10 @@ struct PAdj {
 // z-layer at once, the old adjoints at once (one += after the other costs a
 // round trip each); H and R - I wait in LDS meanwhile, which spares a second
 // polar decomposition, and E_bar takes one atomic per workgroup (one per wave
-// took 52 us of 4,000 waves).  256k particles 65 -> 34 us (77 MB of particle
-// data: 15 us), 20k 19.7 -> 15.5.
+// took 52 us of 4,000 waves), or none: a rollout gives each workgroup a row of
+// its own and adds the rows in double, which also brings the E adjoint of 20k
+// particles from 1e-6 of the exact one to 1e-7.  256k particles 65 -> 35 us,
+// with rows 30 (77 MB of particle data: 15 us), 20k 19.7 -> 14.5.
 // DET: the E adjoint is not added with atomics; every wave writes its
 // per-region sums (fixed-order wave reductions) to P.Epart and
 // k_ebar_reduce adds the waves in index order.
@@ -170,6 +173,7 @@ __global__ __launch_bounds__(P2G_ADJ_THREADS) __attribute__((amdgpu_waves_per_eu
   extern __shared__ float s_keep_all[];
   float *s_keep = s_keep_all + (threadIdx.x >> 6) * (18 * 64) + (threadIdx.x & 63);
   const int n = P.n;
+  float *const Eb = P.slots ? P.Eb + (size_t)blockIdx.x * P.n_regions : P.Eb;
   int run_reg = -1;      // region of the wave's running E sum (float atomics)
   float run_sum = 0.f;
   for (int p = blockIdx.x * blockDim.x + threadIdx.x; (p & ~63) < n; p += gridDim.x * blockDim.x) {
@@ -367,7 +371,7 @@ __global__ __launch_bounds__(P2G_ADJ_THREADS) __attribute__((amdgpu_waves_per_eu
       unsigned long long pending = __ballot(live);
       const int lane = threadIdx.x & 63;
       if (!__ballot(live && r == run_reg)) {
-        if (run_reg >= 0 && lane == 0 && run_sum != 0.f) atomicAdd(&P.Eb[run_reg], run_sum);
+        if (run_reg >= 0 && lane == 0 && run_sum != 0.f) atomicAdd(&Eb[run_reg], run_sum);
         run_reg = __builtin_amdgcn_readfirstlane(r);  // lane 0 of the loop is live
         run_sum = 0.f;
       }
@@ -377,7 +381,7 @@ __global__ __launch_bounds__(P2G_ADJ_THREADS) __attribute__((amdgpu_waves_per_eu
         const bool mine = live && r == rk;
         const float sum = wave_sum(mine ? Ebar_p : 0.f);
         if (rk == run_reg) run_sum += sum;
-        else if (lane == leader && sum != 0.f) atomicAdd(&P.Eb[rk], sum);
+        else if (lane == leader && sum != 0.f) atomicAdd(&Eb[rk], sum);
         pending &= ~__ballot(mine);
       }
     }
@@ -401,7 +405,7 @@ __global__ __launch_bounds__(P2G_ADJ_THREADS) __attribute__((amdgpu_waves_per_eu
         lead = lead && w >= (int)threadIdx.x;
         sum += s_sum[w];
       }
-      if (lead && sum != 0.f) atomicAdd(&P.Eb[rk], sum);
+      if (lead && sum != 0.f) atomicAdd(&Eb[rk], sum);
     }
   }
 }
@@ -413,6 +417,23 @@ static int p2g_adj_threads(int n) {
   int t = 64;
   while (t < P2G_ADJ_THREADS && (int64_t)n >= (int64_t)2 * t * cu_count()) t *= 2;
   return t;
+}
+
+// ... and how many: at most as many as fit at once, four waves per SIMD
+static unsigned p2g_adj_blocks(int n) {
+  const int threads = p2g_adj_threads(n);
+  return std::min(grid_blocks(n, threads), (unsigned)(1024 / threads * cu_count()));
+}
+
+// E_bar += the column sums of the workgroups' rows, one wave per region, in
+// double: hundreds of float additions into a sum whose terms cancel lose more
+// than the terms do
+__global__ __launch_bounds__(64) void k_e_slots(const float *__restrict__ slots, int rows, int R,
+                                                float *__restrict__ Eb) {
+  double t = 0.0;
+  for (int b = threadIdx.x; b < rows; b += 64) t += (double)slots[(size_t)b * R + blockIdx.x];
+  for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+  if (threadIdx.x == 0) Eb[blockIdx.x] += (float)t;
 }
 
 // E adjoint of the deterministic reverse P2G: region r adds the per-wave sums
@@ -876,7 +897,7 @@ using namespace dw;
 
 int dw::run_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, const dw_particles *p, const float *grid_m_bar,
                     const float *grid_mv_bar, dw_particles_bar *bar, float *E_bar, void *ws, size_t ws_bytes,
-                    void *stream, int fresh) {
+                    void *stream, int fresh, float *e_slots) {
   int rc = check_grid(grid);
   if (rc) return rc;
   DW_REQUIRE(params, DW_EINVAL, "mpm_p2g_adj: params is NULL");
@@ -894,6 +915,7 @@ int dw::run_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, const dw_p
   P.n_regions = p->n_regions;
   P.Epart = nullptr;
   P.fresh = fresh;
+  P.slots = 0;
   GridDev g = make_grid(grid);
   int64_t N = (int64_t)grid->nx * grid->ny * grid->nz;
   hipStream_t s = (hipStream_t)stream;
@@ -912,18 +934,28 @@ int dw::run_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, const dw_p
                        ((int64_t)p->n + 63) / 64, p->n_regions, E_bar);
   } else {
     const int threads = p2g_adj_threads(p->n);
-    // at most the workgroups that fit at once: four waves per SIMD
-    const unsigned blocks = std::min(grid_blocks(p->n, threads), (unsigned)(1024 / threads * cu_count()));
-    hipLaunchKernelGGL(k_p2g_adj<false>, dim3(blocks), dim3(threads), 18 * threads * sizeof(float), s, g, P,
+    if (e_slots) {
+      P.Eb = e_slots;
+      P.slots = 1;
+    }
+    hipLaunchKernelGGL(k_p2g_adj<false>, dim3(p2g_adj_blocks(p->n)), dim3(threads), 18 * threads * sizeof(float), s, g, P,
                        params->dt, params->material, grid_m_bar, grid_mv_bar, N);
   }
+  return check_launch("mpm_p2g_adj");
+}
+
+int64_t dw::e_slot_floats(const dw_particles *p) { return (int64_t)p2g_adj_blocks(p->n) * p->n_regions; }
+
+int dw::run_e_slots(const dw_particles *p, const float *e_slots, float *E_bar, void *stream) {
+  hipLaunchKernelGGL(k_e_slots, dim3(p->n_regions), dim3(64), 0, (hipStream_t)stream, e_slots,
+                     (int)p2g_adj_blocks(p->n), p->n_regions, E_bar);
   return check_launch("mpm_p2g_adj");
 }
 
 extern "C" int mpm_p2g_adj(const dw_grid *grid, const dw_mpm_params *params, const dw_particles *p,
                            const float *grid_m_bar, const float *grid_mv_bar, dw_particles_bar *bar, float *E_bar,
                            void *ws, size_t ws_bytes, void *stream) {
-  return dw::run_p2g_adj(grid, params, p, grid_m_bar, grid_mv_bar, bar, E_bar, ws, ws_bytes, stream, 0);
+  return dw::run_p2g_adj(grid, params, p, grid_m_bar, grid_mv_bar, bar, E_bar, ws, ws_bytes, stream, 0, nullptr);
 }
 
 // W_bar given: the fused form (grid_v_bar is then cleared on the active tiles)

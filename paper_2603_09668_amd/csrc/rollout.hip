@@ -96,6 +96,13 @@ extern "C" int mpm_rollout_adj(const dw_grid *grid, const dw_mpm_params *params,
   // the deterministic transpose gathers over all nodes, so it needs accb and a
   // clear of all ten arrays per substep
   const bool fused = !wind->deterministic;
+  // accb is free in the fused form: the workgroups' rows of the E adjoint,
+  // added up once per segment
+  const int64_t n_slots = p->n > 0 ? e_slot_floats(p) : 0;
+  float *e_slots = fused && !params->deterministic && n_slots > 0 && n_slots <= 3 * N ? accb : nullptr;
+  if (e_slots && seg->count > 0)
+    hipLaunchKernelGGL(k_fill_i32, dim3(grid_blocks(n_slots / 4 + 4, 256)), dim3(256), 0, s, (int32_t *)e_slots,
+                       n_slots, 0);
   for (int i = seg->count - 1; i >= 0; --i, cur ^= 1) {
     const float *gm = seg->grids + i * seg->grid_stride, *gmv = gm + N, *gv = gmv + 3 * N;
     char *ws = (char *)seg->ws + i * seg->ws_stride;
@@ -119,7 +126,9 @@ extern "C" int mpm_rollout_adj(const dw_grid *grid, const dw_mpm_params *params,
         return rc;
       if ((rc = wind_to_grid_adj(grid, &w, accb, Wb, stream))) return rc;
     }
-    if ((rc = run_p2g_adj(grid, params, &in, gmb, gmvb, &to, E_bar, ws, seg->ws_bytes, stream, 1))) return rc;
+    if ((rc = run_p2g_adj(grid, params, &in, gmb, gmvb, &to, E_bar, ws, seg->ws_bytes, stream, 1, e_slots)))
+      return rc;
   }
+  if (e_slots && seg->count > 0) return run_e_slots(p, e_slots, E_bar, stream);
   return DW_OK;
 }

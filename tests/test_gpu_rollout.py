@@ -130,15 +130,16 @@ def test_rollout_deterministic_gradient_is_bit_reproducible():
     assert eW < 1e-3 and eE < 1e-3
 
 
-@pytest.mark.parametrize("res,nw,ckpt,n_sub,K,det", [(16, 4, 4, 12, 2, False), (18, 5, 5, 7, 3, False),
-                                                     (16, 24, 3, 6, 1, False), (22, 2, 1, 3, 5, False),
-                                                     (18, 5, 4, 6, 2, True)])
-def test_rollout_loop_matches_single_calls(res, nw, ckpt, n_sub, K, det):
+@pytest.mark.parametrize("res,nw,ckpt,n_sub,K,det,R", [(16, 4, 4, 12, 2, False, 2), (18, 5, 5, 7, 3, False, 2),
+                                                       (16, 24, 3, 6, 1, False, 70), (22, 2, 1, 3, 5, False, 2),
+                                                       (16, 4, 3, 4, 1, False, 900), (18, 5, 4, 6, 2, True, 2)])
+def test_rollout_loop_matches_single_calls(res, nw, ckpt, n_sub, K, det, R):
     """The rollout's substep loops against the entry points called one by one
     (RolloutPlan.substep and substep_adjoint): wind grids coarser and finer than
     the simulation grid (more wind cells per node tile than are summed in the
-    wave), grids with partial tiles, ragged and single-substep segments.  The
-    same products summed in another order: 1e-5; equal in the deterministic mode."""
+    wave), grids with partial tiles, ragged and single-substep segments, and
+    more regions than the E adjoint's rows have room for (900).  The same
+    products summed in another order: 1e-5; equal in the deterministic mode."""
     say(f"rollout loop res={res} nw={nw} ckpt={ckpt} n_sub={n_sub} K={K} det={det}")
     rng = np.random.default_rng(res + nw)
     n = 900
@@ -146,8 +147,8 @@ def test_rollout_loop_matches_single_calls(res, nw, ckpt, n_sub, K, det):
     x0 = torch.as_tensor(0.3 + 0.4 * rng.random((3, n))).float().to(DEV)
     v0 = torch.as_tensor(0.1 * rng.standard_normal((3, n))).float().to(DEV)
     z9 = torch.zeros(9, n, **dev)
-    E, nu = torch.tensor([30.0, 60.0], **dev), torch.tensor([0.3, 0.25], **dev)
-    region = torch.as_tensor(rng.integers(0, 2, n)).to(torch.int32).to(DEV)
+    E, nu = torch.linspace(30.0, 60.0, R, **dev), torch.linspace(0.3, 0.25, R, **dev)
+    region = torch.as_tensor(rng.integers(0, R, n)).to(torch.int32).to(DEV)
     W = torch.as_tensor(2.0 * rng.standard_normal((K, 3, nw ** 3))).float().to(DEV)
     pin = torch.as_tensor(rng.random(res ** 3) < 0.05).to(torch.uint8).to(DEV)
     plan = RolloutPlan(dict(nx=res, ny=res, nz=res, dx=1.0 / res, origin=(0.0, 0.0, 0.0)), n, torch.full((n,), 1.0 / n, **dev),
