@@ -332,8 +332,8 @@ typedef struct {
 
 /* Forward substeps (mpm_sort, mpm_p2g, mpm_grid_update, mpm_g2p) from the
  * state in p.  With seg->states NULL the state goes to `out` (which may be p's
- * own arrays); else substep i writes seg->states + 24 n i (x, v, C, F packed),
- * the last substep ends after its grid update, and out is not used.
+ * own arrays); else substep i writes seg->states + 24 n i (x, v, C, F packed)
+ * and the last one `out`, or, with out NULL, ends after its grid update.
  * status_or (device int32 or NULL): the workspace status words are OR-ed in. */
 int mpm_rollout(const dw_grid *grid, const dw_mpm_params *params, const dw_particles *p,
                 const dw_particles_bar *out, const dw_wind *wind, const uint8_t *pin,

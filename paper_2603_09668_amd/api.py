@@ -432,7 +432,7 @@ def rollout_segment(first, count, n_sub, slots, slot_stride, grids, ws, states=N
 
 
 def mpm_rollout(grid: Grid, params: MPMParams, p: ParticleArrays, out, wind: Wind, pin, seg: Segment, status_or=None):
-    """Forward substeps of seg; out = (x, v, C, F), or None with kept states."""
+    """Forward substeps of seg; out = (x, v, C, F), with kept states or None."""
     ps = p.struct()
     po = _bar_struct(p.n, *out) if out is not None else None
     _check(lib().mpm_rollout(ctypes.byref(grid), ctypes.byref(params), ctypes.byref(ps),

@@ -11,8 +11,9 @@ Memory: the forward keeps the particle state every `ckpt` substeps only.  The
 backward walks the segments in reverse; for each it re-runs the segment from
 its checkpoint, keeping every substep's particle state, sort workspace and
 grid (m, mv, v: about 28 B per grid node and 20 B per particle per substep),
-then for every substep (last first) applies the adjoints in reverse order:
-G2P adjoint (sorted scatter into the grid adjoint), grid-update adjoint with
+then for every substep (last first) applies the adjoints in reverse order
+(the last segment is kept by the forward and re-run only if another rollout
+of the plan has used its store since): G2P adjoint (sorted scatter into the grid adjoint), grid-update adjoint with
 the wind transpose into W_bar, P2G adjoint (per-particle gather, also giving
 E_bar).  The substep loops run in the library (mpm_rollout, mpm_rollout_adj);
 torch provides device memory and the final loss.
@@ -63,22 +64,31 @@ class RolloutPlan:
         self._gbar = torch.zeros(10, self.N, **f)
         self.gvb, self.gmb, self.gmvb, self.accb = (self._gbar[0:3], self._gbar[3], self._gbar[4:7],
                                                     self._gbar[7:10])
-        self._seg = None  # workspaces and grids of a segment's substeps, made on first backward
+        self._seg = None  # store of a segment's substeps, made when a gradient is first asked for
+        self._seg_views = None  # segment_buffers' own
+        self._kept = None  # token of the rollout whose last segment is in the store
         self._status = torch.zeros(1, dtype=torch.int32, device=device)  # OR of the substeps' status words
 
     def _segment_store(self):
-        """Workspaces (ckpt, bytes) and grids (ckpt, 7, N) of a segment's substeps."""
+        """Workspaces (ckpt, bytes), grids (ckpt, 7, N) and states between the
+        substeps (ckpt - 1, 24 n) of a segment."""
         if self._seg is None:
+            f = dict(dtype=torch.float32, device=self.device)
             nb = self.ws.numel()
             ws = torch.empty(self.ckpt * nb + 256, dtype=torch.uint8, device=self.device)
             off = (-ws.data_ptr()) % 256
-            self._seg = (ws[off:off + self.ckpt * nb].view(self.ckpt, nb),
-                         torch.empty(self.ckpt, 7, self.N, dtype=torch.float32, device=self.device))
+            self._seg = (ws[off:off + self.ckpt * nb].view(self.ckpt, nb), torch.empty(self.ckpt, 7, self.N, **f),
+                         torch.empty(max(self.ckpt - 1, 1), 24 * self.n, **f))
         return self._seg
 
     def segment_buffers(self):
         """Sort workspaces and grids (m, mv, v) for the substeps of one segment."""
-        return [(ws, g[0], g[1:4], g[4:7]) for ws, g in zip(*self._segment_store())]
+        if self._seg_views is None:
+            f = dict(dtype=torch.float32, device=self.device)
+            self._seg_views = [(api.alloc_workspace(self.grid, self.n, self.device, deterministic=self.deterministic),
+                                torch.empty(self.N, **f), torch.empty(3, self.N, **f), torch.empty(3, self.N, **f))
+                               for _ in range(self.ckpt)]
+        return self._seg_views
 
     def slot(self, s: int) -> int:
         return s * self.K // self.n_sub
@@ -146,7 +156,7 @@ class RolloutPlan:
 
 class _RolloutFn(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, plan: RolloutPlan, W, E, x0, v0, C0, H0):
+    def forward(ctx, plan: RolloutPlan, keep: bool, W, E, x0, v0, C0, H0):
         W = W.detach().contiguous()
         E = E.detach().contiguous()
         state = [t.detach().clone() for t in (x0, v0, C0, H0)]
@@ -155,11 +165,18 @@ class _RolloutFn(torch.autograd.Function):
             # a segment leaves its first state as it is: that is the checkpoint
             ckpts.append(state)
             out = [torch.empty_like(t) for t in state]
-            seg = plan.segment(W, s0, plan._grids, plan.ws)
+            if keep and s0 + plan.ckpt >= plan.n_sub:
+                # the backward starts with this segment
+                plan._kept = None
+                ws, grids, states = plan._segment_store()
+                seg = plan.segment(W, s0, grids, ws, states)
+            else:
+                seg = plan.segment(W, s0, plan._grids, plan.ws)
             api.mpm_rollout(plan.grid, plan.prm, plan.particles(*state, E), out, plan.wind(W, 0), plan.pin, seg,
                             plan._status)
             state = out
         plan.check_status("forward")
+        ctx.kept = plan._kept = object() if keep and ckpts else None
         ctx.plan = plan
         ctx.ckpts = ckpts
         ctx.save_for_backward(W, E)
@@ -171,7 +188,9 @@ class _RolloutFn(torch.autograd.Function):
         W, E = ctx.saved_tensors
         W_bar = torch.zeros_like(W)
         E_bar = torch.zeros_like(E)
-        ws, grids = plan._segment_store()
+        ws, grids, states = plan._segment_store()
+        kept = ctx.kept is not None and plan._kept is ctx.kept
+        plan._kept = None
         # particle-state adjoints: two groups of packed (x, v, C, H)
         shapes = [t.shape for t in ctx.ckpts[0]]
         sizes = [t.numel() for t in ctx.ckpts[0]]
@@ -180,18 +199,18 @@ class _RolloutFn(torch.autograd.Function):
         cur = 0
         for dst, b in zip(groups[cur], (xb, vb, Cb, Hb)):
             dst.zero_() if b is None else dst.copy_(b)
-        states = torch.empty(max(plan.ckpt - 1, 1), sum(sizes), dtype=torch.float32, device=W.device)
         plan.gvb.zero_()  # and zero again after each substep
         wind = plan.wind(W, 0)
         for k in reversed(range(len(ctx.ckpts))):
             # re-run the segment, keeping each substep's state, sort and grid
             seg = plan.segment(W, k * plan.ckpt, grids, ws, states)
             p = plan.particles(*ctx.ckpts[k], E)
-            api.mpm_rollout(plan.grid, plan.prm, p, None, wind, plan.pin, seg, plan._status)
+            if not (kept and k == len(ctx.ckpts) - 1):
+                api.mpm_rollout(plan.grid, plan.prm, p, None, wind, plan.pin, seg, plan._status)
             api.mpm_rollout_adj(plan.grid, plan.prm, p, wind, plan.pin, seg, pair, cur, plan._gbar, W_bar, E_bar)
             cur ^= seg.count & 1
         plan.check_status("backward")
-        return (None, W_bar, E_bar, *[b.clone() for b in groups[cur]])
+        return (None, None, W_bar, E_bar, *[b.clone() for b in groups[cur]])
 
 
 def rollout(plan: RolloutPlan, W, E, x0, v0, C0, H0):
@@ -199,4 +218,5 @@ def rollout(plan: RolloutPlan, W, E, x0, v0, C0, H0):
     gradients flowing to W (K, 3, nw^3), E (n_regions,) and the initial state.
     With plan.xref set, x0 and the returned x are displacements from it.
     Raises DiffWindError if a particle left the grid."""
-    return _RolloutFn.apply(plan, W, E, x0, v0, C0, H0)
+    args = (W, E, x0, v0, C0, H0)
+    return _RolloutFn.apply(plan, torch.is_grad_enabled() and any(t.requires_grad for t in args), *args)

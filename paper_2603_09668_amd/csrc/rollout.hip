@@ -4,7 +4,9 @@
 // is a dozen kernels of a few microseconds, so the launches themselves bound
 // it; driving them from here instead of one binding call per entry point, and
 // with fewer kernels, took 20k particles, 16 substeps with their gradient,
-// from 3,500 to 2,130 us (256k particles: 4,640 to 3,860).
+// from 3,500 to 2,130 us (256k particles: 4,640 to 3,860), and a last segment
+// that the forward keeps for the reverse (seg->states with out) from 2,065 to
+// 1,840 (3,730 to 3,330).
 #include <hip/hip_runtime.h>
 
 #include "dw_internal.h"
@@ -54,7 +56,8 @@ extern "C" int mpm_rollout(const dw_grid *grid, const dw_mpm_params *params, con
                            const dw_segment *seg, int32_t *status_or, void *stream) {
   int rc = check_segment("mpm_rollout", grid, params, p, wind, seg);
   if (rc) return rc;
-  DW_REQUIRE(seg->states || (out && out->n == p->n && (p->n == 0 || (out->x && out->v && out->C && out->F))), DW_EINVAL,
+  DW_REQUIRE(seg->states || out, DW_EINVAL, "mpm_rollout: out is NULL");
+  DW_REQUIRE(!out || (out->n == p->n && (p->n == 0 || (out->x && out->v && out->C && out->F))), DW_EINVAL,
              "mpm_rollout: out must hold the particles");
   const int64_t N = (int64_t)grid->nx * grid->ny * grid->nz;
   dw_particles in = *p;
@@ -65,9 +68,10 @@ extern "C" int mpm_rollout(const dw_grid *grid, const dw_mpm_params *params, con
     if ((rc = mpm_sort(grid, params, in.x, in.xref, in.n, ws, seg->ws_bytes, stream))) return rc;
     if ((rc = mpm_p2g(grid, params, &in, gm, gmv, ws, seg->ws_bytes, stream))) return rc;
     if ((rc = run_grid_update(grid, params, gm, gmv, &w, pin, gv, ws, seg->ws_bytes, stream, status_or))) return rc;
-    if (seg->states && i == seg->count - 1) break;  // the kept segment ends with its grid
+    const bool last = i == seg->count - 1;
+    if (seg->states && last && !out) break;  // the segment ends with its grid
     dw_particles to = in;
-    if (seg->states) {
+    if (seg->states && !last) {
       bind_state(&to, seg->states + (size_t)i * 24 * in.n);
     } else {
       to.x = out->x;

@@ -182,3 +182,40 @@ def test_rollout_loop_matches_single_calls(res, nw, ckpt, n_sub, K, det, R):
     ref = torch.autograd.grad(rollout(plan, *leaves), leaves, [torch.zeros_like(c) if k != 1 else c for k, c in enumerate(cot)])
     for a, b in zip(got, ref):
         assert ((a.double() - b.double()).norm() <= 1e-5 * b.double().norm()).item()
+
+
+@pytest.mark.parametrize("ckpt,n_sub", [(4, 7), (4, 3), (1, 2)])
+def test_rollout_kept_segment(ckpt, n_sub):
+    """The forward leaves its last segment for the backward: gradients are the
+    same (deterministic mode: equal) whether it is still there, another rollout
+    of the plan has replaced it, or a first backward has used it up; a rollout
+    without gradient leaves it alone."""
+    say(f"rollout kept segment ckpt={ckpt} n_sub={n_sub}")
+    rng = np.random.default_rng(ckpt + n_sub)
+    n, res, nw = 700, 16, 4
+    dev = dict(dtype=torch.float32, device=DEV)
+    plan = RolloutPlan(dict(nx=res, ny=res, nz=res, dx=1.0 / res, origin=(0.0, 0.0, 0.0)), n, torch.full((n,), 1.0 / n, **dev),
+                       torch.full((n,), 1.0 / n, **dev), torch.zeros(n, dtype=torch.int32, device=DEV),
+                       torch.tensor([0.3], **dev), None, 1e-3, (0.0, -2.0, 0.0), api.FIXED_COROTATED, 2, (nw,) * 3,
+                       (0, 0, 0), (1, 1, 1), 1, n_sub, ckpt, deterministic=True)
+    W = torch.as_tensor(2.0 * rng.standard_normal((1, 3, nw ** 3))).float().to(DEV)
+    cot = [torch.as_tensor(rng.standard_normal((k, n))).float().to(DEV) for k in (3, 3, 9, 9)]
+
+    def leaves(k):
+        x = torch.as_tensor(np.random.default_rng(k).random((3, n)) * 0.4 + 0.3).float().to(DEV)
+        z3, z9 = torch.zeros(3, n, **dev), torch.zeros(9, n, **dev)
+        return [t.clone().requires_grad_(True) for t in (W, torch.tensor([40.0], **dev), x, z3, z9, z9)]
+
+    la, lb = leaves(1), leaves(2)
+    want = [torch.autograd.grad(rollout(plan, *l), l, cot) for l in (la, lb)]
+    a = rollout(plan, *la)
+    b = rollout(plan, *lb)
+    same = lambda x, y: all(torch.equal(p, q) for p, q in zip(x, y))  # noqa: E731
+    assert same(torch.autograd.grad(b, lb, cot, retain_graph=True), want[1])
+    assert same(torch.autograd.grad(a, la, cot, retain_graph=True), want[0])
+    assert same(torch.autograd.grad(b, lb, cot), want[1])
+    c = rollout(plan, *la)
+    with torch.no_grad():
+        rollout(plan, *lb)
+    rollout(plan, *[t.detach() for t in lb])
+    assert same(torch.autograd.grad(c, la, cot), want[0])
