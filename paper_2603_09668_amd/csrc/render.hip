@@ -33,7 +33,9 @@
 // symmetric).  Loss partial sums are reduced in a fixed order.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
+#include <utility>
 
 #include "dw_internal.h"
 
@@ -46,7 +48,7 @@ constexpr int GS_THREADS = 256;
 // [6] e dx dy, [7] e dy^2, [8] e dy
 constexpr int GS_NB = 9;
 constexpr int RS_THREADS = 256;
-constexpr int RS_ROUNDS = 16, RS_SHORT = 4;       // keys per thread, large and small inputs
+constexpr int RS_ROUNDS = 16;                     // keys per thread of large inputs (small ones: 4 or 8)
 constexpr int RS_CHUNK = RS_THREADS * RS_ROUNDS;  // keys per radix-sort block (at most)
 constexpr int RS_DIRECT = 64;                     // blocks whose histograms a block adds up by itself
 constexpr int SCAN_THREADS = 256;
@@ -105,6 +107,10 @@ struct GsWs {
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 static int64_t rs_blocks(int64_t m) { return (m + RS_CHUNK - 1) / RS_CHUNK; }
+
+// rows of 256 counters that radix_sort has: the histograms of RS_CHUNK blocks,
+// and bsum behind them, which only passes of more than RS_DIRECT blocks use
+static int64_t rs_rows(int64_t n, int64_t P) { return rs_blocks(n > P ? n : P) + SCAN_TOP_MAX / 256; }
 
 static GsWs gs_layout(char *base, int64_t n, int64_t P, int W, int H) {
   GsWs w;
@@ -381,9 +387,10 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_gs_cnt_scan(int n, const int32
 // equal digits.  Keys of equal digit keep their input order, so the passes
 // compose to a stable sort.
 // Bound by latency for small inputs and by the 16 bytes moved per key and
-// pass for large ones.  A pass over 20k keys 31 -> 10 us, over 1M 39 -> 25
-// us; the two tile passes of 5.7M pairs 190 -> 76 us (before: three barriers
-// per round of 256 keys, stores scattered key by key, three scan kernels).
+// pass for large ones; the histograms are therefore added up 32 loads at a
+// time.  A pass over 20k keys 31 -> 8.5 us, over 256k 16, over 1M 39 -> 22 us;
+// the two tile passes of 5.7M pairs 190 -> 76 us (before: three barriers per
+// round of 256 keys, stores scattered key by key, three scan kernels).
 
 template <int ROUNDS>
 __global__ __launch_bounds__(RS_THREADS) void k_rs_hist(const uint32_t *__restrict__ key, int64_t m_cap,
@@ -472,11 +479,15 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(const uint32_t *__res
   const int nblk = (int)((m + CHUNK - 1) / CHUNK);
   int before = 0, all = 0;
   if (nblk <= RS_DIRECT) {
-#pragma unroll 8
-    for (int q = 0; q < nblk; ++q) {
-      const int c = hist[(int64_t)q * 256 + threadIdx.x];
-      all += c;
-      before += q < (int)blockIdx.x ? c : 0;
+    for (int q0 = 0; q0 < nblk; q0 += 32) {
+      int c[32];
+#pragma unroll
+      for (int e = 0; e < 32; ++e) c[e] = hist[(int64_t)min(q0 + e, nblk - 1) * 256 + threadIdx.x];
+#pragma unroll
+      for (int e = 0; e < 32; ++e) {
+        all += q0 + e < nblk ? c[e] : 0;
+        before += q0 + e < (int)blockIdx.x ? c[e] : 0;
+      }
     }
   } else {
     before = hist[(int64_t)blockIdx.x * 256 + threadIdx.x];
@@ -556,39 +567,41 @@ static void rs_scatter(int w, unsigned g, hipStream_t s, const uint32_t *kin, co
                      total, kout, vout);
 }
 
+template <int ROUNDS>
+static void radix_passes(uint32_t **ka, int32_t **va, uint32_t **kb, int32_t **vb, int64_t m_cap, const int32_t *m_dev,
+                         int bits, bool have_hist, int32_t *hist, int32_t *total, hipStream_t s) {
+  const int w = rs_digit(bits) < 4 ? 4 : rs_digit(bits);  // digits below 4 bits: the key bits above are zero
+  const unsigned g = grid_blocks(m_cap, RS_THREADS * ROUNDS);
+  for (int p = 0; p < rs_passes(bits); ++p) {
+    const int shift = p * w;
+    if (p > 0 || !have_hist)
+      hipLaunchKernelGGL(k_rs_hist<ROUNDS>, dim3(g), dim3(RS_THREADS), 0, s, *ka, m_cap, m_dev, shift, (1u << w) - 1u,
+                         hist);
+    if (g > RS_DIRECT)
+      hipLaunchKernelGGL(k_rs_scan, dim3((1u << w) / 16), dim3(1024), 0, s, m_cap, m_dev, hist, total);
+    rs_scatter<ROUNDS>(w, g, s, *ka, *va, m_cap, m_dev, shift, hist, total, *kb, *vb);
+    std::swap(*ka, *kb);
+    std::swap(*va, *vb);
+  }
+}
+
 // Sorts (key, value) pairs by key bits [0, bits) stably; the result ends in
 // *ka / *va (the pointers are swapped when it lands in the second buffer).
 // have_hist: hist already holds the first pass's histograms (blocks of
-// RS_CHUNK keys).  Inputs of up to RS_DIRECT short blocks are cut into short
-// ones: their passes are a chain of latencies that four rounds make shorter
-// (20k keys: 13 -> 8 us).
+// RS_CHUNK keys).  Inputs are cut into blocks of the fewest rounds (4, 8) that
+// make at most RS_DIRECT blocks and fit the rows: their passes are a chain of
+// latencies that few rounds make shorter and more blocks spread over the chip
+// (a depth pass of 20k keys 13 -> 8 us; at 256k keys 125 blocks of eight rounds
+// gain 1 of 16 us).
 static void radix_sort(uint32_t **ka, int32_t **va, uint32_t **kb, int32_t **vb, int64_t m_cap, const int32_t *m_dev,
-                       int bits, bool have_hist, int32_t *hist, int32_t *total, hipStream_t s) {
-  const int w = rs_digit(bits) < 4 ? 4 : rs_digit(bits);  // digits below 4 bits: the key bits above are zero
-  const bool brief = !have_hist && m_cap <= RS_DIRECT * RS_THREADS * RS_SHORT;
-  const int64_t chunk = brief ? RS_THREADS * RS_SHORT : RS_CHUNK;
-  const int64_t nb = (m_cap + chunk - 1) / chunk;
-  const unsigned g = (unsigned)(nb < 1 ? 1 : nb);
-  for (int p = 0; p < rs_passes(bits); ++p) {
-    const int shift = p * w;
-    const uint32_t mask = (1u << w) - 1u;
-    if (p == 0 && have_hist) {
-    } else if (brief) {
-      hipLaunchKernelGGL(k_rs_hist<RS_SHORT>, dim3(g), dim3(RS_THREADS), 0, s, *ka, m_cap, m_dev, shift, mask, hist);
-    } else {
-      hipLaunchKernelGGL(k_rs_hist<RS_ROUNDS>, dim3(g), dim3(RS_THREADS), 0, s, *ka, m_cap, m_dev, shift, mask, hist);
-    }
-    if (nb > RS_DIRECT)
-      hipLaunchKernelGGL(k_rs_scan, dim3((1u << w) / 16), dim3(1024), 0, s, m_cap, m_dev, hist, total);
-    if (brief) rs_scatter<RS_SHORT>(w, g, s, *ka, *va, m_cap, m_dev, shift, hist, total, *kb, *vb);
-    else rs_scatter<RS_ROUNDS>(w, g, s, *ka, *va, m_cap, m_dev, shift, hist, total, *kb, *vb);
-    uint32_t *tk = *ka;
-    *ka = *kb;
-    *kb = tk;
-    int32_t *tv = *va;
-    *va = *vb;
-    *vb = tv;
-  }
+                       int bits, bool have_hist, int32_t *hist, int64_t rows, int32_t *total, hipStream_t s) {
+  const int64_t most = have_hist ? 0 : std::min<int64_t>(RS_DIRECT, rows);
+  if (grid_blocks(m_cap, RS_THREADS * 4) <= most)
+    radix_passes<4>(ka, va, kb, vb, m_cap, m_dev, bits, have_hist, hist, total, s);
+  else if (grid_blocks(m_cap, RS_THREADS * 8) <= most)
+    radix_passes<8>(ka, va, kb, vb, m_cap, m_dev, bits, have_hist, hist, total, s);
+  else
+    radix_passes<RS_ROUNDS>(ka, va, kb, vb, m_cap, m_dev, bits, have_hist, hist, total, s);
 }
 
 // ---------------------------------------------------------- tile binning
@@ -1685,7 +1698,7 @@ extern "C" int gs_render(const dw_camera *cam, int n, const float *mu, const flo
     hipLaunchKernelGGL(k_gs_project, dim3(grid_blocks(n, 256)), dim3(256), 0, s, K, n, mu, sigma, color, opacity, w);
     uint32_t *ka = w.key_a, *kb = w.key_b;
     int32_t *va = w.id_a, *vb = w.id_b;
-    radix_sort(&ka, &va, &kb, &vb, n, nullptr, 32, false, w.hist, w.bsum, s);  // 4 passes: back in buffer a
+    radix_sort(&ka, &va, &kb, &vb, n, nullptr, 32, false, w.hist, rs_rows(n, max_pairs), w.bsum, s);  // 4 passes: back in buffer a
     const unsigned nsc = grid_blocks(n, SCAN_CHUNK);
     hipLaunchKernelGGL(k_gs_cnt_sums, dim3(nsc), dim3(SCAN_THREADS), 0, s, n, va, w.cnt, w.off, w.bsum);
     hipLaunchKernelGGL(k_gs_cnt_scan, dim3(nsc), dim3(SCAN_THREADS), 0, s, n, w.bsum, max_pairs, w.off, w.hdr);
@@ -1695,7 +1708,7 @@ extern "C" int gs_render(const dw_camera *cam, int n, const float *mu, const flo
                          w.hdr, (1u << w0) - 1u, w.pk_a, w.pv_a, w.hist);
       uint32_t *pa = w.pk_a, *pb = w.pk_b;
       int32_t *qa = w.pv_a, *qb = w.pv_b;
-      radix_sort(&pa, &qa, &pb, &qb, max_pairs, w.hdr + 1, bits, true, w.hist, w.bsum, s);
+      radix_sort(&pa, &qa, &pb, &qb, max_pairs, w.hdr + 1, bits, true, w.hist, rs_rows(n, max_pairs), w.bsum, s);
       hipLaunchKernelGGL(k_gs_ranges, dim3(grid_blocks(max_pairs < 8 * (int64_t)n ? max_pairs : 8 * (int64_t)n, 1024)),
                          dim3(256), 0, s, pa, w.hdr, w.range);
     }

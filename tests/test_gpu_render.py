@@ -406,10 +406,10 @@ def test_nonfinite_colour_stays_in_its_pixels(n):
     assert torch.equal(imgs[2][~touched], imgs[0][~touched])
 
 
-@pytest.mark.parametrize("n", [1, 2, 1023, 1025, 65_536, 65_537, 262_144, 262_145])
+@pytest.mark.parametrize("n", [1, 2, 1023, 1025, 65_536, 65_537, 131_072, 131_073, 262_144, 262_145])
 def test_depth_and_tile_sort_sizes(n):
     """Kernel counts at the edges of the sort's blocks and of its ways to add
-    up histograms (64 short blocks, 64 long ones, more), with depths on 64
+    up histograms (64 blocks of 4, 8 and 16 rounds, more), with depths on 64
     levels only, so that most neighbours in the list are ties and the input
     order decides.  Sampled pixels against the oracle, bounds as above."""
     W, H = 150, 131
