@@ -24,7 +24,7 @@
 // entries x 4 pixels at a time.  With s_i = G . c_i (G the image gradient at
 // the pixel), dL/dalpha_i = T_i s_i - (G . C - P_i) / (1 - alpha_i) where
 // P_i = sum_{j <= i} T_j alpha_j s_j and C includes the background term.  The
-// sums over pixels run on the matrix cores; k_gs_project_adj takes the centre
+// sums over pixels are taken in registers; k_gs_project_adj takes the centre
 // and conic adjoints back to mu and Sigma through the projection.
 // Loss (render_loss): L1 and SSIM with an 11 x 11 Gaussian window
 // (sigma 1.5, zero padding) per channel; the five window sums are separable
@@ -1130,6 +1130,19 @@ __device__ __forceinline__ void row_scan_add4(float (&v)[4]) {
 __device__ __forceinline__ float row_below(float old, float v) { return dpp_mov<0x111>(old, v); }
 __device__ __forceinline__ float row_last(float v) { return dpp_mov<0x15F>(v, v); }
 
+// Sums of a, b, c, d over the four rows of 16 lanes: row 0 gets a's, row 1 c's,
+// row 2 b's, row 3 d's.  A swap exchanges half of one register with half of
+// another, so that one addition serves two values.
+__device__ __forceinline__ float swap32_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float row_sums(float a, float b, float c, float d) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(swap32_add(a, b)), __float_as_uint(swap32_add(c, d)),
+                                                  false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // 1 / m to about one rounding: the hardware reciprocal and a Newton step
 __device__ __forceinline__ float recip(float m) {
   const float r = __builtin_amdgcn_rcpf(m);
@@ -1144,12 +1157,10 @@ __device__ __forceinline__ float recip(float m) {
 // (for kernels of a few pixels about a fifth of the tile's list).  In a
 // quarter a wave has 4 x 4 pixels, in a whole tile 8 x 8 as four blocks per
 // group of entries; the pixels' state waits in LDS meanwhile.
-// An entry's sums over the pixel rows are taken in its lanes (the column's dx
-// is one number), those over the four columns by 16x16x4 fp32 MFMAs whose
-// second operand has just this layout (lane l: k = column l / 16, n = entry
-// l % 16) and whose first operand holds ones in one row: the accumulator
-// collects the nine values, value r of entry n in row r.  (Moments about a
-// block's centre, moved to the kernel afterwards, need one MFMA less and lose
+// An entry's sums over the pixel rows (the column's dx is one number) and over
+// a tile's four blocks are taken in its lanes, those over the four columns by
+// eight half-register swaps and additions.  (Moments about a
+// block's centre, moved to the kernel afterwards, need one sum less and lose
 // digits to cancellation where a kernel is smaller than a pixel.)  Every wave
 // leaves its sums in an LDS table of its own (an entry comes up once per wave
 // and batch: plain stores); for a whole tile the workgroup adds the tables of
@@ -1158,8 +1169,9 @@ __device__ __forceinline__ float recip(float m) {
 // took 375 us at 1M kernels and 1024^2 pixels, one global atomic per wave and
 // value 532 us.)
 // Against one wave per tile walking the list entry by entry: 256k kernels,
-// 512^2 3,016 -> 113 us, 20k 1,768 -> 49 us, 1M kernels, 1024^2 357 -> 220 us
-// (there the vector units are busy two thirds of the time).
+// 512^2 3,016 -> 108 us, 20k 1,768 -> 48 us, 1M kernels, 1024^2 357 -> 175 us,
+// where the vector units are busy 84 % of the time (220 with nine MFMAs with
+// ones for the column sums of every block, 182 with nine per group).
 constexpr int GS_ADJ_N = 128;  // list entries per batch
 struct GsPixel {
   float T, P, G0, G1, G2, gC;
@@ -1181,10 +1193,6 @@ __global__ __launch_bounds__(GS_THREADS, 4) void k_gs_raster_adj(CamDev K, GsWs 
   const int e = lane & 15, g = lane >> 4;
   const int64_t HW = (int64_t)K.W * K.H;
   const int nsplit = w.hdr[3], items = 4 * nsplit + w.hdr[2];
-  // first operands: this lane's element of row e
-  float row[GS_NB];
-#pragma unroll
-  for (int v = 0; v < GS_NB; ++v) row[v] = e == v ? 1.f : 0.f;
   int it = blockIdx.x;
   while (it < items) {
     const GsItem t = gs_item(w, it, nsplit);
@@ -1233,7 +1241,9 @@ __global__ __launch_bounds__(GS_THREADS, 4) void k_gs_raster_adj(CamDev K, GsWs 
         const int j = has ? (int)s.list[wid][q + e] : 0;
         const GsRec r = gs_entry(s, j);
         const int idx = has ? first + j : INT_MAX;
-        gs_floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+        float m[GS_NB];  // the lane's sums over its pixels of all blocks
+#pragma unroll
+        for (int k = 0; k < GS_NB; ++k) m[k] = 0.f;
         for (int b = 0; b < nblk; ++b) {
           const int bx = lx + 4 * (b & 1), by = ly + 4 * (b >> 1);
           const float x0 = (float)(X0 + bx), y0 = (float)(Y0 + by);
@@ -1268,9 +1278,7 @@ __global__ __launch_bounds__(GS_THREADS, 4) void k_gs_raster_adj(CamDev K, GsWs 
           }
           row_scan_add4(v);
           const float dx = x - r.mx;
-          float m[GS_NB];
-#pragma unroll
-          for (int k = 0; k < GS_NB; ++k) m[k] = 0.f;
+          float d0 = 0.f, d1 = 0.f;  // sums of e and e dy
 #pragma unroll
           for (int p = 0; p < 4; ++p) {
             const float Pi = P[p] + v[p];
@@ -1279,28 +1287,30 @@ __global__ __launch_bounds__(GS_THREADS, 4) void k_gs_raster_adj(CamDev K, GsWs 
             const float de = on[p] ? dal * ex[p] : 0.f, dy = y + (float)p - r.my;
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) m[ch] += wg[p] * G[p][ch];
-            m[3] += de;
-            m[8] += de * dy;
+            d0 += de;
+            d1 += de * dy;
             m[7] += de * dy * dy;
           }
-          m[4] = m[3] * dx;
-          m[5] = m[4] * dx;
-          m[6] = m[8] * dx;
+          m[3] += d0;
+          m[4] += d0 * dx;
+          m[5] += d0 * dx * dx;
+          m[6] += d1 * dx;
+          m[8] += d1;
           if (e == 0) {
 #pragma unroll
             for (int p = 0; p < 4; ++p)
               *reinterpret_cast<float2 *>(&px[(by + p) * GS_TILE + bx + g]) = make_float2(T[p], P[p]);
           }
-#pragma unroll
-          for (int k = 0; k < GS_NB; ++k)
-            sum = __builtin_amdgcn_mfma_f32_16x16x4f32(row[k], m[k], sum, 0, 0, 0);
         }
-        // lane: values 4 g .. 4 g + 3 of entry e
+        // sums over the four columns: value at[k] of the lane's entry
+        const float low = row_sums(m[0], m[1], m[2], m[3]), high = row_sums(m[4], m[5], m[6], m[7]),
+                    top = row_sums(m[8], 0.f, 0.f, 0.f);
+        const int at = ((g & 1) << 1) | (g >> 1);
         float *dst = s_sum[wid] + (whole ? j : e) * GS_NB;
         if (has || !whole) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k)
-            if (4 * g + k < GS_NB) dst[4 * g + k] = sum[k];
+          dst[at] = low;
+          dst[4 + at] = high;
+          if (g == 0) dst[8] = top;
         }
         if (!whole) {
           // few waves meet an entry: straight to memory, 64 consecutive of the
