@@ -69,14 +69,24 @@ struct ConvGeom {
 //    layer's field) is requested ahead of the MFMAs too, so that one wait per
 //    tile is all that memory costs; with copies that the compiler waited for
 //    and gates read in the epilogue, 16 x 64^3 voxels took 220 (32 -> 32), 150
-//    (32 -> 3) and 322 us (data gradient), now 200, 118 and 226.  The matrix
-//    cores need 92 us of the first at 2.4 GHz, the memory 55 of the second and
-//    160 of the third.  Wave w computes a
+//    (32 -> 3) and 322 us (data gradient), then 200, 118 and 226.  The matrix
+//    cores need 92 us of the first at 2.4 GHz, the memory 160 of the third.
+//    Wave w computes a
 //    4 (y) x RZ (z) block of output rows for one 16-channel m-tile, holding
 //    that m-tile's 27 weight fragments in registers for the life of the
 //    kernel.  For each x-shift it walks the (RZ+2) x 6 input rows; every
 //    fragment read from LDS feeds up to 3 RZ MFMAs (all (dz, dy) taps that
 //    map it onto an output row).
+//    The 3-channel output layer would leave 13 of the 16 rows of a weight
+//    fragment empty: its rows are 3 x taps x 4 (3 channels and a zero) instead,
+//    so a (dz, dy) pair costs one MFMA per row, not three, and a row's
+//    fragment is read once.  Lane row dx then holds the products of tap dx at
+//    the row's own voxels; the epilogue shifts them by a voxel and adds the
+//    lane rows, each of which ends up with one output row.  What the taps need
+//    from the voxels beside the 16 is one more fragment, of the four output
+//    rows' ends, per (dz, dy).  45 MFMAs and 27 reads instead of 108 and 54
+//    for 64 voxels: 256 x 128 x 128 voxels 116 -> 94 us, of which the memory
+//    needs 73.
 //  * 8-channel inputs (3 channels padded): tiles of FX x FY x FZ = 16 x 4 x 8
 //    outputs, one patch per tile; K = 32 spans 4 taps; each wave computes 8
 //    whole rows, all m-tiles, two rows at a time, and stores whole voxels
@@ -240,10 +250,8 @@ __device__ __forceinline__ ColItem col_item(const FwdTiles &T, int v) {
 // (ragged edge tiles).  Per-field bases plus 32-bit element offsets.
 template <int COUTP, int EPI>
 __device__ __forceinline__ void conv_epilogue(const ConvGeom &G, const TileOrigin &o, bool live, uint32_t vi,
-                                              int co0, floatx4 acc, const float *s_bias, int cout,
-                                              uint16_t *__restrict__ y, uint16_t *__restrict__ zpre,
-                                              uint2 zg, const float *__restrict__ u, float sb,
-                                              float *__restrict__ u_out) {
+                                              int co0, floatx4 acc, const float *s_bias,
+                                              uint16_t *__restrict__ y, uint16_t *__restrict__ zpre, uint2 zg) {
   if (!live) return;
   const uint32_t ei = vi * COUTP + co0;  // element offset in the field's activations
   const size_t fb = (size_t)o.b * G.L * COUTP;
@@ -253,17 +261,6 @@ __device__ __forceinline__ void conv_epilogue(const ConvGeom &G, const TileOrigi
     for (int j = 0; j < 4; ++j) zv[j] = acc[j] + s_bias[co0 + j];
     *reinterpret_cast<uint2 *>(y + fb + ei) = make_uint2(f2bf2(silu(zv[0]), silu(zv[1])), f2bf2(silu(zv[2]), silu(zv[3])));
     if (zpre) *reinterpret_cast<uint2 *>(zpre + fb + ei) = make_uint2(f2bf2(zv[0], zv[1]), f2bf2(zv[2], zv[3]));
-  } else if (EPI == DW_CONV_OUTPUT) {
-    const size_t ub = (size_t)o.b * cout * G.L;
-    const uint32_t L = (uint32_t)G.L;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int co = co0 + j;
-      if (co < cout) {
-        const uint32_t ui = (uint32_t)co * L + vi;
-        u_out[ub + ui] = u[ub + ui] + sb * (acc[j] + s_bias[co]);
-      }
-    }
   } else {  // DW_CONV_DGRAD: gradient through the previous layer's silu
     const float zf[4] = {bf2f((uint16_t)(zg.x & 0xffff)), bf2f((uint16_t)(zg.x >> 16)), bf2f((uint16_t)(zg.y & 0xffff)),
                          bf2f((uint16_t)(zg.y >> 16))};
@@ -310,6 +307,39 @@ __device__ __forceinline__ void wide_epilogue(uint32_t vi, int g, const floatx4 
   *reinterpret_cast<uint4 *>(y + ei) = make_uint4(out[0], out[1], out[2], out[3]);
 }
 
+// `x` of the lane that DPP control `CTRL` names, in the rows of 16 lanes of
+// `ROWS`; `old` in the others and where that lane is outside the row
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp(float old, float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(x), CTRL, ROWS, 0xf, false));
+}
+constexpr int DPP_SHL = 0x100, DPP_SHR = 0x110, DPP_SAME = 0xe4;
+
+// a and b summed over the rows of 16 lanes: first over rows two apart (a in
+// the lower half, b in the upper), then over adjacent ones (a in the even
+// rows, b in the odd)
+__device__ __forceinline__ float halves_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float quarters_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Output layer: the three x taps of output row YO, channel sums v (lane row dx
+// = the products of tap dx at the row's own voxels) and e (the same at the two
+// voxels beside the row: lane YO left of it, lane 12 + YO right of it), moved
+// to the voxel they belong to.  Lane row 3 holds no tap.
+template <int YO>
+__device__ __forceinline__ float x_taps(int g, float v, float e) {
+  float t = dpp<YO ? DPP_SHL + YO : DPP_SAME, 1>(v, e);
+  t = dpp<YO < 3 ? DPP_SHR + 3 - YO : DPP_SAME, 4>(t, e);
+  t = dpp<DPP_SHR + 1, 1>(t, v);
+  t = dpp<DPP_SHL + 1, 4>(t, v);
+  return g < 3 ? t : 0.f;
+}
+
 // Packed weights: [chunk][COUTP][32] bf16, see conv_pack_weights.
 template <int CINP, int COUTP, int EPI>
 __global__ __launch_bounds__(256, CINP == 32 ? 2 : 4) void k_conv(ConvGeom G, FwdTiles T, const uint16_t *__restrict__ x,
@@ -327,14 +357,25 @@ __global__ __launch_bounds__(256, CINP == 32 ? 2 : 4) void k_conv(ConvGeom G, Fw
   if (threadIdx.x < 32) s_bias[threadIdx.x] = (bias && (int)threadIdx.x < cout) ? bias[threadIdx.x] : 0.f;
 
   if constexpr (CINP == 32) {
+    constexpr bool OUT = EPI == DW_CONV_OUTPUT;
+    static_assert(OUT ? MT == 1 : MT == 2, "32 or 3 output channels");
     // wave -> (m-tile, z rows of the 16 x 4 x 4 tile)
-    constexpr int RZ = MT == 2 ? 2 : 1;
-    const int mt = MT == 2 ? (wid & 1) : 0;
-    const int zb = MT == 2 ? (wid >> 1) * 2 : wid;
-    bf16x8 wf[27];
+    constexpr int RZ = OUT ? 1 : 2;
+    const int mt = OUT ? 0 : (wid & 1);
+    const int zb = OUT ? wid : (wid >> 1) * 2;
+    bf16x8 wf[OUT ? 9 : 27];
+    if constexpr (OUT) {
+      // row 4 dx + co of a fragment: x tap dx, output channel co
 #pragma unroll
-    for (int tap = 0; tap < 27; ++tap)
-      wf[tap] = *reinterpret_cast<const bf16x8 *>(wk + ((tap * COUTP + mt * 16 + r16) * 32 + g * 8));
+      for (int tap = 0; tap < 9; ++tap)
+        wf[tap] = r16 < 12 ? *reinterpret_cast<const bf16x8 *>(
+                                 wk + (((3 * tap + (r16 >> 2)) * COUTP + (r16 & 3)) * 32 + g * 8))
+                           : bf16x8{};
+    } else {
+#pragma unroll
+      for (int tap = 0; tap < 27; ++tap)
+        wf[tap] = *reinterpret_cast<const bf16x8 *>(wk + ((tap * COUTP + mt * 16 + r16) * 32 + g * 8));
+    }
     // Work items in an order that gives the workgroups of one XCD (dispatch
     // is round-robin over the 8 XCDs) neighbouring columns, so the x and y
     // halos of concurrent tiles meet in one L2.  A column is walked along z
@@ -350,8 +391,8 @@ __global__ __launch_bounds__(256, CINP == 32 ? 2 : 4) void k_conv(ConvGeom G, Fw
       ci = col_item(T, v);
       zt = ci.zt0;
     }
-    floatx4 acc[RZ][FY];
-    float uin[RZ][FY][3];
+    floatx4 acc[RZ][FY], edge;
+    float uin[3];
     uint2 zin[RZ][FY];
     uint32_t off[PCH];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_bytes_t)s_in;
@@ -361,27 +402,28 @@ __global__ __launch_bounds__(256, CINP == 32 ? 2 : 4) void k_conv(ConvGeom G, Fw
       const int gx = oe.x0 + r16;
       const uint32_t sy = (uint32_t)G.nx, sz = (uint32_t)G.nx * (uint32_t)G.ny;
       const uint32_t v00 = (uint32_t)gx + sy * (uint32_t)oe.y0 + sz * (uint32_t)(oe.z0 + zb);
-      const float sb = EPI == DW_CONV_OUTPUT ? scale[oe.b] : 0.f;
+      if constexpr (OUT) {
+        // u_{t+k} = u_t + s (sum + bias): lane row yo gets output row yo
+        const float sb = scale[oe.b];
+        const bool live = gx < G.nx && oe.y0 + g < G.ny && oe.z0 + zb < G.nz;
+        const size_t ub = (size_t)oe.b * 3 * G.L;
 #pragma unroll
-      for (int zo = 0; zo < RZ; ++zo)
-#pragma unroll
-        for (int yo = 0; yo < FY; ++yo) {
-          const bool live = gx < G.nx && oe.y0 + yo < G.ny && oe.z0 + zb + zo < G.nz;
-          if constexpr (EPI == DW_CONV_OUTPUT) {
-            // u_{t+k} = u_t + s (acc + bias), channels 0 .. cout-1 held by the lanes of group 0
-            if (live && g == 0) {
-              const size_t ub = (size_t)oe.b * cout * G.L;
-              const uint32_t L = (uint32_t)G.L;
-#pragma unroll
-              for (int j = 0; j < 3; ++j)
-                if (j < cout)
-                  u_out[ub + (uint32_t)j * L + v00 + yo * sy + zo * sz] = uin[zo][yo][j] + sb * (acc[zo][yo][j] + s_bias[j]);
-            }
-          } else {
-            conv_epilogue<COUTP, EPI>(G, oe, live, v00 + yo * sy + zo * sz, mt * 16 + 4 * g, acc[zo][yo], s_bias,
-                                      cout, y, zpre, zin[zo][yo], u, sb, u_out);
-          }
+        for (int j = 0; j < 3; ++j) {
+          const float s02 = halves_add(x_taps<0>(g, acc[0][0][j], edge[j]), x_taps<2>(g, acc[0][2][j], edge[j])),
+                      s13 = halves_add(x_taps<1>(g, acc[0][1][j], edge[j]), x_taps<3>(g, acc[0][3][j], edge[j]));
+          const float sum = quarters_add(s02, s13);
+          if (live) u_out[ub + (uint32_t)j * (uint32_t)G.L + v00 + g * sy] = uin[j] + sb * (sum + s_bias[j]);
         }
+      } else {
+#pragma unroll
+        for (int zo = 0; zo < RZ; ++zo)
+#pragma unroll
+          for (int yo = 0; yo < FY; ++yo) {
+            const bool live = gx < G.nx && oe.y0 + yo < G.ny && oe.z0 + zb + zo < G.nz;
+            conv_epilogue<COUTP, EPI>(G, oe, live, v00 + yo * sy + zo * sz, mt * 16 + 4 * g, acc[zo][yo], s_bias, y,
+                                      zpre, zin[zo][yo]);
+          }
+      }
     };
     while (v < T.nitems) {
       const TileOrigin o{ci.b, ci.x0, ci.y0, zt * CZ};
@@ -421,33 +463,33 @@ __global__ __launch_bounds__(256, CINP == 32 ? 2 : 4) void k_conv(ConvGeom G, Fw
             zin[zo][yo] = live ? *reinterpret_cast<const uint2 *>(zf + (v00 + yo * sy + zo * sz) * COUTP) : uint2{};
           }
       }
-      if constexpr (EPI == DW_CONV_OUTPUT) {
+      if constexpr (OUT) {
         const int gx = o.x0 + r16;
         const uint32_t sy = (uint32_t)G.nx, sz = (uint32_t)G.nx * (uint32_t)G.ny;
-        const uint32_t v00 = (uint32_t)gx + sy * (uint32_t)o.y0 + sz * (uint32_t)(o.z0 + zb);
-        const size_t ub = (size_t)o.b * cout * G.L;
-        const uint32_t L = (uint32_t)G.L;
+        const uint32_t v00 = (uint32_t)gx + sy * (uint32_t)(o.y0 + g) + sz * (uint32_t)(o.z0 + zb);
+        const bool live = gx < G.nx && o.y0 + g < G.ny && o.z0 + zb < G.nz;
 #pragma unroll
-        for (int zo = 0; zo < RZ; ++zo)
-#pragma unroll
-          for (int yo = 0; yo < FY; ++yo) {
-            const bool live = g == 0 && gx < G.nx && o.y0 + yo < G.ny && o.z0 + zb + zo < G.nz;
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-              uin[zo][yo][j] = (live && j < cout) ? u[ub + (uint32_t)j * L + v00 + yo * sy + zo * sz] : 0.f;
-          }
+        for (int j = 0; j < 3; ++j) uin[j] = live ? u[(size_t)o.b * 3 * G.L + (uint32_t)j * (uint32_t)G.L + v00] : 0.f;
       }
 #pragma unroll
       for (int zo = 0; zo < RZ; ++zo)
 #pragma unroll
         for (int yo = 0; yo < FY; ++yo) acc[zo][yo] = floatx4{0.f, 0.f, 0.f, 0.f};
-      // lane's fragment offset per x-shift; every read below adds a constant.
-      // The empty asm keeps the compiler from hoisting 108 precomputed
-      // addresses out of the tile loop (which costs 108 registers).
-      int base[3];
+      // lane's fragment offset per x-shift (output layer: at the row's own
+      // voxels, and at the voxels beside rows 0 .. 3); every read below adds a
+      // constant.  The empty asm keeps the compiler from hoisting 108
+      // precomputed addresses out of the tile loop (which costs 108 registers).
+      int base[OUT ? 2 : 3];
+      if constexpr (OUT) {
+        const int xe = r16 < 8 ? 0 : QX - 1;
+        base[0] = (r16 + 1) * 32 + (g ^ swz(r16 + 1)) * 8;
+        base[1] = (xe + QX * (r16 & 3)) * 32 + (g ^ swz(xe)) * 8;
+        asm volatile("" : "+v"(base[0]), "+v"(base[1]));
+      } else {
 #pragma unroll
-      for (int dx = 0; dx < 3; ++dx) base[dx] = (r16 + dx) * 32 + (g ^ swz(r16 + dx)) * 8;
-      asm volatile("" : "+v"(base[0]), "+v"(base[1]), "+v"(base[2]));
+        for (int dx = 0; dx < 3; ++dx) base[dx] = (r16 + dx) * 32 + (g ^ swz(r16 + dx)) * 8;
+        asm volatile("" : "+v"(base[0]), "+v"(base[1]), "+v"(base[2]));
+      }
       // LDS offset of the slot that holds patch plane zb + zi
       int poff[RZ + 2];
 #pragma unroll
@@ -455,29 +497,51 @@ __global__ __launch_bounds__(256, CINP == 32 ? 2 : 4) void k_conv(ConvGeom G, Fw
         const int sl = rot + zb + zi;
         poff[zi] = (sl >= RING ? sl - RING : sl) * CPLANE;
       }
+      if constexpr (OUT) {
+        edge = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int dx = 0; dx < 3; ++dx) {
-#pragma unroll
-        for (int zi = 0; zi < RZ + 2; ++zi) {
-          // the row's six fragments are read together, so their LDS latency
-          // overlaps instead of stalling the matrix core per fragment
-          bf16x8 bfr[QY];
+        for (int zi = 0; zi < 3; ++zi) {
+          bf16x8 bfr[QY], efr[3];
 #pragma unroll
           for (int yi = 0; yi < QY; ++yi)
-            bfr[yi] = *reinterpret_cast<const bf16x8 *>(s_in + base[dx] + poff[zi] + QX * yi * 32);
-          __builtin_amdgcn_sched_barrier(0);  // keep the six reads ahead of the MFMAs
+            bfr[yi] = *reinterpret_cast<const bf16x8 *>(s_in + base[0] + poff[zi] + QX * yi * 32);
 #pragma unroll
-          for (int yi = 0; yi < QY; ++yi) {
+          for (int dy = 0; dy < 3; ++dy)
+            efr[dy] = *reinterpret_cast<const bf16x8 *>(s_in + base[1] + poff[zi] + QX * dy * 32);
+          __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the MFMAs
 #pragma unroll
-            for (int dz = 0; dz < 3; ++dz) {
-              const int zo = zi - dz;
-              if (zo < 0 || zo >= RZ) continue;
+          for (int dy = 0; dy < 3; ++dy) {
 #pragma unroll
-              for (int dy = 0; dy < 3; ++dy) {
-                const int yo = yi - dy;
-                if (yo < 0 || yo >= FY) continue;
-                acc[zo][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[9 * dz + 3 * dy + dx], bfr[yi],
-                                                                      acc[zo][yo], 0, 0, 0);
+            for (int yo = 0; yo < FY; ++yo)
+              acc[0][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[3 * zi + dy], bfr[yo + dy], acc[0][yo], 0, 0, 0);
+            edge = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[3 * zi + dy], efr[dy], edge, 0, 0, 0);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) {
+#pragma unroll
+          for (int zi = 0; zi < RZ + 2; ++zi) {
+            // the row's six fragments are read together, so their LDS latency
+            // overlaps instead of stalling the matrix core per fragment
+            bf16x8 bfr[QY];
+#pragma unroll
+            for (int yi = 0; yi < QY; ++yi)
+              bfr[yi] = *reinterpret_cast<const bf16x8 *>(s_in + base[dx] + poff[zi] + QX * yi * 32);
+            __builtin_amdgcn_sched_barrier(0);  // keep the six reads ahead of the MFMAs
+#pragma unroll
+            for (int yi = 0; yi < QY; ++yi) {
+#pragma unroll
+              for (int dz = 0; dz < 3; ++dz) {
+                const int zo = zi - dz;
+                if (zo < 0 || zo >= RZ) continue;
+#pragma unroll
+                for (int dy = 0; dy < 3; ++dy) {
+                  const int yo = yi - dy;
+                  if (yo < 0 || yo >= FY) continue;
+                  acc[zo][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[9 * dz + 3 * dy + dx], bfr[yi],
+                                                                        acc[zo][yo], 0, 0, 0);
+                }
               }
             }
           }
