@@ -291,8 +291,9 @@ constexpr int P2G_PER_CU = 1024 / P2G_THREADS;  // resident workgroups per compu
 
 // One workgroup (8 waves) per work item -- a chunk of at most WORK_CHUNK
 // sorted particles of one cell tile, so a dense tile is spread over several
-// workgroups.  The grid is as many workgroups as fit at once; each draws
-// items from a ticket counter until the list is done.  No float atomics in LDS:
+// workgroups.  The grid is as many workgroups as fit at once; each takes whole
+// rounds of the item list by its index and draws what is left from a ticket
+// counter.  No float atomics in LDS:
 // Pass A1: thread j takes the item's particle j, finds its cell in the tile
 //   (LDS histogram) and issues the loads of the rest of its state.
 // Pass B: exclusive scan of the 64 cell counts; cells cut into units.
@@ -775,8 +776,7 @@ namespace dw {
 
 constexpr int PERSISTENT_BLOCKS = 2048;
 
-// P2G grid: the workgroups that fit at once (two per compute unit), which
-// then draw work items from the ticket counter
+// P2G grid: the workgroups that fit at once (two per compute unit)
 static unsigned p2g_blocks() { return (unsigned)(P2G_PER_CU * cu_count()); }
 
 static PView make_pview(const dw_particles *p) {
